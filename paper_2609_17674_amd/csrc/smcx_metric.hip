@@ -6,18 +6,32 @@
 // the NUTS section of the paper asks for (the Hessian of the negative log
 // posterior; a uniform prior adds nothing inside its box).
 //
-// One wave owns one particle and walks the samples in steps of 8. Per step
-// each lane forms J at 4 samples for its coordinate in each block of 32
-// coordinates, in natural units (J~ = J * s with s = (1, w, w) for pulses and
-// (1, 1/T_obs, 1/T_obs^2, 1) for sinusoids, so every entry is of order one),
-// rounds them to FP16 and feeds them as both operands of
-// v_mfma_f32_32x32x8_f16: with A[i][k] held by lane i + 32 (k/4), element
-// k%4, and B[k][j] by lane j + 32 (k/4), a lane's own values are its row of
-// A and column of B, and D = J~_block_i^T J~_block_j. The FP32 accumulators
-// are flushed into the FP64 output after each window of 4096 samples (one
-// launch per window), each entry owned by one lane (read-add-write, no
+// A wave owns up to 32 components, those of one particle or of several small
+// ones (metric_group_kernel packs them), and walks the samples in steps of 8.
+// Lane l stands for component row l % 32 and per step forms the P partials of
+// its component at four samples, in natural units (J~ = J * s with s =
+// (1, w, w) for pulses and (1, 1/T_obs, 1/T_obs^2, 1) for sinusoids, so every
+// entry is of order one), so that the exponential or the phase of a component
+// is taken once per sample and not once per parameter. The values are rounded
+// to FP16 and feed both operands of v_mfma_f32_32x32x8_f16, one product per
+// pair of parameters (6 for pulses, 10 for sinusoids): with A[i][k] held by
+// lane i + 32 (k/4), element k%4, and B[k][j] by lane j + 32 (k/4), a lane's
+// own values of parameter p are its row of A and those of p' its column of
+// B, and D_pp' = J~_p^T J~_p' over the wave's rows; the entries between rows
+// of different particles are dropped. The FP32 accumulators
+// are flushed into the FP64 output after each window of 4096 samples, each
+// entry owned by one lane and the windows in order (read-add-write, no
 // atomics), so the result is deterministic; entries
 // below the diagonal are written as copies of those above it.
+// Few particles, and k_max P > 64, take the coordinate form instead: one wave
+// per particle, lanes over its coordinates k P + p in NB blocks of 32,
+// NB (NB + 1) / 2 products per step; see launch_metric for where the line lies.
+// What bounds the grouped form: per step about 205 cycles of vector work (8 of
+// the 41 instructions are the conversions, 9 cycles each) beside 6 x 32 of the
+// matrix cores, overlapped to about 300 at three waves per SIMD. Measured on
+// 16384 pulse particles, K uniform on 0..20, T = 4096, dense blocks: 0.50 ms
+// against 1.30-1.36 ms for the coordinate form; sinusoids, 8000 particles,
+// K on 0..16, T = 4096: 0.47 against 1.03 ms.
 // Error: FP16 rounding of J~ (2^-11 relative) bounds |dF~_ac| by about
 // 2^-10 sqrt(F~_aa F~_cc), plus FP32 accumulation over 512 steps.
 #include "smcx_internal.h"
@@ -49,12 +63,401 @@ struct MetricArgs {
   int64_t f_size;  // entries of F: every block must fit
   double* F;
   int* flag;
-  int64_t w0, w1;  // sample window of this launch; the first window writes F, later ones add
-  int tempered;    // 1: the window's samples carry beta_i (0: before a bridge split)
+  int64_t w0, w1;  // coordinate form: the sample window of this launch; the first window
+                   // writes F, later ones add
+  int tempered;    // coordinate form: 1: the window's samples carry beta_i (0: before a
+                   // bridge split)
   int blocks;      // 1: only each component's P x P block, at F + m P P (source row m)
   const uint8_t* mask;  // [N] or nullptr: particles with mask[i] == 0 get zero blocks
+  int64_t split;   // samples before it carry weight 1, later ones beta_i
+  MetricWork work; // groups of particles (metric_group_kernel)
+  int nblk;        // blocks of kGroupBlock particles
 };
 
+// Whether particle i's rows, and its output block, are as they should be; its
+// components in K, its block's start in fo. Raises the flag if not.
+__device__ __forceinline__ bool metric_particle(const MetricArgs& a, int64_t i, int64_t& o0, int& K,
+                                                int64_t& fo, bool raise) {
+  o0 = a.offsets[i];
+  const int64_t o1 = a.offsets[i + 1];
+  bool ok = o0 >= 0 && o1 >= o0 && o1 <= a.M && o1 - o0 <= a.k_max;
+  K = ok ? (int)(o1 - o0) : 0;
+  const int64_t n = (int64_t)K * a.P;
+  fo = a.blocks ? o0 * a.P * a.P : a.f_offsets[i];
+  if (ok && !a.blocks)
+    ok = a.f_offsets[i + 1] - fo == n * n && fo >= 0 && fo + n * n <= a.f_size;
+  if (!ok && raise) atomicOr(a.flag, kFlagOffsets);
+  return ok;
+}
+
+// ---------------------------------------------------------------- groups
+// Packs the particles of each block of kGroupBlock into groups of at most 32
+// components, first-fit decreasing: a counting sort by K, then the wave opens
+// a group and keeps adding the largest particle that still fits. A group is
+// a range of perm (particle indices); block b's groups are the first cnt[b]
+// of its kGroupBlock slots. The placing is a serial chain per particle, which
+// is what the kernel's time is made of (22 us with blocks of 128 and LDS scans
+// at N = 16384): one wave takes 64 particles and scans in registers. For K
+// uniform on 0..20 the rows are 93% filled (96% in blocks of 128, 79% when
+// neighbours are taken as they come). Particles without components are in
+// no group; with a mask those not selected get their zero blocks here.
+constexpr int kGroupBlock = 64;
+
+__global__ __launch_bounds__(kGroupBlock) void metric_group_kernel(MetricArgs a) {
+  __shared__ int hist[64], sorted[kGroupBlock];
+  const int lane = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * kGroupBlock, i = i0 + lane;
+  hist[lane] = 0;
+  __syncthreads();
+  int K = 0;
+  bool zero = false;
+  if (i < a.N) {
+    int64_t o0, fo;
+    if (!metric_particle(a, i, o0, K, fo, true)) K = 0;
+    zero = K > 0 && a.mask && !a.mask[i];
+    if (zero) K = 0;
+  }
+  const int rank = K > 0 ? atomicAdd(&hist[K], 1) : 0;
+  __syncthreads();
+  int left = lane > 0 ? hist[lane] : 0;  // lane k: particles with K = k still to place
+  int pos = left;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(pos, o);
+    if (lane >= o) pos += y;
+  }
+  pos -= left;  // lane k: the first place of K = k in sorted order
+  const int at = __shfl(pos, K) + rank;
+  if (K > 0) sorted[at] = (int)i - (int)i0;
+  __syncthreads();
+  int mine = 0, o = 0, g = 0;  // lane o keeps the o-th particle of the groups
+  unsigned long long any = __builtin_amdgcn_ballot_w64(left > 0);
+  while (any) {
+    const int start = o;
+    int rem = 32;
+    for (;;) {
+      const unsigned long long fit = any & ((2ull << rem) - 1ull);
+      if (!fit) break;
+      const int k = 63 - __builtin_clzll(fit);
+      const int p = __builtin_amdgcn_readlane(pos, k);
+      mine = lane == o ? p : mine;
+      ++o;
+      rem -= k;
+      left -= lane == k ? 1 : 0;
+      pos += lane == k ? 1 : 0;
+      any = __builtin_amdgcn_ballot_w64(left > 0);
+    }
+    if (lane == 0) a.work.groups[i0 + g] = ((i0 + o) << 32) | (i0 + start);
+    ++g;
+  }
+  if (lane == 0) a.work.cnt[blockIdx.x] = g;
+  if (lane < o) a.work.perm[i0 + lane] = (int32_t)(i0 + sorted[mine]);
+  for (unsigned long long z = __builtin_amdgcn_ballot_w64(zero); z; z &= z - 1) {
+    int64_t o0, fo;
+    int Kz;
+    metric_particle(a, i0 + __builtin_ctzll(z), o0, Kz, fo, false);
+    const int64_t n = (int64_t)Kz * a.P, cnt = a.blocks ? n * a.P : n * n;
+    for (int64_t e = lane; e < cnt; e += kGroupBlock) a.F[fo + e] = 0.0;
+  }
+}
+
+// ---------------------------------------------------------------- grouped form
+// Per-lane description of one component. Rows past the group's components
+// have zero coefficients.
+template <int MODEL>
+struct Comp;
+
+// pulse: x = s - nf (exact), z = x a - fa, e = 2^(-z^2),
+// J~ = (e, e (c1 z), e (c2 z^2)): c1 = A k, c2 = A k^2 with
+// k = 1 / sqrt(log2(e)/2), so that k z = (t - t0)/w. A width so small that z
+// is not finite on some sample has fa = NaN, an empty row a = 0 and fa so
+// large that e is zero.
+template <>
+struct Comp<SMCX_PULSE> {
+  float nf = 0.f, a = 0.f, fa = 1e6f, c1 = 0.f, c2 = 0.f;
+};
+
+// sinusoid: phase in cycles ph0 + ph1 s + ph2 s^2 (FP64), tr = t / T_obs =
+// tr0 + s dtr, J~ = (c0 sin, cos (k1 tr), cos (k2 tr^2), cos k3) with k1 =
+// 2 pi A', k2 = pi A', k3 = A'
+template <>
+struct Comp<SMCX_GBSINE> {
+  double ph0 = 0.0, ph1 = 0.0, ph2 = 0.0;
+  float c0 = 0.f, k1 = 0.f, k2 = 0.f, k3 = 0.f;
+};
+
+__device__ __forceinline__ void make_comp(const MetricArgs& a, const double* r, Comp<SMCX_PULSE>& q,
+                                          double* scale) {
+  const double A = r[0], t0 = r[1], w = r[2];
+  const double cc = (t0 - a.t_start) / a.dt;
+  double nn = floor(cc);
+  nn = fmin(fmax(nn, -4194304.0), 4194304.0);
+  const double al = kHalfLog2eRoot * a.dt / w;
+  const double k = 1.0 / kHalfLog2eRoot;
+  q.nf = (float)nn;
+  q.a = (float)al;
+  q.fa = (float)((cc - nn) * al);
+  const float x_max = fmaxf(fabsf(q.nf), fabsf((float)(a.T - 1) - q.nf));
+  if (!(fabsf(x_max * q.a) < INFINITY && fabsf(q.fa) < INFINITY)) q.fa = __builtin_nanf("");
+  q.c1 = (float)(A * k);
+  q.c2 = (float)(A * k * k);
+  scale[0] = 1.0;
+  scale[1] = scale[2] = w;
+}
+__device__ __forceinline__ void make_comp(const MetricArgs& a, const double* r, Comp<SMCX_GBSINE>& q,
+                                          double* scale) {
+  const double A = r[0], f0 = r[1], fd = r[2], phi0 = r[3];
+  const double ts = a.t_start, dt = a.dt;
+  q.ph0 = f0 * ts + 0.5 * fd * ts * ts + phi0 / kTwoPiM;
+  q.ph1 = (f0 + fd * ts) * dt;
+  q.ph2 = 0.5 * fd * dt * dt;
+  q.c0 = 1.f;
+  q.k1 = (float)(kTwoPiM * A);
+  q.k2 = (float)(kPiM * A);
+  q.k3 = (float)A;
+  scale[0] = scale[3] = 1.0;
+  scale[1] = 1.0 / a.t_obs;
+  scale[2] = 1.0 / (a.t_obs * a.t_obs);
+}
+
+// The partials of one component at sample s (sf = s - nf for pulses).
+__device__ __forceinline__ void jvalues(const Comp<SMCX_PULSE>& q, float x, int, float, float,
+                                        float (&j)[3]) {
+  const float z = __builtin_fmaf(x, q.a, -q.fa);
+  const float e = __builtin_amdgcn_exp2f(-(z * z));
+  j[0] = e;
+  j[1] = e * (q.c1 * z);
+  j[2] = e * (q.c2 * z * z);
+}
+__device__ __forceinline__ void jvalues(const Comp<SMCX_GBSINE>& q, float, int s, float tr0,
+                                        float dtr, float (&j)[4]) {
+  const double sd = (double)s;
+  const double ph = fma(fma(q.ph2, sd, q.ph1), sd, q.ph0);
+  const float rev = (float)(ph - rint(ph));  // revolutions in [-0.5, 0.5]
+  const float tr = __builtin_fmaf((float)s, dtr, tr0);
+  const float c = __builtin_amdgcn_sinf(rev + 0.25f);  // the cosine, a quarter cycle on
+  j[0] = __builtin_amdgcn_sinf(rev) * q.c0;
+  j[1] = c * (q.k1 * tr);
+  j[2] = c * (q.k2 * tr * tr);
+  j[3] = c * q.k3;
+}
+__device__ __forceinline__ float centre(const Comp<SMCX_PULSE>& q) { return q.nf; }
+__device__ __forceinline__ float centre(const Comp<SMCX_GBSINE>&) { return 0.f; }
+
+// The partials at this half's four samples of a step from s0 on (x = s0 minus
+// the pulse's centre index, exact), in FP16. TAIL: samples from w1 on are
+// left out.
+template <int MODEL, int P, bool TAIL>
+__device__ __forceinline__ void step_partials(const Comp<MODEL>& q, float x, int s0, int w1, float tr0,
+                                              float dtr, half4 (&h)[P]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float j[P];
+    jvalues(q, x + (float)e, s0 + e, tr0, dtr, j);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      // a value that ends in a product is converted with it (one rounding);
+      // the empty asm on the first of two keeps the compiler from converting
+      // such values in pairs, with the products rounded to FP32 first
+      _Float16 v = (_Float16)(!TAIL || s0 + e < w1 ? j[p] : 0.f);
+      if ((MODEL != SMCX_PULSE || p > 0) && (TAIL || e % 2 == 0)) asm volatile("" : "+v"(v));
+      h[p][e] = v;
+    }
+  }
+}
+
+template <int P>
+__device__ __forceinline__ void step_products(const half4 (&h)[P], float16v (&acc)[P * (P + 1) / 2]) {
+  int y = 0;
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int r = p; r < P; ++r, ++y)
+      acc[y] = __builtin_amdgcn_mfma_f32_32x32x8f16(h[p], h[r], acc[y], 0, 0, 0);
+}
+
+// The products of one wave's group for one window, in LDS for the flush.
+template <int P>
+struct FlushTile {
+  float d[P * (P + 1) / 2][32 * 33];  // D_pp', rows of p by rows of p'
+};
+// What the flush needs to know of a wave's group.
+template <int P>
+struct FlushGroup {
+  double scale[32 * P];  // inverse natural scales of the rows
+  double beta[32];       // per particle of the group
+  int64_t fo[32];        // its block in F
+  int r0[32], K[32];     // its rows
+  int parts;             // particles
+};
+
+// One window's products into F, by the whole workgroup: rows of the output
+// over the waves and its columns over the lanes, so that every store covers
+// a stretch of an output row (written straight from the accumulators the
+// columns lie P entries apart and the mirrored half n entries, 110 us for
+// the 157 MB of a pulse population instead of 60). Of a symmetric product only
+// the upper triangle is read, so that the result is exactly symmetric.
+template <int P>
+__device__ __forceinline__ void flush_group(const MetricArgs& a, const FlushTile<P>& t,
+                                            const FlushGroup<P>& g, bool tempered, bool first) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  for (int l = 0; l < g.parts; ++l) {
+    const int K = g.K[l], r0 = g.r0[l];
+    const double bs = (tempered ? g.beta[l] : 1.0) * a.inv_sigma2;
+    double* Fi = a.F + g.fo[l];
+    // entry (row r, p) x (row c, pc), p <= pc after ordering
+    auto entry = [&](int r, int p, int c, int pc) {
+      const bool up = p < pc || (p == pc && r <= c);
+      const int u = up ? r : c, pu = up ? p : pc, v = up ? c : r, pv = up ? pc : p;
+      const int y = pu * P - pu * (pu - 1) / 2 + (pv - pu);
+      // scaled in the order of the coordinate form
+      const int a0 = u * P + pu, a1 = v * P + pv, lo = a0 < a1 ? a0 : a1, hi = a0 < a1 ? a1 : a0;
+      return (double)t.d[y][u * 33 + v] * (bs * g.scale[hi]) * g.scale[lo];
+    };
+    if (a.blocks) {
+      for (int e = threadIdx.x; e < K * P * P; e += 256) {
+        const int k = e / (P * P), p = e / P % P, pc = e % P;
+        const double v = entry(r0 + k, p, r0 + k, pc);
+        Fi[e] = first ? v : Fi[e] + v;
+      }
+      continue;
+    }
+    const int n = K * P;
+    if (lane >= n) continue;  // n <= 64
+    const int c = r0 + lane / P, pc = lane % P;
+    if (first) {
+#pragma unroll 4
+      for (int x = wid; x < n; x += 4)
+        Fi[(int64_t)x * n + lane] = entry(r0 + x / P, x % P, c, pc);
+    } else {
+      for (int x = wid; x < n; x += 4)
+        Fi[(int64_t)x * n + lane] += entry(r0 + x / P, x % P, c, pc);
+    }
+  }
+}
+
+// Waves of a workgroup that share a group, one window each in turn: with
+// several windows of samples a group's windows run side by side and are
+// flushed in order.
+// The step loop takes the partials of the next step while the products of
+// the current one are in the matrix cores.
+template <int MODEL, int WPG>
+__global__ __launch_bounds__(256, (MODEL == SMCX_PULSE ? 3 : 2)) void metric_group_wave_kernel(MetricArgs a) {
+  constexpr int P = n_params(MODEL);
+  constexpr int NP = P * (P + 1) / 2;
+  __shared__ FlushTile<P> tile;
+  __shared__ FlushGroup<P> groups[4];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  FlushGroup<P>& gr = groups[wid];
+  const int half = lane >> 5;  // which group of 4 samples of a step this lane feeds
+  const int row = lane & 31;
+  // slot s of block b: the filled slots of all blocks come first
+  const int64_t item = ((int64_t)blockIdx.x * 4 + wid) / WPG;
+  const int blk = (int)(item % a.nblk), slot = (int)(item / a.nblk);
+  const bool have = slot < kGroupBlock && slot < a.work.cnt[blk];
+  if (!__syncthreads_or(have)) return;
+  int64_t g0 = 0;
+  int parts = 0;
+  if (have) {
+    const int64_t g = a.work.groups[(int64_t)blk * kGroupBlock + slot];
+    g0 = g & 0xffffffffll;
+    parts = (int)((g >> 32) - g0);
+  }
+  // lane l < parts holds the group's l-th particle
+  int Kl = 0, end = 0;
+  int64_t ol = 0;
+  if (lane < parts) {
+    const int64_t i = a.work.perm[g0 + lane];
+    ol = a.offsets[i];
+    Kl = (int)(a.offsets[i + 1] - ol);
+    gr.beta[lane] = a.beta ? a.beta[i] : 1.0;
+    gr.fo[lane] = a.blocks ? ol * P * P : a.f_offsets[i];
+    gr.K[lane] = Kl;
+  }
+  if (lane == 0) gr.parts = parts;
+  end = Kl;
+  for (int o = 1; o < 32; o <<= 1) {
+    const int y = __shfl_up(end, o);
+    if (lane >= o) end += y;
+  }
+  if (lane < parts) gr.r0[lane] = end - Kl;
+  // this lane's component: row `row` of the group
+  Comp<MODEL> q;
+  int64_t src = -1;  // its row of theta
+  for (int l = 0; l < parts; ++l) {
+    const int e = __builtin_amdgcn_readlane(end, l), k = __builtin_amdgcn_readlane(Kl, l);
+    const int64_t o = ((int64_t)__builtin_amdgcn_readlane((int)(ol >> 32), l) << 32) |
+                      (uint32_t)__builtin_amdgcn_readlane((int)ol, l);
+    if (row >= e - k && row < e) src = o + row - (e - k);
+  }
+  if (src >= 0) {
+    double natural[P];
+    make_comp(a, a.theta + src * P, q, natural);
+    if (half == 0)
+      for (int p = 0; p < P; ++p) gr.scale[row * P + p] = 1.0 / natural[p];
+  }
+  const float tr0 = (float)(a.t_start / a.t_obs), dtr = (float)(a.dt / a.t_obs);
+  const float nf = centre(q);
+  // windows of at most 4096 samples, none across the split
+  const int nlo = (int)((a.split + kFlushSamples - 1) / kFlushSamples);
+  const int nwin = nlo + (int)((a.T - a.split + kFlushSamples - 1) / kFlushSamples);
+  for (int w = 0; w < nwin; w += WPG) {
+    const int win = w + wid % WPG;
+    float16v acc[NP];
+#pragma unroll
+    for (int y = 0; y < NP; ++y) acc[y] = float16v{};
+    if (have && win < nwin) {
+      const bool lo = win < nlo;
+      // sample indices fit in 32 bits (T <= 2^22)
+      const int w0 = lo ? win * kFlushSamples : (int)a.split + (win - nlo) * kFlushSamples;
+      const int last = lo ? (int)a.split : (int)a.T;
+      const int w1 = w0 + kFlushSamples < last ? w0 + kFlushSamples : last;
+      const int full = w0 + (w1 - w0) / 8 * 8;
+      float x = (float)(w0 + 4 * half) - nf;  // exact: integers below 2^24
+      half4 h[P];
+      if (full > w0) {
+        step_partials<MODEL, P, false>(q, x, w0 + 4 * half, w1, tr0, dtr, h);
+#pragma unroll 1
+        for (int s = w0 + 8; s < full; s += 8) {
+          half4 hn[P];
+          x += 8.f;
+          step_partials<MODEL, P, false>(q, x, s + 4 * half, w1, tr0, dtr, hn);
+          step_products<P>(h, acc);
+#pragma unroll
+          for (int y = 0; y < NP; ++y) {
+            // one product, then a share of the next step's vector work
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x402, MODEL == SMCX_PULSE ? 7 : 9, 0);
+          }
+#pragma unroll
+          for (int p = 0; p < P; ++p) h[p] = hn[p];
+        }
+        step_products<P>(h, acc);
+        x += 8.f;
+      }
+      if (full < w1) {
+        step_partials<MODEL, P, true>(q, x, full + 4 * half, w1, tr0, dtr, h);
+        step_products<P>(h, acc);
+      }
+    }
+    // flush, one wave's products after the other: lane holds D[i][j] of rows
+    // j = lane % 32 and i = 8 (r/4) + 4 half + r % 4
+    for (int turn = 0; turn < 4; ++turn) {
+      __syncthreads();
+      if (wid == turn)
+#pragma unroll
+        for (int y = 0; y < NP; ++y)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            tile.d[y][(8 * (r >> 2) + 4 * half + (r & 3)) * 33 + row] = acc[y][r];
+      __syncthreads();
+      const int wt = w + turn % WPG;  // that wave's window
+      if (wt < nwin) flush_group<P>(a, tile, groups[turn], wt >= nlo, wt == 0);
+    }
+  }
+}
+
+// ---------------------------------------------------------------- coordinate form
 // Per-lane description of one coordinate (component k, parameter p), set up
 // so that J~ needs no branch on p; padding lanes get zero coefficients.
 template <int MODEL>
@@ -540,17 +943,58 @@ hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
   return hipGetLastError();
 }
 
+namespace {
+template <int MODEL>
+hipError_t launch_groups(const MetricArgs& a, int64_t windows, hipStream_t st) {
+  hipLaunchKernelGGL(metric_group_kernel, dim3((unsigned)a.nblk), dim3(kGroupBlock), 0, st, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t items = (int64_t)a.nblk * kGroupBlock;  // most slots are empty
+  // one wave per group on a single window, else up to four windows of a group
+  // at once (a long record of few particles has few groups)
+  if (windows == 1)
+    hipLaunchKernelGGL((metric_group_wave_kernel<MODEL, 1>), dim3((unsigned)((items + 3) / 4)),
+                       dim3(256), 0, st, a);
+  else if (windows == 2)
+    hipLaunchKernelGGL((metric_group_wave_kernel<MODEL, 2>), dim3((unsigned)((items + 1) / 2)),
+                       dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((metric_group_wave_kernel<MODEL, 4>), dim3((unsigned)items), dim3(256), 0, st,
+                       a);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_metric(int model, int P, int64_t N, int64_t M, int64_t T, double t_start,
                          double dt, double inv_sigma2, int32_t k_max, const int64_t* offsets,
                          const double* theta, const double* beta, const int64_t* f_offsets,
                          int64_t f_size, double* F, int64_t split, int blocks, int* flag,
-                         hipStream_t st, const uint8_t* mask) {
+                         const MetricWork& work, int n_cu, hipStream_t st, const uint8_t* mask) {
   MetricArgs a{P, N, M, T, t_start, dt, inv_sigma2, (double)T * dt, k_max, offsets, theta,
-               beta, f_offsets, f_size, F, flag, 0, 0, 1, blocks, mask};
+               beta, f_offsets, f_size, F, flag, 0, 0, 1, blocks, mask, split, work,
+               (int)((N + kGroupBlock - 1) / kGroupBlock)};
   const int nmax = k_max * P;
-  const dim3 grid((unsigned)((N + 3) / 4)), block(256);
-  const int nb = nmax <= 32 ? 1 : (nmax <= 64 ? 2 : 4);
   if (nmax > 128) return hipErrorInvalidValue;
+  const int nb = nmax <= 32 ? 1 : (nmax <= 64 ? 2 : 4);
+  {
+    // The grouped form saves vector work and takes several windows at once,
+    // but spends about 30 us on packing and flushing and more per step of
+    // a lone wave (0.15 us against 0.09 with one block of coordinates). It wins
+    // where the coordinate form would put four waves of work or more on each
+    // SIMD (pulses, K on 0..7, T = 4096: 222 -> 128 us at 4000 particles, 84 ->
+    // 122 at 1000; K on 0..21: 395 -> 194 at 4000, 142 -> 118 at 1000), or
+    // on more than two windows (200 particles, T = 20000: 333 -> 191 us).
+    // Beyond 64 coordinates the compiler rounds some of the coordinate
+    // form's products to FP32 before FP16 and others once, depending on the
+    // block; the grouped form would change F by 2e-7 there (below it gives the
+    // same bits), so those keep the coordinate form.
+    const int64_t windows = (split + kFlushSamples - 1) / kFlushSamples +
+                            (T - split + kFlushSamples - 1) / kFlushSamples;
+    if (nb <= 2 && (windows > 2 || N * nb >= 16 * (int64_t)n_cu))
+      return model == SMCX_PULSE ? launch_groups<SMCX_PULSE>(a, windows, st)
+                                 : launch_groups<SMCX_GBSINE>(a, windows, st);
+  }
+  const dim3 grid((unsigned)((N + 3) / 4)), block(256);
   const size_t lds = 4 * 32 * (size_t)nb * sizeof(double);
   // one launch per window of samples: later windows add to what earlier ones
   // wrote; with a bridge split the windows stop at the split, and only those
