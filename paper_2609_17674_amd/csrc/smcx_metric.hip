@@ -51,6 +51,13 @@ constexpr double kPiM = 3.141592653589793238462643383279;
 constexpr double kHalfLog2eRoot = 0.84932180028801904272150283410289;  // sqrt(log2(e) / 2)
 constexpr int kFlushSamples = 4096;
 
+// Orders the LDS accesses of one wave around it.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 struct MetricArgs {
   int P;
   int64_t N, M, T;
@@ -763,6 +770,176 @@ __global__ __launch_bounds__(64) void factor_kernel(FactorArgs a) {
   }
 }
 
+// ---- blocks of up to 64 rows, in registers
+// factor_block's LDS form spends its time in serial LDS chains: 577 us for 8192
+// blocks of 3 K coordinates, K uniform on 0..20, whose bytes take 31 us. This
+// form takes 150 us, bound by the latency of a step (about 0.8 us at n = 63,
+// the LDS round trip and the chain from pivot to pivot); one wave per
+// workgroup, so that a long block holds no other's slot (178 us with four).
+// Here lane r keeps row r of the block in registers and one sweep over the
+// columns both eliminates and inverts, in place: with F + diag(ridge) =
+// U^{-1} D U^{-T} (U unit lower triangular), step j takes m_r = -A_rj / A_jj
+// in every lane r > j and adds m_r times one broadcast vector b to the whole
+// row, where b_c is A_cj (the column, held by the lanes) for c > j and U_jc
+// (lane j's finished row) for c < j; column j then becomes U_rj = m_r. At the
+// end W = D^{-1/2} U. The vector goes through LDS once per step and comes
+// back 16 entries to a register, one per lane of a row of 16, from where
+// v_fmac_f64 broadcasts each entry by itself (DPP row_newbcast): one
+// instruction per entry and step, where a read of every entry by all lanes
+// would keep the LDS busy longer than the FMAs take.
+// The register array is rotated by eight columns after every eight steps,
+// so that the step's column sits at a fixed place: register i of block jb
+// holds column (jb + i) mod NR.
+#define SMCX_FMAC8(r, o, b, m, c0, c1, c2, c3, c4, c5, c6, c7)                                     \
+  asm("s_nop 1\n\t" /* b may come from a register copy: two wait states before DPP */            \
+      "v_fmac_f64_dpp %0, %8, %9 row_newbcast:" #c0 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %1, %8, %9 row_newbcast:" #c1 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %2, %8, %9 row_newbcast:" #c2 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %3, %8, %9 row_newbcast:" #c3 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %4, %8, %9 row_newbcast:" #c4 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %5, %8, %9 row_newbcast:" #c5 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %6, %8, %9 row_newbcast:" #c6 " row_mask:0xf bank_mask:0xf\n\t"            \
+      "v_fmac_f64_dpp %7, %8, %9 row_newbcast:" #c7 " row_mask:0xf bank_mask:0xf"                  \
+      : "+v"(r[(o) + 0]), "+v"(r[(o) + 1]), "+v"(r[(o) + 2]), "+v"(r[(o) + 3]), "+v"(r[(o) + 4]),  \
+        "+v"(r[(o) + 5]), "+v"(r[(o) + 6]), "+v"(r[(o) + 7])                                       \
+      : "v"(b), "v"(m))
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+constexpr int kRowPad = 17;  // doubles per row of the 16-column stage
+
+// Factor of the n x n block Fi (n <= NR <= 64, NR - n < 8) into Wi by one
+// full wave; sh: the wave's LDS, NR rows of kRowPad doubles. Returns false
+// (in every lane, Wi untouched) if a pivot is not > 0.
+template <int NR>
+__device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* Fi, double* Wi, int n,
+                                            double* sh, int lane) {
+  double r[NR];
+  const int sub = lane & 15;
+  // rows in whole lines, 16 columns at a time through LDS; only the lower
+  // triangle is read
+#pragma unroll
+  for (int c0 = 0; c0 < NR; c0 += 16) {
+    const int c = c0 + sub;
+    for (int row = c0 + (lane >> 4); row < n; row += 4)
+      sh[row * kRowPad + sub] =
+          c <= row ? Fi[row * n + c] + (c == row ? a.ridge[c % a.P] : 0.0) : 0.0;
+    wave_lds_order();
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (c0 + u < NR) r[c0 + u] = lane >= c0 && lane < n ? sh[lane * kRowPad + u] : 0.0;
+    wave_lds_order();
+  }
+  double pivot = 1.0;
+#pragma unroll 1
+  for (int jb = 0; jb < NR; jb += 8) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int j = jb + u;
+      if (j < n) {
+        const double x = r[u];
+        const double d = lane_value(x, j);
+        if (!(d > 0.0)) return false;
+        // b: lane j's row (its columns before j), then the column below j
+        if (lane == j) {
+          pivot = d;
+#pragma unroll
+          for (int g = 0; g < NR; g += 8)
+            if (g == 0 || g >= NR - jb)
+#pragma unroll
+              for (int i = g; i < g + 8; ++i) sh[i] = r[i];
+        }
+        if (lane > j && lane < NR) sh[lane - jb] = x;
+        wave_lds_order();
+        double b[(NR + 15) / 16];
+#pragma unroll
+        for (int q = 0; q < (NR + 15) / 16; ++q) b[q] = sh[16 * q + sub];
+        wave_lds_order();
+        const double m = lane > j && lane < n ? -(x * (1.0 / d)) : 0.0;
+#pragma unroll
+        for (int q = 0; q < (NR + 15) / 16; ++q) {
+          SMCX_FMAC8(r, 16 * q, b[q], m, 0, 1, 2, 3, 4, 5, 6, 7);
+          if constexpr (NR % 16 == 0) {
+            SMCX_FMAC8(r, 16 * q + 8, b[q], m, 8, 9, 10, 11, 12, 13, 14, 15);
+          } else {
+            if (16 * q + 8 < NR)
+              SMCX_FMAC8(r, (16 * q + 8 < NR ? 16 * q + 8 : 0), b[q], m, 8, 9, 10, 11, 12, 13, 14, 15);
+          }
+        }
+        r[u] = lane == j ? 1.0 : m;
+      }
+    }
+    double t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = r[u];
+#pragma unroll
+    for (int i = 0; i + 8 < NR; ++i) r[i] = r[i + 8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) r[NR - 8 + u] = t[u];
+  }
+  const double s = 1.0 / sqrt(pivot);
+#pragma unroll
+  for (int c0 = 0; c0 < NR; c0 += 16) {
+    if (lane < NR)
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (c0 + u < NR) sh[lane * kRowPad + u] = r[c0 + u] * s;
+    wave_lds_order();
+    const int c = c0 + sub;
+    if (c < n)
+      for (int row = lane >> 4; row < n; row += 4) Wi[row * n + c] = sh[row * kRowPad + sub];
+    wave_lds_order();
+  }
+  return true;
+}
+
+// One wave per particle, CAP >= k_max P rows at most.
+template <int CAP>
+__global__ __launch_bounds__(64, (CAP <= 32 ? 5 : 3)) void factor_rows_kernel(FactorArgs a) {
+  __shared__ double sh[CAP * kRowPad];
+  const int lane = threadIdx.x;
+  const int64_t i = blockIdx.x;
+  const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
+  if (!(o0 >= 0 && o1 >= o0 && o1 <= a.M && o1 - o0 <= a.k_max)) {
+    if (lane == 0) atomicOr(a.flag, kFlagOffsets);
+    return;
+  }
+  const int n = __builtin_amdgcn_readfirstlane((int)(o1 - o0) * a.P);
+  const int64_t fo = a.f_offsets[i];
+  if (a.f_offsets[i + 1] - fo != (int64_t)n * n || fo < 0 || fo + (int64_t)n * n > a.f_size) {
+    if (lane == 0) atomicOr(a.flag, kFlagOffsets);
+    return;
+  }
+  if (n == 0 || (a.mask && !a.mask[i])) return;
+  const double* Fi = a.F + fo;
+  double* Wi = a.W + fo;
+  bool ok = false;
+  switch ((n + 7) / 8) {
+    case 1: ok = factor_rows<8>(a, Fi, Wi, n, sh, lane); break;
+    case 2: ok = factor_rows<16>(a, Fi, Wi, n, sh, lane); break;
+    case 3: ok = factor_rows<24>(a, Fi, Wi, n, sh, lane); break;
+    case 4: ok = factor_rows<32>(a, Fi, Wi, n, sh, lane); break;
+    default:
+      if constexpr (CAP > 32) {
+        switch ((n + 7) / 8) {
+          case 5: ok = factor_rows<40>(a, Fi, Wi, n, sh, lane); break;
+          case 6: ok = factor_rows<48>(a, Fi, Wi, n, sh, lane); break;
+          case 7: ok = factor_rows<56>(a, Fi, Wi, n, sh, lane); break;
+          case 8: ok = factor_rows<64>(a, Fi, Wi, n, sh, lane); break;
+        }
+      }
+  }
+  if (!ok) {
+    if (lane == 0) atomicOr(a.flag, kFlagNotPD);
+    for (int e = lane; e < n * n; e += 64) Wi[e] = __builtin_nan("");
+  }
+}
+
 // One P x P block per thread, W_m = L^{-1} with L L^T = F_m + diag(ridge),
 // in registers: the same steps in the same order as factor_block, so a block
 // comes out bitwise as the workgroup factor's block mode gives it. A pivot
@@ -938,6 +1115,17 @@ hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
   a.flag = flag;
   a.mask = mask;
   a.block = block;
+  // whole blocks of up to 64 coordinates in registers, a wave per particle;
+  // larger ones do not fit a row per lane, and the block mode's small blocks
+  // leave most lanes of either form idle
+  if (block == 0 && k_max * P <= 64) {
+    const dim3 grid((unsigned)N);
+    if (k_max * P <= 32)
+      hipLaunchKernelGGL(factor_rows_kernel<32>, grid, dim3(64), 0, st, a);
+    else
+      hipLaunchKernelGGL(factor_rows_kernel<64>, grid, dim3(64), 0, st, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(factor_kernel, dim3((unsigned)N), dim3(64),
                      factor_lds_bytes(block > 0 ? block : k_max * P), st, a);
   return hipGetLastError();
