@@ -871,16 +871,18 @@ struct FdItem {
   int K;
 };
 
-// Listed work items of a launch: the ordering pass's count in sorted mode
-// (valid particles with K > 0, or all valid ones for birth/death), else N.
+// Listed work items of a launch: the entries of a compact list, the ranks of
+// the ordering pass (valid particles with K > 0, or all valid ones for
+// birth/death), else N.
 __device__ __forceinline__ int64_t fd_count(const PopArgs& a) {
-  return a.order ? (int64_t)*a.n_active : a.N;
+  return !a.order ? a.N : (a.n_active ? (int64_t)*a.n_active : a.n_ranks);
 }
 
-// Work item at rank < fd_count(a); false for a particle whose offsets are
-// invalid or exceed k_max.
+// Work item at rank < fd_count(a); false for an empty rank and for a particle
+// whose offsets are invalid or exceed k_max.
 __device__ __forceinline__ bool fd_item_at(const PopArgs& a, int64_t rank, FdItem& it) {
   it.i = a.order ? (int64_t)a.order[rank] : rank;
+  if (it.i < 0) return false;  // an empty rank
   const int64_t o0 = a.offsets[it.i], o1 = a.offsets[it.i + 1];
   if (!(o0 >= 0 && o1 >= o0 && o1 <= a.M && o1 - o0 <= a.k_max)) return false;
   it.m0 = o0;
@@ -1250,7 +1252,7 @@ __global__ __launch_bounds__(256) void fd_src_kernel(PopArgs a, double T2) {
 // listed (late NUTS doublings). Full passes keep one workgroup per group of
 // particles, which the hardware hands out in the K-sorted order.
 unsigned fd_grid(const PopArgs& a, int64_t per_block, int64_t blocks_per_cu) {
-  const int64_t need = (a.N + per_block - 1) / per_block;
+  const int64_t need = (launch_ranks(a) + per_block - 1) / per_block;
   const int64_t cap = blocks_per_cu * (a.n_cu > 0 ? a.n_cu : 256);
   return (unsigned)std::max<int64_t>(1, a.stride_grid ? std::min(need, cap) : need);
 }
@@ -1282,7 +1284,7 @@ hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((fd_kernel<1, 2, true>), dim3(fd_grid(a, 4, 6)), block, lds2, st, a, a.fd_src);
     return hipGetLastError();
   }
-  const dim3 grid((unsigned)((a.N + 3) / 4));
+  const dim3 grid((unsigned)((launch_ranks(a) + 3) / 4));
   if (nr2)
     hipLaunchKernelGGL((fd_kernel<MODE, 2, false>), grid, block, lds2, st, a, a.fd_src);
   else

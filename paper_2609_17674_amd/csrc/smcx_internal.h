@@ -58,6 +58,7 @@ struct Tiling {
   int nch;            // chunks covering [s_lo, s_hi)
   int sorted;         // 1: items ordered by K descending (ordering pass), 0: particle order,
                       // 2: as 1 on a persistent grid (waves step through the items)
+  int strict = 0;     // particle order that stands in for an ordering pass (PopArgs::strict)
 };
 
 // Arguments of the batched population kernels (forward, fused forward +
@@ -78,8 +79,11 @@ struct PopArgs {
   const double* k0_dev;    // device scalar used in place of k0 when set (nullptr: k0)
   int64_t split;           // posterior-start bridge: samples s < split are untempered
                            // (weight 1), later ones weighted by beta; 0 (or <= s_lo) = off
-  const int32_t* order;    // [N] particles sorted by K descending, or nullptr: particle order
-  const int32_t* n_active; // device scalar: number of entries of order (sorted mode)
+  const int32_t* order;    // particles longest-K first, or nullptr: particle order
+  const int32_t* n_active; // device scalar: entries of a compact order, or nullptr: n_ranks
+  int64_t n_ranks;         // ranks of the ordering pass's order (prep_ranks), -1 where empty
+  int strict;              // particle order: offsets that do not span [0, M] make every
+                           // particle invalid (as the ordering pass has it)
   int nch;
   int64_t chunk_len;
   // outputs
@@ -164,9 +168,7 @@ struct PrepArgs {
   double* dlogl_birth; // birth/death outputs for invalid particles (nullptr to skip)
   double* dlogl_death;
   const int32_t* death_idx;  // validated against [-1, K_i) when dlogl_death is set
-  int32_t* order;
-  int32_t* n_active;
-  int32_t* block_hist; // [prep_slices(N)][k_max + 1] workspace of the ordering pass
+  int32_t* order;      // [prep_ranks(N)]
   int* flag;
   int tempered;        // 1: K=0 value times beta_i, 0: untempered
   int include_k0;      // 1: K = 0 particles stay in the work list (birth pass)
@@ -243,8 +245,12 @@ hipError_t launch_nuts_finalize(const NutsArgs& a, hipStream_t st);
 
 // Host launchers (defined in smcx_kernels.hip / smcx_plain.hip).
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
-// Number of particle slices of the ordering pass (its histogram workspace rows).
+// Number of particle slices of the ordering pass, and of ranks of its order (at
+// most N + prep_slices(N) - 1).
 int64_t prep_slices(int64_t N);
+int64_t prep_ranks(int64_t N);
+// Ranks a launch over the work list has to cover.
+inline int64_t launch_ranks(const PopArgs& a) { return a.order && !a.n_active ? a.n_ranks : a.N; }
 
 // Gauss-Newton metric on the matrix cores (smcx_metric.hip); k_max * P <= 128.
 // blocks: write only the P x P block of each component, at F + m P P for its

@@ -697,21 +697,34 @@ struct Item {
   int K;       // components
 };
 
+// Ranks of the work list: those of the ordering pass, or the entries of a
+// compact list.
+__device__ __forceinline__ int64_t rank_count(const PopArgs& a) {
+  return a.n_active ? (int64_t)*a.n_active : a.n_ranks;
+}
+
+// Whether offsets[0] != 0 or offsets[N] != M.
+__device__ __forceinline__ bool bad_offsets(const PopArgs& a) {
+  return a.offsets[0] != 0 || a.offsets[a.N] != a.M;
+}
+
 // Map a wave's item index to (particle, chunk). In sorted mode the ordering
 // pass has already validated the particles and settled K = 0 ones. In
 // particle order the wave validates its own particle: its rows must lie in
 // [0, M] and K in [0, k_max] (and a death index in [-1, K)); an invalid
 // particle gets NaN outputs and raises the device flag, a particle without
-// components gets the precomputed K = 0 value (unless `with_k0`).
+// components gets the precomputed K = 0 value (unless `with_k0`). With
+// a.strict (particle order in place of an ordering pass) offsets that do not
+// span [0, M] make every particle invalid, as that pass has it.
 // Returns false when the wave has nothing more to do.
 __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int lane, int P,
                                             bool with_k0, Item& it) {
   if (a.order) {
-    const int64_t n_items = (int64_t)(*a.n_active) * a.nch;
-    if (item >= n_items) return false;
+    if (item >= rank_count(a) * a.nch) return false;
     const int64_t rank = item / a.nch;
     it.c = (int)(item - rank * a.nch);
     it.i = a.order[rank];
+    if (it.i < 0) return false;  // a slice's unused rank
     it.m0 = a.offsets[it.i];
     it.K = (int)(a.offsets[it.i + 1] - it.m0);
     return true;
@@ -720,11 +733,13 @@ __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int 
   const int64_t i = item / a.nch;
   it.c = (int)(item - i * a.nch);
   it.i = (int)i;
-  if (item == 0 && lane == 0 && (a.offsets[0] != 0 || a.offsets[a.N] != a.M))
-    atomicOr(a.flag, a.offsets[0] != 0 ? kFlagOffsets : kFlagMMax);
   const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
+  const bool bad_all = bad_offsets(a);
+  if (item == 0 && lane == 0 && bad_all)
+    atomicOr(a.flag, a.offsets[0] != 0 ? kFlagOffsets : kFlagMMax);
   const bool rows_ok = o0 >= 0 && o1 >= o0 && o1 <= a.M;
-  int bad = rows_ok ? 0 : kFlagOffsets;
+  const bool strict_bad = a.strict && bad_all;
+  int bad = rows_ok && !strict_bad ? 0 : kFlagOffsets;
   if (rows_ok && o1 - o0 > a.k_max) bad |= kFlagKMax;
   if (a.death_idx) {
     const int32_t j = a.death_idx[i];
@@ -734,14 +749,25 @@ __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int 
     if (it.c == 0) {
       const double nan = __builtin_nan("");
       if (lane == 0) {
-        atomicOr(a.flag, bad);
+        if (!strict_bad) atomicOr(a.flag, bad);
         if (a.logl) a.logl[i] = nan;
-        if (a.dlogl_birth) a.dlogl_birth[i] = nan;
-        if (a.dlogl_death) a.dlogl_death[i] = nan;
+        if (a.theta_birth && a.dlogl_birth) a.dlogl_birth[i] = nan;
+        if (a.death_idx && a.dlogl_death) a.dlogl_death[i] = nan;
       }
-      if (a.grad && rows_ok)
-        for (int64_t m = o0 + lane; m < o1; m += 64)
+      if (a.grad && !strict_bad && (rows_ok || (a.strict && o0 >= 0))) {
+        // rows past theta, or claimed by the next valid particle, are not its own
+        int64_t end = o1 < a.M ? o1 : a.M;
+        if (!rows_ok)
+          for (int64_t j = i + 1; j < a.N; ++j) {
+            const int64_t q0 = a.offsets[j], q1 = a.offsets[j + 1];
+            if (q0 >= 0 && q1 >= q0 && q1 <= a.M) {
+              end = q0 < end ? q0 : end;
+              break;
+            }
+          }
+        for (int64_t m = o0 + lane; m < end; m += 64)
           for (int p = 0; p < P; ++p) a.grad[m * P + p] = nan;
+      }
     }
     return false;
   }
@@ -760,10 +786,11 @@ __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int 
 __device__ __forceinline__ bool combine_item(const PopArgs& a, int64_t rank, bool with_k0,
                                              Item& it) {
   if (a.order) {
-    if (rank >= *a.n_active) return false;
+    if (rank >= rank_count(a)) return false;
     it.i = a.order[rank];
+    if (it.i < 0) return false;
   } else {
-    if (rank >= a.N) return false;
+    if (rank >= a.N || (a.strict && bad_offsets(a))) return false;
     it.i = (int)rank;
   }
   const int64_t o0 = a.offsets[it.i], o1 = a.offsets[it.i + 1];
@@ -782,13 +809,17 @@ __device__ __forceinline__ bool combine_item(const PopArgs& a, int64_t rank, boo
 
 // ---------------------------------------------------------------- prep
 // Ordering pass: validates every particle, settles the ones without work (K = 0
-// outside the birth pass, invalid ones) and lists the rest longest-K first
-// (a counting sort). Two launches over slices of kPrepSlice particles: the
-// count pass writes one K histogram per slice, the scatter pass combines them
-// into list positions and places its slice's particles. Each thread loads all
-// of its particles of a slice before it uses any, so a pass pays about one
-// memory latency. Particles of equal K are listed in no particular order
-// (results do not depend on it).
+// outside the birth pass, invalid ones) and lists the rest longest-K first.
+// One launch: each workgroup sorts a slice of at most kPrepSlice particles
+// by itself (a counting sort in LDS), and the work list takes the slices'
+// p-th particles in turn (rank p S + b for slice b of S), which hands the long
+// particles out first as one sorted list would: a slice of thousands holds
+// about the same mix of K as the next. A slice with fewer than its share
+// of particles to list leaves its last ranks empty (-1). (Two launches, a
+// histogram per slice and then one global order, took 5.3 + 5.0 us at N =
+// 16384.) Each thread loads all of its particles before it uses any, so the
+// pass pays about one memory latency. Particles of equal K are listed in no
+// particular order (results do not depend on it).
 constexpr int kPrepBlock = 256;
 constexpr int kPrepUnroll = 8;
 constexpr int kPrepSlice = kPrepBlock * kPrepUnroll;
@@ -800,7 +831,7 @@ __device__ __forceinline__ int prep_key(const PrepArgs& a, int64_t i, int64_t o0
   const int64_t K = o1 - o0;
   int bits = 0;
   if (bad_global) bits |= kFlagOffsets;
-  if (K < 0) bits |= kFlagOffsets;
+  if (K < 0 || o0 < 0 || o1 > a.M) bits |= kFlagOffsets;
   if (K > a.k_max) bits |= kFlagKMax;
   if (a.dlogl_death && a.death_idx && (dj < -1 || (int64_t)dj >= K)) bits |= kFlagDeath;
   if (bits) {
@@ -824,17 +855,26 @@ __device__ __forceinline__ int prep_key(const PrepArgs& a, int64_t i, int64_t o0
   return (int)K;
 }
 
-// Runs fn(i, key) for every particle of this block's slice. The loads are
-// unconditional, on a clamped index, so that they are all in flight together.
-template <bool SETTLE, bool DEATH, typename F>
-__device__ __forceinline__ void prep_slice(const PrepArgs& a, int bad_global, F fn) {
-  const int64_t base = (int64_t)blockIdx.x * kPrepSlice + threadIdx.x;
+// Particles per slice: S slices of (almost) equal size.
+__host__ __device__ inline int64_t prep_slice_len(int64_t N, int64_t S) { return (N + S - 1) / S; }
+
+template <bool DEATH>
+__global__ __launch_bounds__(kPrepBlock) void prep_kernel(PrepArgs a) {
+  extern __shared__ int hist[];  // [k_max + 1] particles with K = k, then their next list position
+  __shared__ int wsum[kPrepBlock / 64];
+  __shared__ int bad_global;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int nk = a.k_max + 1;  // at most 4 * kPrepBlock
+  const int64_t S = gridDim.x, len = prep_slice_len(a.N, S), base = blockIdx.x * len;
+  const int64_t end = base + len < a.N ? base + len : a.N;
   int64_t o0[kPrepUnroll], o1[kPrepUnroll];
   int32_t dj[kPrepUnroll];
   double bt[kPrepUnroll];
+  // the loads are unconditional, on a clamped index, so that they are all in
+  // flight together
 #pragma unroll
   for (int u = 0; u < kPrepUnroll; ++u) {
-    int64_t i = base + (int64_t)u * kPrepBlock;
+    int64_t i = base + (int64_t)u * kPrepBlock + tid;
     i = i < a.N ? i : a.N - 1;
     o0[u] = a.offsets[i];
     o1[u] = a.offsets[i + 1];
@@ -842,110 +882,65 @@ __device__ __forceinline__ void prep_slice(const PrepArgs& a, int bad_global, F 
     bt[u] = 1.0;
   }
   // the K = 0 outputs are tempered: fetch beta with the rest
-  if (SETTLE && a.tempered && a.beta && a.logl) {
+  if (a.tempered && a.beta && a.logl) {
 #pragma unroll
     for (int u = 0; u < kPrepUnroll; ++u) {
-      const int64_t i = base + (int64_t)u * kPrepBlock;
+      const int64_t i = base + (int64_t)u * kPrepBlock + tid;
       bt[u] = a.beta[i < a.N ? i : a.N - 1];
     }
   }
+  for (int k = tid; k < nk; k += kPrepBlock) hist[k] = 0;
+  if (tid == 0) {
+    // offsets[0] != 0 or offsets[N] != M: every particle is then invalid
+    const int bad = a.offsets[0] != 0 || a.offsets[a.N] != a.M ? 1 : 0;
+    bad_global = bad;
+    if (bad && blockIdx.x == 0) atomicOr(a.flag, a.offsets[0] != 0 ? kFlagOffsets : kFlagMMax);
+  }
+  __syncthreads();
+  int key[kPrepUnroll];
 #pragma unroll
   for (int u = 0; u < kPrepUnroll; ++u) {
-    const int64_t i = base + (int64_t)u * kPrepBlock;
-    if (i < a.N) fn(i, prep_key(a, i, o0[u], o1[u], dj[u], bt[u], bad_global, SETTLE));
-  }
-}
-
-template <bool SETTLE, typename F>
-__device__ __forceinline__ void prep_slice(const PrepArgs& a, int bad_global, F fn) {
-  if (a.dlogl_death && a.death_idx)
-    prep_slice<SETTLE, true>(a, bad_global, fn);
-  else
-    prep_slice<SETTLE, false>(a, bad_global, fn);
-}
-
-// Whether offsets[0] != 0 or offsets[N] != M (every particle is then invalid).
-__device__ __forceinline__ int prep_bad_global(const PrepArgs& a, bool raise) {
-  __shared__ int bad_global;
-  if (threadIdx.x == 0) {
-    int bad = 0;
-    if (a.N > 0 && (a.offsets[0] != 0 || a.offsets[a.N] != a.M)) bad = 1;
-    bad_global = bad;
-    if (bad && raise) atomicOr(a.flag, a.offsets[0] != 0 ? kFlagOffsets : kFlagMMax);
+    const int64_t i = base + (int64_t)u * kPrepBlock + tid;
+    key[u] = i < end ? prep_key(a, i, o0[u], o1[u], dj[u], bt[u], bad_global, true) : -1;
+    if (key[u] >= 0) atomicAdd(&hist[key[u]], 1);
   }
   __syncthreads();
-  return bad_global;
-}
-
-__global__ __launch_bounds__(kPrepBlock) void prep_count_kernel(PrepArgs a) {
-  extern __shared__ int hist[];  // [k_max + 1]
-  const int nk = a.k_max + 1;
-  for (int k = threadIdx.x; k < nk; k += kPrepBlock) hist[k] = 0;
-  const int bg = prep_bad_global(a, blockIdx.x == 0);
-  prep_slice<true>(a, bg, [&](int64_t, int key) {
-    if (key >= 0) atomicAdd(&hist[key], 1);
-  });
-  __syncthreads();
-  for (int k = threadIdx.x; k < nk; k += kPrepBlock) a.block_hist[(size_t)blockIdx.x * nk + k] = hist[k];
-}
-
-__global__ __launch_bounds__(kPrepBlock) void prep_scatter_kernel(PrepArgs a) {
-  extern __shared__ int sh[];
-  const int nk = a.k_max + 1;  // at most 4 * kPrepBlock
-  int* tot = sh;               // [nk] particles with K = k, all slices
-  int* pos = sh + nk;          // [nk] particles with K = k in earlier slices, then list positions
-  __shared__ int scan[kPrepBlock];
-  const int tid = threadIdx.x;
-  for (int k = tid; k < nk; k += kPrepBlock) tot[k] = pos[k] = 0;
-  const int bg = prep_bad_global(a, false);
-  // combine the slice histograms (loads batched four at a time)
-  const int nh = (int)gridDim.x * nk;
-  for (int base = 0; base < nh; base += 4 * kPrepBlock) {
-    int c[4], idx[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      idx[q] = base + q * kPrepBlock + tid;
-      c[q] = a.block_hist[idx[q] < nh ? idx[q] : nh - 1];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (idx[q] < nh && c[q]) {
-        const int b = idx[q] / nk, k = idx[q] - b * nk;
-        atomicAdd(&tot[k], c[q]);
-        if (b < (int)blockIdx.x) atomicAdd(&pos[k], c[q]);
-      }
-    }
-  }
-  __syncthreads();
-  // exclusive prefix of tot over K in descending order: 4 entries per thread,
-  // then a Hillis-Steele scan over the thread sums
+  // exclusive prefix over K in descending order: 4 entries per thread, then a
+  // scan over the threads
   int loc[4], sum = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int j = 4 * tid + q;  // j-th K in descending order
-    loc[q] = j < nk ? tot[a.k_max - j] : 0;
+    loc[q] = j < nk ? hist[a.k_max - j] : 0;
     sum += loc[q];
   }
-  scan[tid] = sum;
-  __syncthreads();
-  for (int off = 1; off < kPrepBlock; off <<= 1) {
-    const int v = tid >= off ? scan[tid - off] : 0;
-    __syncthreads();
-    scan[tid] += v;
-    __syncthreads();
+  int run = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(run, o);
+    if (lane >= o) run += y;
   }
-  int run = scan[tid] - sum;
+  if (lane == 63) wsum[tid >> 6] = run;
+  __syncthreads();
+  int total = 0;
+  run -= sum;
+#pragma unroll
+  for (int w = 0; w < kPrepBlock / 64; ++w) {
+    if (w < tid >> 6) run += wsum[w];
+    total += wsum[w];
+  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int j = 4 * tid + q;
-    if (j < nk) pos[a.k_max - j] += run;
+    if (j < nk) hist[a.k_max - j] = run;
     run += loc[q];
   }
-  if (blockIdx.x == 0 && tid == kPrepBlock - 1) *a.n_active = scan[kPrepBlock - 1];
   __syncthreads();
-  prep_slice<false>(a, bg, [&](int64_t i, int key) {
-    if (key >= 0) a.order[atomicAdd(&pos[key], 1)] = (int32_t)i;
-  });
+#pragma unroll
+  for (int u = 0; u < kPrepUnroll; ++u)
+    if (key[u] >= 0)
+      a.order[atomicAdd(&hist[key[u]], 1) * S + blockIdx.x] =
+          (int32_t)(base + (int64_t)u * kPrepBlock + tid);
+  for (int64_t p = total + tid; p < len; p += kPrepBlock) a.order[p * S + blockIdx.x] = -1;
 }
 
 // ---------------------------------------------------------------- population kernel
@@ -1009,6 +1004,22 @@ __device__ __forceinline__ void pop_tiles(const PopArgs& a, typename Model<MODEL
   }
 }
 
+// The kernel's arguments, read again from the kernarg segment (the one
+// argument of the kernels that call this is a PopArgs). What only the end of
+// a work item needs is taken from here: held from the start, it would keep
+// scalar registers through the tile loops, which then spill into vector
+// lanes (56 of them in the pulse gradient kernel).
+__device__ __forceinline__ PopArgs late_args() {
+#ifdef __HIP_DEVICE_COMPILE__  // (the host pass has no address spaces to convert between)
+  using Arg = const __attribute__((address_space(4))) PopArgs;
+  Arg* p = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+#else
+  return PopArgs();
+#endif
+}
+
 // One work item of the population kernel (a wave-uniform index).
 template <int MODEL, int S, bool GRAD>
 __device__ __forceinline__ void pop_item(const PopArgs& a, int64_t item, int lane, int wid,
@@ -1062,28 +1073,29 @@ __device__ __forceinline__ void pop_item(const PopArgs& a, int64_t item, int lan
     else
       pop_tiles<MODEL, S, GRAD, false>(a, cst, acc, K, lane, cs, ce, split, b, ss, ss_lo);
   }
+  const PopArgs z = late_args();
   ss = lane63_d(wave_sum_d(ss));
   if (split) ss = lane63_d(wave_sum_d(ss_lo)) + b * ss;
   const double outer = split ? 1.0 : b;  // tempering still to apply
 
-  if (a.nch == 1) {
-    if (lane == 0 && a.logl) a.logl[i] = outer * (-0.5 * ss * a.inv_sigma2);
+  if (z.nch == 1) {
+    if (lane == 0 && z.logl) z.logl[i] = outer * (-0.5 * ss * z.inv_sigma2);
     if constexpr (GRAD) {
       wave_sync();
-      const double bs = outer * a.inv_sigma2;
+      const double bs = outer * z.inv_sigma2;
       // scale each component's sums in place, then write the rows out in
       // whole lines (lane idx of the particle's K P values)
       for (int k = lane; k < K; k += 64) {
         double g[P];
-        M::scale(thl + k * P, acc + k * P, bs, a, g);
+        M::scale(thl + k * P, acc + k * P, bs, z, g);
         for (int p = 0; p < P; ++p) acc[k * P + p] = g[p];
       }
       wave_sync();
-      double* gd = a.grad + m0 * P;
-      if (a.p_half) {
-        const double he = 0.5 * a.eps * (a.dir ? (double)a.dir[i] : 1.0);
-        const double* ph = a.p_half + m0 * P;
-        double* po = a.p_out + m0 * P;
+      double* gd = z.grad + m0 * P;
+      if (z.p_half) {
+        const double he = 0.5 * z.eps * (z.dir ? (double)z.dir[i] : 1.0);
+        const double* ph = z.p_half + m0 * P;
+        double* po = z.p_out + m0 * P;
         for (int idx = lane; idx < K * P; idx += 64) {
           const double g = acc[idx];
           gd[idx] = g;
@@ -1094,10 +1106,10 @@ __device__ __forceinline__ void pop_item(const PopArgs& a, int64_t item, int lan
       }
     }
   } else {
-    if (lane == 0) a.part[(size_t)c * a.N + i] = ss;
+    if (lane == 0) z.part[(size_t)c * z.N + i] = ss;
     if constexpr (GRAD) {
       wave_sync();
-      double* dst = a.part_g + ((size_t)c * a.m_max + m0) * P;
+      double* dst = z.part_g + ((size_t)c * z.m_max + m0) * P;
       for (int idx = lane; idx < K * P; idx += 64) dst[idx] = acc[idx];
     }
   }
@@ -1120,7 +1132,7 @@ __global__ __launch_bounds__(256, (pop_waves_per_simd<MODEL, S, GRAD>())) void p
     pop_item<MODEL, S, GRAD>(a, first, lane, wid, lds);
     return;
   }
-  const int64_t n = (a.order ? (int64_t)*a.n_active : a.N) * a.nch;
+  const int64_t n = (a.order ? rank_count(a) : a.N) * a.nch;
   const int64_t stride = (int64_t)gridDim.x * wpb;
   for (int64_t item = first; item < n; item += stride) {
     pop_item<MODEL, S, GRAD>(a, item, lane, wid, lds);
@@ -1576,7 +1588,7 @@ template <int MODEL, bool GRAD>
 hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   const int wpb = waves_per_block(MODEL, a.k_max, GRAD);
   const size_t lds = pop_lds_bytes_per_wave(MODEL, a.k_max, GRAD) * wpb;
-  const int64_t items = a.N * (int64_t)a.nch;
+  const int64_t ranks = launch_ranks(a), items = ranks * a.nch;
   if (items == 0) return a.prof_stop ? hipEventRecord((hipEvent_t)a.prof_stop, st) : hipSuccess;
   int64_t blocks = (items + wpb - 1) / wpb;
   const void* fn;
@@ -1601,7 +1613,7 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess && a.prof_stop) e = hipEventRecord((hipEvent_t)a.prof_stop, st);
   if (e != hipSuccess || a.nch == 1) return e;
-  const dim3 fgrid((unsigned)((a.N + 3) / 4));
+  const dim3 fgrid((unsigned)((ranks + 3) / 4));
   hipLaunchKernelGGL((finalize_kernel<MODEL, GRAD>), fgrid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
@@ -1610,7 +1622,7 @@ template <int MODEL>
 hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   const int wpb = waves_per_block(MODEL, a.k_max, false);
   const size_t lds = pop_lds_bytes_per_wave(MODEL, a.k_max, false) * wpb;
-  const int64_t items = a.N * (int64_t)a.nch;
+  const int64_t ranks = launch_ranks(a), items = ranks * a.nch;
   if (items == 0) return hipSuccess;
   const dim3 grid((unsigned)((items + wpb - 1) / wpb));
   const dim3 block(64 * wpb);
@@ -1621,7 +1633,7 @@ hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st)
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.nch == 1) return e;
-  hipLaunchKernelGGL(delta_finalize_kernel, dim3((unsigned)((a.N + 255) / 256)), dim3(256), 0, st,
+  hipLaunchKernelGGL(delta_finalize_kernel, dim3((unsigned)((ranks + 255) / 256)), dim3(256), 0, st,
                      a);
   return hipGetLastError();
 }
@@ -1636,16 +1648,20 @@ size_t pop_lds_bytes_per_wave(int model, int32_t k_max, bool grad) {
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st) {
   if (a.k_max + 1 > 4 * kPrepBlock) return hipErrorInvalidValue;
   const dim3 grid((unsigned)prep_slices(a.N));
-  hipLaunchKernelGGL(prep_count_kernel, grid, dim3(kPrepBlock), (size_t)(a.k_max + 1) * sizeof(int),
-                     st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(prep_scatter_kernel, grid, dim3(kPrepBlock),
-                     2 * (size_t)(a.k_max + 1) * sizeof(int), st, a);
+  const size_t lds = (size_t)(a.k_max + 1) * sizeof(int);
+  if (a.dlogl_death && a.death_idx)
+    hipLaunchKernelGGL(prep_kernel<true>, grid, dim3(kPrepBlock), lds, st, a);
+  else
+    hipLaunchKernelGGL(prep_kernel<false>, grid, dim3(kPrepBlock), lds, st, a);
   return hipGetLastError();
 }
 
 int64_t prep_slices(int64_t N) { return N > 0 ? (N + kPrepSlice - 1) / kPrepSlice : 1; }
+
+int64_t prep_ranks(int64_t N) {
+  const int64_t S = prep_slices(N);
+  return S * prep_slice_len(N, S);
+}
 
 hipError_t launch_forward(int model, const Tiling& t, const PopArgs& a, hipStream_t st) {
   if (model == SMCX_GBLISA) return launch_fd(0, a, st);

@@ -37,9 +37,7 @@ struct smcx_problem {
   smcx_problem* partner = nullptr;  // bridge partner (smcx_set_bridge_partner), or none
   int max_nch = 0;       // capacity of part (chunks per particle)
   int max_nch_grad = 0;  // capacity of part_g
-  int32_t* order = nullptr;
-  int32_t* n_active = nullptr;
-  int32_t* prep_hist = nullptr;  // [prep_slices(n_max)][k_max + 1]
+  int32_t* order = nullptr;  // work list (order_bytes)
   smcx::SmcWork smc{};            // SMC-step workspace, [n_max] each
   int* flag = nullptr;
   double* part = nullptr;   // [max_nch][n_max][4]

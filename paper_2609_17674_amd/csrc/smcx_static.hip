@@ -53,19 +53,22 @@ int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // Byte offsets of the workspace parts for one call.
 struct Layout {
-  size_t flag, n_active, k0, energy, d32, order, hist, part, part_g, total;
+  size_t flag, k0, energy, d32, order, part, part_g, total;
 };
 
 Layout layout(int64_t T_pad, int64_t N, int64_t M, int P, int32_t k_max, int nch) {
   Layout L;
   size_t o = 0;
   L.flag = o;     o += align256(sizeof(int));
-  L.n_active = o; o += align256(sizeof(int32_t));
   L.k0 = o;       o += align256(sizeof(double));
   L.energy = o;   o += align256((size_t)(T_pad / kStageSpan) * sizeof(double));
   L.d32 = o;      o += align256((size_t)T_pad * sizeof(float));
-  L.order = o;    o += align256((size_t)N * sizeof(int32_t));
-  L.hist = o;     o += align256((size_t)smcx::prep_slices(N) * (k_max + 1) * sizeof(int32_t));
+  // the work list with its empty ranks (at most one per slice); the room for a
+  // slot per slice and K keeps the sizes that fit the scratch, and the chunks
+  // taken for them, what they were
+  L.order = o;
+  o += align256(1) + align256((size_t)N * sizeof(int32_t)) +
+       align256((size_t)smcx::prep_slices(N) * (k_max + 1) * sizeof(int32_t));
   L.part = o;     o += nch > 1 ? align256((size_t)nch * N * sizeof(double)) : 0;
   L.part_g = o;   o += nch > 1 ? align256((size_t)nch * M * P * sizeof(double)) : 0;
   L.total = o;
@@ -191,8 +194,6 @@ extern "C" int logl_grad_batch_static(int model, const double* d, int64_t T, dou
   pa.logl = logl;
   pa.grad = grad;
   pa.order = reinterpret_cast<int32_t*>(base + L.order);
-  pa.n_active = reinterpret_cast<int32_t*>(base + L.n_active);
-  pa.block_hist = reinterpret_cast<int32_t*>(base + L.hist);
   pa.flag = flag;
   pa.tempered = 1;
   e = smcx::launch_prep(pa, st);
@@ -215,7 +216,7 @@ extern "C" int logl_grad_batch_static(int model, const double* d, int64_t T, dou
   a.m_max = M;
   a.k0_dev = k0;
   a.order = pa.order;
-  a.n_active = pa.n_active;
+  a.n_ranks = smcx::prep_ranks(N);
   a.nch = t.nch;
   a.chunk_len = t.chunk_len;
   a.logl = logl;
