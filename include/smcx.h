@@ -61,14 +61,14 @@
  * 5e5: a component beyond that, or whose chirp moves the phase by 1/64 cycle
  * or more across a tile, gets NaN outputs and raises the device flag); the
  * per-particle inner products are accumulated in FP64 and all outputs are
- * FP64. In logl_batch, logl_grad_batch, reweight_extend and the leapfrog and
- * NUTS calls, a pulse is truncated to |t - t0| < sqrt(128 ln 2) |w| (about
+ * FP64. In logl_batch, logl_grad_batch, delta_logl_birth_death, reweight_extend
+ * and the leapfrog and NUTS calls, a pulse is truncated to |t - t0| < sqrt(128 ln 2) |w| (about
  * 9.42 |w|), outside which its template is below 2^-64 of its peak. Blocks of
  * 64 samples that meet the support are evaluated whole. The truncation is far
  * under the FP32 resolution of the residual; only a component lying entirely
- * outside the sample range notices it, whose negligible gradient may then come
- * out as exactly zero. delta_logl_birth_death and smcx_plain_logl_grad
- * evaluate pulses on every sample.
+ * outside the sample range notices it, whose negligible gradient (or, in
+ * delta_logl_birth_death, change) may then come out as exactly zero.
+ * smcx_plain_logl_grad evaluates pulses on every sample.
  *
  * Errors. Every call returns SMCX_OK or a negative code and never throws
  * across the ABI; smcx_last_error() gives a message for the calling thread.

@@ -488,22 +488,13 @@ __device__ __forceinline__ void gb_moments(float A, float B, float C, float& c0,
   c2 = __builtin_fmaf((float)(2 * S + 1), c1, __builtin_fmaf(-(float)(S * S + S), A, 2.f * C));
 }
 
-template <int S, bool LIN, int J = 0>
-__device__ __forceinline__ void gb_sub2_j(const GbTile& t, unsigned int F, float A, float (&r1)[S],
-                                          float (&r2)[S]) {
+// fn(j, sin(phase)) at the lane's samples of a tile (for birth/death).
+template <int S, bool LIN, int J = 0, class F>
+__device__ __forceinline__ void gb_each_j(const GbTile& t, unsigned int F0, F fn) {
   if constexpr (J < S) {
-    const float s = __builtin_amdgcn_sinf(LIN ? gb_rev1(F) : gb_rev<J, LIN>(t, F));
-    r1[J] = __builtin_fmaf(-A, s, r1[J]);
-    r2[J] = __builtin_fmaf(-A, s, r2[J]);
-    gb_sub2_j<S, LIN, J + 1>(t, F + t.D, A, r1, r2);
-  }
-}
-
-template <int S, bool LIN, int J = 0>
-__device__ __forceinline__ void gb_val_j(const GbTile& t, unsigned int F, float A, float (&h)[S]) {
-  if constexpr (J < S) {
-    h[J] = A * __builtin_amdgcn_sinf(LIN ? gb_rev1(F) : gb_rev<J, LIN>(t, F));
-    gb_val_j<S, LIN, J + 1>(t, F + t.D, A, h);
+    fn(std::integral_constant<int, J>(),
+       __builtin_amdgcn_sinf(LIN ? gb_rev1(F0) : gb_rev<J, LIN>(t, F0)));
+    gb_each_j<S, LIN, J + 1>(t, F0 + t.D, fn);
   }
 }
 
@@ -560,28 +551,46 @@ struct Model<SMCX_PULSE> {
       if ((lane & 15) == 0 && lane < 48) *ap = prev + (double)tot;
     }
   }
-  // Template values of one component on the tile (for birth/death).
+  // Birth/death: one component's template off one residual, or off two with
+  // the same values, and fn(j, h) for its values on the tile, all over the
+  // block groups that meet the support.
   template <int S, bool LIN = true>
-  __device__ static void values(const C& c, int64_t tile, int lane, float (&h)[S]) {
-    const float base = (float)(int)(tile + lane) - c.nf;
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-      const float dj = base + (float)(64 * j);
-      const float z = __builtin_fmaf(dj, c.a, -c.fa);
-      h[j] = c.A * __builtin_amdgcn_exp2f(-(z * z));
-    }
+  __device__ static void sub1(const C& c, int64_t tile, int lane, float (&r)[S]) {
+    each<S>(c, tile, lane, [&](auto j, float e) { r[j] = __builtin_fmaf(-c.A, e, r[j]); });
   }
   template <int S, bool LIN = true>
   __device__ static void sub2(const C& c, int64_t tile, int lane, float (&r1)[S], float (&r2)[S]) {
-    const float base = (float)(int)(tile + lane) - c.nf;
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-      const float dj = base + (float)(64 * j);
-      const float z = __builtin_fmaf(dj, c.a, -c.fa);
-      const float e = __builtin_amdgcn_exp2f(-(z * z));
+    each<S>(c, tile, lane, [&](auto j, float e) {
       r1[j] = __builtin_fmaf(-c.A, e, r1[j]);
       r2[j] = __builtin_fmaf(-c.A, e, r2[j]);
+    });
+  }
+  template <int S, bool LIN = true, class F>
+  __device__ static void values(const C& c, int64_t tile, int lane, F fn) {
+    each<S>(c, tile, lane, [&](auto j, float e) { fn(j, c.A * e); });
+  }
+  // fn(j, exp(-x^2 / 2 w^2)) at the lane's samples tile + 64 j + lane
+  template <int S, int J = 0, class F>
+  __device__ static void each(const C& c, int64_t tile, int lane, F fn) {
+    asm volatile("" ::"v"(c.nf), "v"(c.a), "v"(c.fa), "v"(c.A));  // one LDS round trip
+    const unsigned int groups = __builtin_amdgcn_readfirstlane(c.groups);
+    if (groups) each_j<S, 0>(c, (float)(int)(tile + lane) - c.nf, groups, fn);
+  }
+  template <int S, int J, class F>
+  __device__ static void each_j(const C& c, float base, unsigned int groups, F fn) {
+    if constexpr (J < S) {
+      static_assert(kPulseGroup == 2, "two blocks per group");
+      if (__builtin_expect((groups >> (J / kPulseGroup)) & 1u, 1u)) {
+        each_at<J>(c, base, fn);
+        each_at<J + 1>(c, base, fn);
+      }
+      each_j<S, J + kPulseGroup>(c, base, groups, fn);
     }
+  }
+  template <int J, class F>
+  __device__ static void each_at(const C& c, float base, F fn) {
+    const float z = __builtin_fmaf(base + (float)(64 * J), c.a, -c.fa);
+    fn(std::integral_constant<int, J>(), __builtin_amdgcn_exp2f(-(z * z)));
   }
   // g = beta/sigma^2 * sum_s r_s dh/dtheta from the accumulated sums
   // S0 = sum r e, S1 = sum r e z, S2 = -sum r e z^2 with z = a x (x in samples).
@@ -655,15 +664,26 @@ struct Model<SMCX_GBSINE> {
       if ((lane & 15) == 0) *ap = prev + (double)tot;
     }
   }
-  template <int S, bool LIN>
-  __device__ static void values(const C& c, int64_t tile, int lane, float (&h)[S]) {
+  // birth/death, as for the pulses, over the whole tile
+  template <int S, bool LIN, class F>
+  __device__ static void each(const C& c, int64_t tile, int lane, F fn) {
     const GbTile t = gb_tile<LIN, S>(c, (double)(tile + lane));
-    gb_val_j<S, LIN>(t, t.F0, c.A, h);
+    gb_each_j<S, LIN>(t, t.F0, fn);
+  }
+  template <int S, bool LIN>
+  __device__ static void sub1(const C& c, int64_t tile, int lane, float (&r)[S]) {
+    each<S, LIN>(c, tile, lane, [&](auto j, float e) { r[j] = __builtin_fmaf(-c.A, e, r[j]); });
   }
   template <int S, bool LIN>
   __device__ static void sub2(const C& c, int64_t tile, int lane, float (&r1)[S], float (&r2)[S]) {
-    const GbTile t = gb_tile<LIN, S>(c, (double)(tile + lane));
-    gb_sub2_j<S, LIN>(t, t.F0, c.A, r1, r2);
+    each<S, LIN>(c, tile, lane, [&](auto j, float e) {
+      r1[j] = __builtin_fmaf(-c.A, e, r1[j]);
+      r2[j] = __builtin_fmaf(-c.A, e, r2[j]);
+    });
+  }
+  template <int S, bool LIN, class F>
+  __device__ static void values(const C& c, int64_t tile, int lane, F fn) {
+    each<S, LIN>(c, tile, lane, [&](auto j, float e) { fn(j, c.A * e); });
   }
   // sums: S_sin = sum r sin, C0 = sum r cos, C1 = sum r cos s, C2 = sum r cos s^2.
   __device__ static void scale(const double* th, const double* sums, double bs, const PopArgs& a,
@@ -1186,77 +1206,80 @@ __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
 // One pass per (particle, chunk): r (all components) and r_-j (all but j)
 // in index order, the templates of the death candidate j and of the birth
 // candidate, and four FP64 inner products per lane.
+// Up to component j the two residuals are the same and one is kept; without a
+// death, or without a birth, there is only one. A pulse's template is taken
+// over the block groups of its truncation support, as in the likelihood
+// passes: beyond it the template is below 2^-64 of its peak, which neither an
+// FP32 residual nor the FP64 sums can show (the sums of the candidate's own
+// template are skipped there too). The candidates' templates are formed again
+// for the inner products instead of held through the pass, which leaves
+// registers for seven waves per SIMD (pulses) instead of four. VALU issue
+// bounds it: 8192 pulse particles, K on 0..20, T = 4096, birth and death:
+// 102 -> 59 us; 500 sinusoid particles, K on 0..30, T = 2^17: 322 -> 286 us.
+// (An unbranched path for tiles inside the support spills; four block groups
+// at a time instead of two is three times slower.)
+
+// Adds one candidate's <r, h> and <h, h> over the tile to the lane's sums.
+template <int MODEL, int S, bool LIN>
+__device__ __forceinline__ void delta_sums(const PopArgs& a, const typename Model<MODEL>::C& c,
+                                           int64_t tile, int lane, int64_t ce, bool split, double bw,
+                                           const float (&r)[S], double& x, double& y) {
+  const int nv = (int)min(ce - tile, (int64_t)(64 * S)) - lane;
+  if (!split) {
+    Model<MODEL>::template values<S, LIN>(c, tile, lane, [&](auto j, float h) {
+      const bool ok = 64 * j < nv;
+      const double r1 = ok ? (double)r[j] : 0.0, h1 = ok ? (double)h : 0.0;
+      x = fma(r1, h1, x);
+      y = fma(h1, h1, y);
+    });
+  } else {  // per-sample weight: 1 before the split, beta after (products of floats are exact)
+    Model<MODEL>::template values<S, LIN>(c, tile, lane, [&](auto j, float h) {
+      const bool ok = 64 * j < nv;
+      const double r1 = ok ? (double)r[j] : 0.0, h1 = ok ? (double)h : 0.0;
+      const double ws = tile + 64 * j + lane < a.split ? 1.0 : bw;
+      x = fma(ws, r1 * h1, x);
+      y = fma(ws, h1 * h1, y);
+    });
+  }
+}
+
 // The tiles of one birth/death work item: the four inner products of the lane.
 template <int MODEL, int S, bool LIN>
-__device__ __forceinline__ void delta_tiles(const PopArgs& a, const typename Model<MODEL>::C* cst,
+__device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MODEL>::C* cst,
                                             int K, int j_death, bool birth, int lane, int64_t cs,
                                             int64_t ce, bool split, double bw, double& xb,
                                             double& yb, double& xd, double& yd) {
   using M = Model<MODEL>;
-  using C = typename M::C;
+  const int shared = j_death < 0 ? K : j_death;  // components the two residuals share
   for (int64_t tile = cs; tile < ce; tile += 64 * S) {
-    float rf[S], rn[S], hj[S];
+    float rf[S], rn[S];
     const float* dp = a.d32 + tile + lane;
 #pragma unroll
-    for (int jj = 0; jj < S; ++jj) {
-      rf[jj] = dp[64 * jj];
-      rn[jj] = rf[jj];
-      hj[jj] = 0.f;
-    }
-    for (int k = 0; k < K; ++k) {
-      const C cc = cst[k];
-      if (k == j_death) {
-        M::template values<S, LIN>(cc, tile, lane, hj);
-        // r (all components) still subtracts h_j, with the same fma as below
-        float dummy[S];
+    for (int jj = 0; jj < S; ++jj) rf[jj] = dp[64 * jj];
+    M::template prepare<S>(cst, K + (birth ? 1 : 0), tile, lane);
+    for (int k = 0; k < shared; ++k) M::template sub1<S, LIN>(cst[k], tile, lane, rf);
+    if (j_death >= 0) {
 #pragma unroll
-        for (int jj = 0; jj < S; ++jj) dummy[jj] = 0.f;
-        M::template sub2<S, LIN>(cc, tile, lane, rf, dummy);
+      for (int jj = 0; jj < S; ++jj) rn[jj] = rf[jj];
+      if (birth) {
+        M::template sub1<S, LIN>(cst[j_death], tile, lane, rf);
+        for (int k = j_death + 1; k < K; ++k) M::template sub2<S, LIN>(cst[k], tile, lane, rf, rn);
       } else {
-        M::template sub2<S, LIN>(cc, tile, lane, rf, rn);
+        for (int k = j_death + 1; k < K; ++k) M::template sub1<S, LIN>(cst[k], tile, lane, rn);
       }
+      delta_sums<MODEL, S, LIN>(a, cst[j_death], tile, lane, ce, split, bw, rn, xd, yd);
     }
-    float hn[S];
-    if (birth) {
-      M::template values<S, LIN>(cst[K], tile, lane, hn);
-    } else {
-#pragma unroll
-      for (int jj = 0; jj < S; ++jj) hn[jj] = 0.f;
-    }
-    const int nv = (int)min(ce - tile, (int64_t)(64 * S)) - lane;
-    if (!split) {
-#pragma unroll
-      for (int jj = 0; jj < S; ++jj) {
-        const bool ok = 64 * jj < nv;
-        const double r1 = ok ? (double)rf[jj] : 0.0;
-        const double r2 = ok ? (double)rn[jj] : 0.0;
-        const double h1 = ok ? (double)hn[jj] : 0.0;
-        const double h2 = ok ? (double)hj[jj] : 0.0;
-        xb = fma(r1, h1, xb);
-        yb = fma(h1, h1, yb);
-        xd = fma(r2, h2, xd);
-        yd = fma(h2, h2, yd);
-      }
-    } else {  // per-sample weight: 1 before the split, beta after (products of floats are exact)
-#pragma unroll
-      for (int jj = 0; jj < S; ++jj) {
-        const bool ok = 64 * jj < nv;
-        const double r1 = ok ? (double)rf[jj] : 0.0;
-        const double r2 = ok ? (double)rn[jj] : 0.0;
-        const double h1 = ok ? (double)hn[jj] : 0.0;
-        const double h2 = ok ? (double)hj[jj] : 0.0;
-        const double ws = tile + 64 * jj + lane < a.split ? 1.0 : bw;
-        xb = fma(ws, r1 * h1, xb);
-        yb = fma(ws, h1 * h1, yb);
-        xd = fma(ws, r2 * h2, xd);
-        yd = fma(ws, h2 * h2, yd);
-      }
-    }
+    if (birth) delta_sums<MODEL, S, LIN>(a, cst[K], tile, lane, ce, split, bw, rf, xb, yb);
   }
 }
 
 template <int MODEL, int S>
-__global__ __launch_bounds__(256, (S <= 8 ? 6 : 4)) void delta_kernel(PopArgs a) {
+constexpr int delta_waves_per_simd() {  // what the registers allow without spills
+  return S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 5);
+}
+
+template <int MODEL, int S>
+__global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta_kernel(PopArgs a) {
   using M = Model<MODEL>;
   using C = typename M::C;
   constexpr int P = M::P;
@@ -1267,12 +1290,13 @@ __global__ __launch_bounds__(256, (S <= 8 ? 6 : 4)) void delta_kernel(PopArgs a)
   const int64_t item = (int64_t)blockIdx.x * wpb + wid;
   Item it;
   if (!decode_item(a, item, lane, P, true, it)) return;
-  const int c = it.c;
-  const int i = it.i;
-  const int64_t m0 = it.m0;
-  const int K = it.K;
+  // one wave per item: make the item's fields scalar
+  const int c = __builtin_amdgcn_readfirstlane(it.c);
+  const int i = __builtin_amdgcn_readfirstlane(it.i);
+  const int64_t m0 = uniform_i64(it.m0);
+  const int K = __builtin_amdgcn_readfirstlane(it.K);
   if (a.active && !a.active[i]) return;
-  const int j_death = a.death_idx ? a.death_idx[i] : -1;
+  const int j_death = __builtin_amdgcn_readfirstlane(a.death_idx ? a.death_idx[i] : -1);
   const bool birth = a.theta_birth != nullptr;
   if (!birth && j_death < 0) {  // nothing to evaluate: no birth, no death
     if (c == 0 && lane == 0) a.dlogl_death[i] = 0.0;
@@ -1294,17 +1318,22 @@ __global__ __launch_bounds__(256, (S <= 8 ? 6 : 4)) void delta_kernel(PopArgs a)
   // other components (or candidates) the two calls see
   delta_tiles<MODEL, S, MODEL != SMCX_GBSINE>(a, cst, K, j_death, birth, lane, cs, ce, split, bw,
                                               xb, yb, xd, yd);
-  xb = lane63_d(wave_sum_d(xb));
-  yb = lane63_d(wave_sum_d(yb));
-  xd = lane63_d(wave_sum_d(xd));
-  yd = lane63_d(wave_sum_d(yd));
+  const PopArgs z = late_args();
+  if (birth) {
+    xb = lane63_d(wave_sum_d(xb));
+    yb = lane63_d(wave_sum_d(yb));
+  }
+  if (j_death >= 0) {
+    xd = lane63_d(wave_sum_d(xd));
+    yd = lane63_d(wave_sum_d(yd));
+  }
   if (lane != 0) return;
-  if (a.nch == 1) {
+  if (z.nch == 1) {
     const double b = split ? 1.0 : bw;  // tempering still to apply
-    if (birth) a.dlogl_birth[i] = b * (xb - 0.5 * yb) * a.inv_sigma2;
-    if (a.death_idx) a.dlogl_death[i] = j_death < 0 ? 0.0 : -(b * (xd - 0.5 * yd) * a.inv_sigma2);
+    if (birth) z.dlogl_birth[i] = b * (xb - 0.5 * yb) * z.inv_sigma2;
+    if (z.death_idx) z.dlogl_death[i] = j_death < 0 ? 0.0 : -(b * (xd - 0.5 * yd) * z.inv_sigma2);
   } else {
-    double* dst = a.part + ((size_t)c * a.N + i) * 4;
+    double* dst = z.part + ((size_t)c * z.N + i) * 4;
     dst[0] = xb;
     dst[1] = yb;
     dst[2] = xd;
