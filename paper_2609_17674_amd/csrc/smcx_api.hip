@@ -167,6 +167,7 @@ void free_problem(smcx_problem* p) {
   (void)hipFree(p->smc.skip);
   (void)hipFree(p->smc.append);
   (void)hipFree(p->smc.count);
+  (void)hipFree(p->smc.tiles);
   (void)hipFree(p->flag);
   (void)hipFree(p->part);
   (void)hipFree(p->part_g);
@@ -491,6 +492,7 @@ int smcx_problem_create(int model, const double* d_dev, int64_t T, double t_star
       {(void**)&p->smc.skip, n1 * sizeof(int32_t)},
       {(void**)&p->smc.append, n1 * sizeof(int32_t)},
       {(void**)&p->smc.count, n1 * sizeof(int64_t)},
+      {(void**)&p->smc.tiles, 2 * smcx::kScanTiles * sizeof(int64_t)},
       {(void**)&p->flag, sizeof(int)},
       {(void**)&p->part, part_elems * sizeof(double)},
       {(void**)&p->part_g, partg_elems * sizeof(double)},
@@ -591,6 +593,7 @@ int smcx_problem_create_fd(int model, const double* d_dev, int64_t k0, int64_t B
       {(void**)&p->smc.skip, n1 * sizeof(int32_t)},
       {(void**)&p->smc.append, n1 * sizeof(int32_t)},
       {(void**)&p->smc.count, n1 * sizeof(int64_t)},
+      {(void**)&p->smc.tiles, 2 * smcx::kScanTiles * sizeof(int64_t)},
       {(void**)&p->flag, sizeof(int)},
       {(void**)&p->part, n1 * 4 * sizeof(double)},
       {(void**)&p->part_g, sizeof(double)},

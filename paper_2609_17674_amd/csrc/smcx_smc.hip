@@ -4,13 +4,15 @@
 // resampling, the accept/reject of birth and death moves (eq. rj_acceptance),
 // and the CSR rebuild the last two share.
 //
-// Population-wide reductions run in one block with a fixed combination order
-// (butterfly within a wave, then waves in order), so results do not depend on
-// timing. Resampling works on integer weights so that its prefix sums, and
-// therefore the ancestors, are exact.
+// Population-wide sums of reals have a fixed order of additions (butterfly
+// within a wave, then waves, then workgroups in order), so results do not
+// depend on timing. Resampling works on integer weights so that its prefix
+// sums, and therefore the ancestors, are exact however they are grouped.
 #include "smcx_internal.h"
 
 #include <math.h>
+
+#include <algorithm>
 
 namespace smcx {
 namespace {
@@ -40,63 +42,40 @@ __device__ void block_sum2(double& a, double& b, double* sh) {
   }
 }
 
-// Loads per batch in the single-block prefix passes: the loads of a batch are
-// in flight together.
-constexpr int kScanBatch = 16;
+// ---------------------------------------------------------------- prefix sums over tiles
+// The rebuild passes cut the items into at most kScanTiles tiles of a whole
+// number of workgroup widths, one workgroup per tile: it leaves prefix sums
+// within its tile and the tile's sum, and the next launch's workgroups add the
+// sums of the tiles before theirs. Integer sums are exact, so the grouping
+// does not change them. (One workgroup over the whole population, with the
+// loads of 16 waves to hide its latency: 40000 items took 39 and 50 us per
+// prefix pass; these launches take 3 to 7.)
+constexpr int kScanBlock = 256;
 
-// Prefix sums over the block of the int64 values value(i), i < N, for the
-// single-block rebuild passes: wave w takes a contiguous segment of items in
-// chunks of 64, lane l holding item c + l, so every load is coalesced and
-// kScanBatch chunks are in flight together. out(i, before, through) receives
-// the sums of the items before i and through i. Integer sums are exact, so
-// the grouping does not change them. Returns the total (all threads).
-template <class Val, class Out>
-__device__ int64_t block_prefix(int64_t N, Val value, Out out, int64_t* wsum) {
+__host__ __device__ inline int64_t scan_tile(int64_t N) {
+  const int64_t per = (int64_t)kScanBlock * kScanTiles;
+  return kScanBlock * ((N + per - 1) / per);
+}
+
+// Inclusive prefix sum of v over the workgroup's threads; sum receives the
+// total. All threads call it; wsum is kScanBlock / 64 words of LDS.
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t& sum, int64_t* wsum) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t seg = ((N + kBlockWaves - 1) / kBlockWaves + 63) / 64 * 64;
-  const int64_t s0 = (int64_t)w * seg, s1 = s0 + seg < N ? s0 + seg : N;
-  constexpr int64_t kSpan = 64 * kScanBatch;
-  int64_t s = 0;
-  for (int64_t c0 = s0; c0 < s1; c0 += kSpan) {
-    int64_t v[kScanBatch];
-#pragma unroll
-    for (int u = 0; u < kScanBatch; ++u) {
-      const int64_t i = c0 + 64 * u + lane;
-      v[u] = i < s1 ? value(i) : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kScanBatch; ++u) s += v[u];
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t y = __shfl_up(v, o);
+    if (lane >= o) v += y;
   }
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-  if (lane == 0) wsum[w] = s;
+  __syncthreads();  // the previous call's words have been read
+  if (lane == 63) wsum[w] = v;
   __syncthreads();
-  int64_t run = 0, total = 0;
-  for (int i = 0; i < kBlockWaves; ++i) {
+  sum = 0;
+#pragma unroll
+  for (int i = 0; i < kScanBlock / 64; ++i) {
     const int64_t x = wsum[i];
-    run += i < w ? x : 0;
-    total += x;
+    v += i < w ? x : 0;
+    sum += x;
   }
-  __syncthreads();  // wsum may be reused
-  for (int64_t c0 = s0; c0 < s1; c0 += kSpan) {
-    int64_t v[kScanBatch];
-#pragma unroll
-    for (int u = 0; u < kScanBatch; ++u) {
-      const int64_t i = c0 + 64 * u + lane;
-      v[u] = i < s1 ? value(i) : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kScanBatch; ++u) {
-      int64_t x = v[u];
-      for (int o = 1; o < 64; o <<= 1) {
-        const int64_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-      }
-      const int64_t i = c0 + 64 * u + lane;
-      if (i < s1) out(i, run + x - v[u], run + x);
-      run += __shfl(x, 63);
-    }
-  }
-  return total;
+  return v;
 }
 
 __device__ double block_max(double a, double* sh) {
@@ -277,12 +256,6 @@ struct NbMultiArgs {
   int G;
 };
 
-__device__ __forceinline__ double nb_max_l(const NbMultiArgs& a) {
-  double L = -INFINITY;
-  for (int g = 0; g < a.G; ++g) L = fmax(L, a.pmax[g]);
-  return L;
-}
-
 // The search's step after an evaluation at st[kX] with sums (s1, s2); the
 // same arithmetic as next_beta_kernel's bracketing search.
 __device__ void nb_advance(const NbMultiArgs& a, double* st, double s1, double s2) {
@@ -339,6 +312,55 @@ __device__ void nb_advance(const NbMultiArgs& a, double* st, double s1, double s
   st[kX] = x;
 }
 
+// The search state before launch k in st: launch k - 1's, advanced by its
+// evaluation. All threads call it. The workgroups' sums come in by all threads
+// and are added in workgroup order, s1 by thread 0 and s2 by thread 1: a
+// thread that also loaded them took most of an evaluation launch (7.6 -> 5.0 us
+// with 40 workgroups). ch is 2 NT words of LDS.
+template <int NT>
+__device__ void nb_state(const NbMultiArgs& a, int k, double* st, double* ch) {
+  const int tid = threadIdx.x;
+  if (k == 0) {
+    double L = -INFINITY;
+    for (int g = tid; g < a.G; g += NT) L = fmax(L, a.pmax[g]);
+    for (int o = 32; o >= 1; o >>= 1) L = fmax(L, __shfl_xor(L, o));
+    if ((tid & 63) == 0) ch[tid >> 6] = L;
+    if (tid < kNbState) st[tid] = 0.0;
+    __syncthreads();
+    if (tid == 0) {
+      for (int w = 1; w < NT / 64; ++w) L = fmax(L, ch[w]);
+      st[kX] = 1.0;
+      st[kL] = L;
+    }
+    __syncthreads();
+    return;
+  }
+  const double* ps = a.psum + (size_t)((k - 1) & 1) * a.G * 2;
+  const double* prev = a.state + ((k - 1) & 1) * kNbState;
+  if (tid < kNbState) st[tid] = prev[tid];
+  if (prev[kPhase] == 2.0) {
+    __syncthreads();
+    return;
+  }
+  double s = 0.0;
+  for (int g0 = 0; g0 < a.G; g0 += NT) {
+    const int n = a.G - g0 < NT ? a.G - g0 : NT;
+    if (g0) __syncthreads();
+    if (tid < n) {
+      ch[tid] = ps[2 * (g0 + tid)];
+      ch[NT + tid] = ps[2 * (g0 + tid) + 1];
+    }
+    __syncthreads();
+    if (tid < 2) {
+#pragma unroll 8
+      for (int g = 0; g < n; ++g) s += ch[tid * NT + g];
+    }
+  }
+  const double s2 = __shfl(s, 1);
+  if (tid == 0) nb_advance(a, st, s, s2);
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(kNbBlock) void nb_max_kernel(NbMultiArgs a) {
   __shared__ double sh[kNbBlock / 64];
   const int64_t base = (int64_t)blockIdx.x * kNbSlice;
@@ -362,41 +384,27 @@ __global__ __launch_bounds__(kNbBlock) void nb_max_kernel(NbMultiArgs a) {
 // evaluate the new point.
 __global__ __launch_bounds__(kNbBlock) void nb_eval_kernel(NbMultiArgs a, int k) {
   __shared__ double st[kNbState];
-  __shared__ double sh[2 * (kNbBlock / 64)];
-  if (threadIdx.x == 0) {
-    if (k == 0) {
-      for (int q = 0; q < kNbState; ++q) st[q] = 0.0;
-      st[kX] = 1.0;
-      st[kL] = nb_max_l(a);
-    } else {
-      const double* prev = a.state + ((k - 1) & 1) * kNbState;
-      for (int q = 0; q < kNbState; ++q) st[q] = prev[q];
-      if (st[kPhase] != 2.0) {
-        const double* ps = a.psum + (size_t)((k - 1) & 1) * a.G * 2;
-        double s1 = 0.0, s2 = 0.0;
-        for (int g = 0; g < a.G; ++g) {
-          s1 += ps[2 * g];
-          s2 += ps[2 * g + 1];
-        }
-        nb_advance(a, st, s1, s2);
-      }
-    }
-    if (blockIdx.x == 0) {
-      double* cur = a.state + (k & 1) * kNbState;
-      for (int q = 0; q < kNbState; ++q) cur[q] = st[q];
-    }
+  __shared__ double sh[2 * kNbBlock];
+  // the particles' values come in under the search's step
+  const int64_t base = (int64_t)blockIdx.x * kNbSlice;
+  double l[kNbPer];
+#pragma unroll
+  for (int u = 0; u < kNbPer; ++u) {
+    const int64_t i = base + u * kNbBlock + threadIdx.x;
+    l[u] = i < a.N ? a.logl[i] : 0.0;
   }
-  __syncthreads();
+  nb_state<kNbBlock>(a, k, st, sh);
+  if (blockIdx.x == 0 && threadIdx.x < kNbState)
+    a.state[(k & 1) * kNbState + threadIdx.x] = st[threadIdx.x];
   if (st[kPhase] == 2.0) return;
   const double db = st[kX] - a.beta_prev;
   const double m = db * st[kL];
-  const int64_t base = (int64_t)blockIdx.x * kNbSlice;
   double s1 = 0.0, s2 = 0.0;
 #pragma unroll
   for (int u = 0; u < kNbPer; ++u) {
     const int64_t i = base + u * kNbBlock + threadIdx.x;
     if (i < a.N) {
-      const double e = exp(db * a.logl[i] - m);
+      const double e = exp(db * l[u] - m);
       s1 += e;
       s2 += e * e;
     }
@@ -405,6 +413,7 @@ __global__ __launch_bounds__(kNbBlock) void nb_eval_kernel(NbMultiArgs a, int k)
     s1 += __shfl_xor(s1, o);
     s2 += __shfl_xor(s2, o);
   }
+  __syncthreads();  // sh has been read
   if ((threadIdx.x & 63) == 0) {
     sh[threadIdx.x >> 6] = s1;
     sh[kNbBlock / 64 + (threadIdx.x >> 6)] = s2;
@@ -422,26 +431,17 @@ __global__ __launch_bounds__(kNbBlock) void nb_eval_kernel(NbMultiArgs a, int k)
   }
 }
 
-// One block: take the step after the last queued evaluation and, should the
-// search still be running, finish it with block-wide evaluations.
-__global__ __launch_bounds__(kBlock) void nb_finish_kernel(NbMultiArgs a) {
+// After the last queued evaluation: every workgroup takes the step from it
+// and, should the search still be running, finishes it over the whole
+// population (the same bits in each, so at most kNbFinish of them); then the
+// weights at the chosen beta (eq. incremental_weight), normalised by the kept
+// sums, and the scalars.
+constexpr int kNbFinish = 256;
+
+__global__ __launch_bounds__(kBlock) void nb_weights_kernel(NbMultiArgs a) {
   __shared__ double st[kNbState];
-  __shared__ double sh[2 * kBlockWaves];
-  constexpr int k = kNbLaunches;  // the step after launch kNbLaunches - 1
-  if (threadIdx.x == 0) {
-    const double* prev = a.state + ((k - 1) & 1) * kNbState;
-    for (int q = 0; q < kNbState; ++q) st[q] = prev[q];
-    if (st[kPhase] != 2.0) {
-      const double* ps = a.psum + (size_t)((k - 1) & 1) * a.G * 2;
-      double s1 = 0.0, s2 = 0.0;
-      for (int g = 0; g < a.G; ++g) {
-        s1 += ps[2 * g];
-        s2 += ps[2 * g + 1];
-      }
-      nb_advance(a, st, s1, s2);
-    }
-  }
-  __syncthreads();
+  __shared__ double sh[2 * kBlock];
+  nb_state<kBlock>(a, kNbLaunches, st, sh);
   while (st[kPhase] != 2.0) {
     const double db = st[kX] - a.beta_prev;
     const double m = db * st[kL];
@@ -456,28 +456,14 @@ __global__ __launch_bounds__(kBlock) void nb_finish_kernel(NbMultiArgs a) {
     if (threadIdx.x == 0) nb_advance(a, st, s1, s2);
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    double* cur = a.state + (k & 1) * kNbState;
-    for (int q = 0; q < kNbState; ++q) cur[q] = st[q];
-  }
-}
-
-// Weights at the chosen beta (eq. incremental_weight), normalised by the
-// kept sums, and the scalars.
-__global__ __launch_bounds__(kNbBlock) void nb_weights_kernel(NbMultiArgs a) {
-  const double* st = a.state + (kNbLaunches & 1) * kNbState;
   const double beta = st[kBeta], db = beta - a.beta_prev;
   const double m = db * st[kL], s1 = st[kS1];
-  const int64_t base = (int64_t)blockIdx.x * kNbSlice;
-#pragma unroll
-  for (int u = 0; u < kNbPer; ++u) {
-    const int64_t i = base + u * kNbBlock + threadIdx.x;
-    if (i < a.N) {
-      const double lw = db * a.logl[i];
-      a.logw[i] = lw;
-      a.w_norm[i] = exp(lw - m) / s1;
-      if (a.beta_out) a.beta_out[i] = beta;
-    }
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < a.N;
+       i += (int64_t)gridDim.x * kBlock) {
+    const double lw = db * a.logl[i];
+    a.logw[i] = lw;
+    a.w_norm[i] = exp(lw - m) / s1;
+    if (a.beta_out) a.beta_out[i] = beta;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.scalars[0] = beta;
@@ -501,7 +487,8 @@ struct RebuildArgs {
   int32_t* src_len;   // [N]
   int32_t* skip;      // [N]
   int32_t* append;    // [N]
-  int64_t* count;     // [N] rows of output particle j
+  int64_t* first;     // [N] first output row of particle j within its tile
+  int64_t* rows;      // [tiles] output rows of each tile
   const double* theta_add;  // [N][P] rows appended (births)
   int64_t* offsets_out;     // [N + 1]
   double* theta_out;        // [m_cap][P]
@@ -525,39 +512,88 @@ __device__ __forceinline__ bool source_rows(const RebuildArgs& a, int64_t i, int
   return true;
 }
 
-// Exclusive prefix sum of count[0..N) into offsets_out[0..N] (one block).
-__global__ __launch_bounds__(kBlock) void csr_scan_kernel(RebuildArgs a) {
-  __shared__ int64_t wsum[kBlockWaves];
-  const int64_t total = block_prefix(
-      a.N, [&](int64_t i) { return a.count[i]; },
-      [&](int64_t i, int64_t before, int64_t) { a.offsets_out[i] = before; }, wsum);
-  if (threadIdx.x == 0) {
-    a.offsets_out[a.N] = total;
-    if (total > a.m_cap) atomicOr(a.flag, kFlagCapacity);
-  }
+// Output particle j's first row within its tile (n rows; -1: no particle j),
+// and after the tile's last pass its sum.
+__device__ __forceinline__ void place_rows(const RebuildArgs& a, int64_t j, int32_t n,
+                                           int64_t& carry, int64_t* wsum) {
+  int64_t sum;
+  const int64_t through = block_scan(n > 0 ? n : 0, sum, wsum);
+  if (n >= 0) a.first[j] = carry + through - n;
+  carry += sum;
 }
 
-// One wave per output particle copies its rows; rows at or past m_cap are
-// not written (the capacity flag is raised by the scan).
-__global__ __launch_bounds__(256) void csr_gather_kernel(RebuildArgs a) {
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (j >= a.N) return;
-  const int64_t start = a.offsets_out[j];
-  const int64_t row = a.src_row[j];
-  const int32_t len = a.src_len[j], skip = a.skip[j];
+// Copies the output particles' rows, 16 lanes per particle, and places them
+// after the rows of the tiles before; rows at or past m_cap are not written
+// (the capacity flag is raised). A chain of dependent loads bounds it, so 16
+// particles share a workgroup and a lane has four loads in flight: 40000
+// particles of 5.5 rows of 8 doubles: 13 -> 10 us (a wave per particle before;
+// its 28 MB take 5.4 at the rate of a copy).
+constexpr int kGatherLanes = 16;
+constexpr int kGatherItems = kScanBlock / kGatherLanes;  // divides a tile
+
+__global__ __launch_bounds__(kScanBlock) void csr_gather_kernel(RebuildArgs a) {
+  __shared__ int64_t wsum[kScanBlock / 64];
+  const int64_t j = (int64_t)blockIdx.x * kGatherItems + threadIdx.x / kGatherLanes;
+  const int lane = threadIdx.x % kGatherLanes;
+  const bool live = j < a.N;
+  int64_t start = 0, row = 0;
+  int32_t len = 0, skip = -1, add = 0;
+  if (live) {
+    start = a.first[j];
+    row = a.src_row[j];
+    len = a.src_len[j];
+    skip = a.skip[j];
+    add = a.append[j];
+  }
+  // the rows are one run of values: the first batch comes in under the base
   const int P = a.P;
-  for (int64_t x = lane; x < (int64_t)len * P; x += 64) {
-    const int32_t k = (int32_t)(x / P);
-    const int p = (int)(x - (int64_t)k * P);
-    if (k == skip) continue;
-    const int64_t out = start + k - (skip >= 0 && k > skip ? 1 : 0);
-    if (out < a.m_cap) a.theta_out[out * P + p] = a.theta[(row + k) * P + p];
+  const double* src = a.theta + row * P;
+  const int n = len * P;
+  double v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int x = lane + u * kGatherLanes;
+    v[u] = x < n ? src[x] : 0.0;
   }
-  if (a.append[j] && lane < P) {
-    const int64_t out = start + len - (skip >= 0 ? 1 : 0);
-    if (out < a.m_cap) a.theta_out[out * P + lane] = a.theta_add[j * P + lane];
+  const int tiles = (int)((int64_t)blockIdx.x * kGatherItems / scan_tile(a.N));
+  int64_t before = 0;
+#pragma unroll
+  for (int u = 0; u < kScanTiles / kScanBlock; ++u) {
+    const int g = u * kScanBlock + threadIdx.x;
+    before += g < tiles ? a.rows[g] : 0;
   }
+  int64_t base;
+  block_scan(before, base, wsum);
+  if (!live) return;
+  start += base;
+  const int64_t end = start + len - (skip >= 0 ? 1 : 0) + (add ? 1 : 0);
+  if (lane == 0) {
+    a.offsets_out[j] = start;
+    if (j == a.N - 1) {
+      a.offsets_out[a.N] = end;
+      if (end > a.m_cap) atomicOr(a.flag, kFlagCapacity);
+    }
+  }
+  // the values after the skipped row move up by P
+  double* dst = a.theta_out + start * P;
+  const int64_t room = (a.m_cap - start) * P;  // values that may be written from dst on
+  const int s0 = skip >= 0 ? skip * P : n, s1 = s0 + P;
+  for (int x0 = lane;;) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int x = x0 + u * kGatherLanes, y = x < s0 ? x : x - P;
+      if (x < n && (x < s0 || x >= s1) && y < room) dst[y] = v[u];
+    }
+    x0 += 4 * kGatherLanes;
+    if (x0 >= n) break;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int x = x0 + u * kGatherLanes;
+      v[u] = x < n ? src[x] : 0.0;
+    }
+  }
+  if (add && end <= a.m_cap)
+    for (int p = lane; p < P; p += kGatherLanes) a.theta_out[(end - 1) * P + p] = a.theta_add[j * P + p];
 }
 
 // ---------------------------------------------------------------- resampling
@@ -565,52 +601,83 @@ struct ResampleArgs {
   RebuildArgs r;
   const double* w_norm;
   double u;
-  int64_t* cum;       // [N] inclusive prefix sums of the integer weights
+  int64_t* cum;       // [N] prefix sums, through i, of its tile's integer weights
+  int64_t* units;     // [tiles] integer weight of each tile
   int32_t* ancestors; // [N]
 };
 
 // Integer weights c_i = round(w_i 2^40) (0 unless w_i > 0) and their inclusive
-// prefix sums, exact in int64 (one block).
+// prefix sums within a tile, exact in int64.
 __device__ __forceinline__ int64_t weight_units(double w) {
   return w > 0.0 ? (int64_t)rint((w < 1.0 ? w : 1.0) * kWeightUnit) : 0;
 }
 
-__global__ __launch_bounds__(kBlock) void resample_prefix_kernel(ResampleArgs a) {
-  __shared__ int64_t wsum[kBlockWaves];
-  const int64_t total = block_prefix(
-      a.r.N, [&](int64_t i) { return weight_units(a.w_norm[i]); },
-      [&](int64_t i, int64_t, int64_t through) { a.cum[i] = through; }, wsum);
-  if (threadIdx.x == 0 && total <= 0) atomicOr(a.r.flag, kFlagWeights);
+__global__ __launch_bounds__(kScanBlock) void resample_prefix_kernel(ResampleArgs a) {
+  __shared__ int64_t wsum[kScanBlock / 64];
+  const int64_t N = a.r.N, tile = scan_tile(N), t0 = blockIdx.x * tile;
+  int64_t carry = 0;
+  for (int64_t i = t0 + threadIdx.x; i - threadIdx.x < t0 + tile; i += kScanBlock) {
+    int64_t sum;
+    const int64_t through = block_scan(i < N ? weight_units(a.w_norm[i]) : 0, sum, wsum);
+    if (i < N) a.cum[i] = carry + through;
+    carry += sum;
+  }
+  if (threadIdx.x == 0) a.units[blockIdx.x] = carry;
 }
 
-// Offspring j: position U_j = floor(((j + u) C) / N), ancestor = first i with
-// cum[i] > U_j (binary search); then its rows for the rebuild.
-__global__ __launch_bounds__(256) void resample_ancestor_kernel(ResampleArgs a) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t N = a.r.N;
-  if (j >= N) return;
-  const int64_t total = a.cum[N - 1];
-  int64_t anc = j;  // no positive weight: every particle keeps itself (flagged)
-  if (total > 0) {
-    int64_t U = (int64_t)floor(((double)j + a.u) * (double)total / (double)N);
-    if (U >= total) U = total - 1;
-    int64_t lo = 0, hi = N - 1;  // cum[hi] = total > U
-    while (lo < hi) {
-      const int64_t mid = lo + (hi - lo) / 2;
-      if (a.cum[mid] > U) hi = mid;
-      else lo = mid + 1;
-    }
-    anc = lo;
+// Offspring j: position U_j = floor(((j + u) C) / N), ancestor = first i whose
+// prefix sum exceeds U_j, by bisection of the tile sums in LDS and of the
+// tile (16-way steps, whose loads are in flight together, touch more lines and
+// took 12 us, this 7); then its rows for the rebuild.
+__global__ __launch_bounds__(kScanBlock) void resample_ancestor_kernel(ResampleArgs a) {
+  __shared__ int64_t wsum[kScanBlock / 64];
+  __shared__ int64_t through[kScanTiles];  // integer weight of the tiles through g
+  const int64_t N = a.r.N, tile = scan_tile(N), t0 = blockIdx.x * tile;
+  const int G = (int)((N + tile - 1) / tile);
+  int64_t total = 0;
+  for (int g0 = 0; g0 < G; g0 += kScanBlock) {
+    const int g = g0 + threadIdx.x;
+    int64_t sum;
+    const int64_t x = block_scan(g < G ? a.units[g] : 0, sum, wsum);
+    if (g < G) through[g] = total + x;
+    total += sum;
   }
-  a.ancestors[j] = (int32_t)anc;
-  int64_t row;
-  int32_t len;
-  source_rows(a.r, anc, row, len);
-  a.r.src_row[j] = row;
-  a.r.src_len[j] = len;
-  a.r.skip[j] = -1;
-  a.r.append[j] = 0;
-  a.r.count[j] = len;
+  __syncthreads();
+  if (total <= 0 && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(a.r.flag, kFlagWeights);
+  int64_t carry = 0;
+  for (int64_t j = t0 + threadIdx.x; j - threadIdx.x < t0 + tile; j += kScanBlock) {
+    int32_t len = -1;
+    if (j < N) {
+      int64_t anc = j;  // no positive weight: every particle keeps itself (flagged)
+      if (total > 0) {
+        int64_t U = (int64_t)floor(((double)j + a.u) * (double)total / (double)N);
+        if (U >= total) U = total - 1;
+        int g = 0;
+        for (int hi = G - 1; g < hi;) {  // through[hi] > U
+          const int mid = (g + hi) / 2;
+          if (through[mid] > U) hi = mid;
+          else g = mid + 1;
+        }
+        if (g) U -= through[g - 1];
+        int64_t lo = g * tile, last = lo + tile < N ? lo + tile - 1 : N - 1;
+        while (lo < last) {  // cum[last] > U
+          const int64_t mid = lo + (last - lo) / 2;
+          if (a.cum[mid] > U) last = mid;
+          else lo = mid + 1;
+        }
+        anc = lo;
+      }
+      a.ancestors[j] = (int32_t)anc;
+      int64_t row;
+      source_rows(a.r, anc, row, len);
+      a.r.src_row[j] = row;
+      a.r.src_len[j] = len;
+      a.r.skip[j] = -1;
+      a.r.append[j] = 0;
+    }
+    place_rows(a.r, j, len, carry, wsum);
+  }
+  if (threadIdx.x == 0) a.r.rows[blockIdx.x] = carry;
 }
 
 // ---------------------------------------------------------------- birth/death
@@ -631,39 +698,47 @@ struct RjArgs {
 // death of a valid index with K - 1 >= k_lo (the reading of eq. rj_acceptance
 // for exchangeable components, a birth proposal equal to the prior and a
 // uniform prior on K); accepted when log_u < log alpha.
-__global__ __launch_bounds__(256) void rj_decide_kernel(RjArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.r.N) return;
-  int64_t row;
-  int32_t K;
-  const bool ok = source_rows(a.r, i, row, K);
-  const int mv = a.move[i];
-  bool acc = false;
-  int32_t skip = -1;
-  if (ok && mv == 1 && a.r.theta_add && a.dlogl_birth && K + 1 <= a.k_hi) {
-    acc = a.log_u[i] < a.dlogl_birth[i] + a.log_pd_over_pb;
-  } else if (ok && mv == 2 && a.death_idx && a.dlogl_death && K - 1 >= a.k_lo) {
-    const int32_t j = a.death_idx[i];
-    if (j >= 0 && j < K) {
-      acc = a.log_u[i] < a.dlogl_death[i] - a.log_pd_over_pb;
-      if (acc) skip = j;
+__global__ __launch_bounds__(kScanBlock) void rj_decide_kernel(RjArgs a) {
+  __shared__ int64_t wsum[kScanBlock / 64];
+  const int64_t N = a.r.N, tile = scan_tile(N), t0 = blockIdx.x * tile;
+  int64_t carry = 0;
+  for (int64_t i = t0 + threadIdx.x; i - threadIdx.x < t0 + tile; i += kScanBlock) {
+    int32_t n = -1;
+    if (i < N) {
+      int64_t row;
+      int32_t K;
+      const bool ok = source_rows(a.r, i, row, K);
+      const int mv = a.move[i];
+      bool acc = false;
+      int32_t skip = -1;
+      if (ok && mv == 1 && a.r.theta_add && a.dlogl_birth && K + 1 <= a.k_hi) {
+        acc = a.log_u[i] < a.dlogl_birth[i] + a.log_pd_over_pb;
+      } else if (ok && mv == 2 && a.death_idx && a.dlogl_death && K - 1 >= a.k_lo) {
+        const int32_t j = a.death_idx[i];
+        if (j >= 0 && j < K) {
+          acc = a.log_u[i] < a.dlogl_death[i] - a.log_pd_over_pb;
+          if (acc) skip = j;
+        }
+      }
+      a.accepted[i] = acc ? 1 : 0;
+      a.r.src_row[i] = row;
+      a.r.src_len[i] = K;
+      a.r.skip[i] = skip;
+      a.r.append[i] = (acc && mv == 1) ? 1 : 0;
+      n = K + (acc ? (mv == 1 ? 1 : -1) : 0);
     }
+    place_rows(a.r, i, n, carry, wsum);
   }
-  a.accepted[i] = acc ? 1 : 0;
-  a.r.src_row[i] = row;
-  a.r.src_len[i] = K;
-  a.r.skip[i] = skip;
-  a.r.append[i] = (acc && mv == 1) ? 1 : 0;
-  a.r.count[i] = K + (acc ? (mv == 1 ? 1 : -1) : 0);
+  if (threadIdx.x == 0) a.r.rows[blockIdx.x] = carry;
 }
 
-hipError_t launch_rebuild(const RebuildArgs& r, hipStream_t st) {
-  hipLaunchKernelGGL(csr_scan_kernel, dim3(1), dim3(kBlock), 0, st, r);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(csr_gather_kernel, dim3((unsigned)((r.N + 3) / 4)), dim3(256), 0, st, r);
+hipError_t launch_gather(const RebuildArgs& r, hipStream_t st) {
+  hipLaunchKernelGGL(csr_gather_kernel, dim3((unsigned)((r.N + kGatherItems - 1) / kGatherItems)),
+                     dim3(kScanBlock), 0, st, r);
   return hipGetLastError();
 }
+
+unsigned scan_tiles(int64_t N) { return (unsigned)((N + scan_tile(N) - 1) / scan_tile(N)); }
 
 }  // namespace
 
@@ -694,8 +769,8 @@ hipError_t launch_next_beta(int64_t N, const double* logl, const double* logw_pr
   const dim3 grid((unsigned)G), block(kNbBlock);
   hipLaunchKernelGGL(nb_max_kernel, grid, block, 0, st, a);
   for (int k = 0; k < kNbLaunches; ++k) hipLaunchKernelGGL(nb_eval_kernel, grid, block, 0, st, a, k);
-  hipLaunchKernelGGL(nb_finish_kernel, dim3(1), dim3(kBlock), 0, st, a);
-  hipLaunchKernelGGL(nb_weights_kernel, grid, block, 0, st, a);
+  const int64_t gw = std::min<int64_t>((N + kBlock - 1) / kBlock, kNbFinish);
+  hipLaunchKernelGGL(nb_weights_kernel, dim3((unsigned)gw), dim3(kBlock), 0, st, a);
   return hipGetLastError();
 }
 
@@ -705,19 +780,19 @@ hipError_t launch_resample(const SmcWork& w, int model, int32_t k_max, int64_t N
                            int64_t* offsets_out, double* theta_out, int* flag, hipStream_t st) {
   ResampleArgs a;
   a.r = RebuildArgs{N, M, n_params(model), k_max, offsets, theta, w.src_row, w.src_len, w.skip,
-                    w.append, w.count, nullptr, offsets_out, theta_out, m_cap, flag};
+                    w.append, w.count, w.tiles + kScanTiles, nullptr, offsets_out, theta_out, m_cap, flag};
   a.w_norm = w_norm;
   a.u = u;
   a.cum = w.cum;
+  a.units = w.tiles;
   a.ancestors = ancestors;
-  hipLaunchKernelGGL(resample_prefix_kernel, dim3(1), dim3(kBlock), 0, st, a);
+  hipLaunchKernelGGL(resample_prefix_kernel, dim3(scan_tiles(N)), dim3(kScanBlock), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(resample_ancestor_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st,
-                     a);
+  hipLaunchKernelGGL(resample_ancestor_kernel, dim3(scan_tiles(N)), dim3(kScanBlock), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_rebuild(a.r, st);
+  return launch_gather(a.r, st);
 }
 
 hipError_t launch_rj_apply(const SmcWork& w, int model, int32_t k_max, int64_t N,
@@ -729,7 +804,7 @@ hipError_t launch_rj_apply(const SmcWork& w, int model, int32_t k_max, int64_t N
                            int8_t* accepted, int* flag, hipStream_t st) {
   RjArgs a;
   a.r = RebuildArgs{N, M, n_params(model), k_max, offsets, theta, w.src_row, w.src_len, w.skip,
-                    w.append, w.count, theta_birth, offsets_out, theta_out, m_cap, flag};
+                    w.append, w.count, w.tiles + kScanTiles, theta_birth, offsets_out, theta_out, m_cap, flag};
   a.move = move;
   a.death_idx = death_idx;
   a.dlogl_birth = dlogl_birth;
@@ -739,10 +814,10 @@ hipError_t launch_rj_apply(const SmcWork& w, int model, int32_t k_max, int64_t N
   a.k_hi = k_hi;
   a.log_pd_over_pb = log_pd_over_pb;
   a.accepted = accepted;
-  hipLaunchKernelGGL(rj_decide_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(rj_decide_kernel, dim3(scan_tiles(N)), dim3(kScanBlock), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_rebuild(a.r, st);
+  return launch_gather(a.r, st);
 }
 
 }  // namespace smcx
