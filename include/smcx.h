@@ -338,7 +338,7 @@ int smcx_leapfrog(smcx_problem* prob, int64_t N, const int64_t* offsets, int64_t
 int smcx_nuts_reserve(smcx_problem* prob, int32_t max_depth);
 
 /* One No-U-Turn transition (Sec. "No-U-Turn-Sampler") for every particle,
- * all trajectories built in lockstep on the device (multinomial NUTS,
+ * all trajectories built on the device, in lockstep (multinomial NUTS,
  * generalised U-turn criterion on every balanced sub-block and on the whole
  * trajectory, divergence when the energy rises by more than 1000 or a
  * position leaves the prior box, tree depth <= max_depth, identity metric;
@@ -348,6 +348,8 @@ int smcx_nuts_reserve(smcx_problem* prob, int32_t max_depth);
  * a hipGraph and replayed when use_graph != 0 (the graph is rebuilt when any
  * pointer or size argument changes). The host synchronises once per
  * doubling to learn whether any trajectory is still growing.
+ * Frequency-domain problems run every trajectory on its own in one launch:
+ * no graph (use_graph makes no difference) and no host synchronisation.
  *   beta, eps          tempering and leapfrog step size (eps > 0)
  *   max_depth          at most the depth reserved with smcx_nuts_reserve
  *   prior_lo, prior_hi [P] box of the uniform prior, or both NULL

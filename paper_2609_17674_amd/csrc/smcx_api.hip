@@ -154,7 +154,6 @@ void free_problem(smcx_problem* p) {
   (void)hipFree(p->nuts_active);
   (void)hipFree(p->nuts_dir);
   (void)hipFree(p->nuts_count);
-  (void)hipFree(p->nuts_list);
   (void)hipFree(p->d32);
   (void)hipFree(p->d64);
   (void)hipFree(p->fd_data);
@@ -272,9 +271,6 @@ smcx::PopArgs base_args(smcx_problem* p, int64_t N, const int64_t* offsets, int6
     a.fd_T_obs = p->fd_T_obs;
     a.fd_scale = p->fd_T_obs / 64.0;
     a.n_cu = p->n_cu;
-    // three workgroups of the gradient kernel fit a compute unit at once; its
-    // grid holds at least this many (six per unit, or one per four particles)
-    a.fd_split = std::min<int64_t>(3 * (int64_t)p->n_cu, (N + 3) / 4);
     if (p->partner) {
       const smcx_problem* q = p->partner;
       a.fd_bridge = 1;
@@ -964,7 +960,7 @@ int smcx_nuts_reserve(smcx_problem* p, int32_t max_depth) {
   auto depth_bytes = [&](int D) {
     return D > 0 ? stride * smcx::kNutsSlots(D) * sizeof(double) + (D + 1) * sizeof(int) : 0;
   };
-  const size_t per_particle = nN * (sizeof(smcx::NutsState) + sizeof(double) + 2 + 2 * sizeof(int32_t));
+  const size_t per_particle = nN * (sizeof(smcx::NutsState) + sizeof(double) + 2);
   // the cap is checked before anything is released: a refused reserve keeps
   // the handle, and its smaller NUTS workspace, as they were
   const size_t grown = p->ws_bytes - depth_bytes(p->nuts_depth) + depth_bytes(max_depth) +
@@ -992,10 +988,9 @@ int smcx_nuts_reserve(smcx_problem* p, int32_t max_depth) {
     if (e == hipSuccess) e = hipMalloc(&p->nuts_logl, nN * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&p->nuts_active, nN);
     if (e == hipSuccess) e = hipMalloc(&p->nuts_dir, nN);
-    if (e == hipSuccess) e = hipMalloc(&p->nuts_list, 2 * nN * sizeof(int32_t));
     if (e != hipSuccess) {
       for (void** q : {(void**)&p->nuts_state, (void**)&p->nuts_logl, (void**)&p->nuts_active,
-                       (void**)&p->nuts_dir, (void**)&p->nuts_list}) {
+                       (void**)&p->nuts_dir}) {
         (void)hipFree(*q);
         *q = nullptr;
       }
@@ -1053,7 +1048,6 @@ int nuts_transition(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t 
   std::memset(&na, 0, sizeof(na));
   na.P = p->P;
   na.D = max_depth;
-  na.n_cu = p->n_cu;
   na.k_max = p->k_max;
   na.N = N;
   na.M = M;
@@ -1079,7 +1073,6 @@ int nuts_transition(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t 
   na.active = p->nuts_active;
   na.dir = p->nuts_dir;
   na.count = p->nuts_count;
-  na.list_next = nullptr;  // init lists nothing: the first doubling runs in natural order
   na.wmat = W;
   na.w_off = W && !w_blocks ? w_offsets : nullptr;
   na.w_size = w_size;
@@ -1113,41 +1106,25 @@ int nuts_transition(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t 
   a.eps = eps;
   a.dir = p->nuts_dir;
 
-  // For the frequency-domain model every launch of doubling j >= 1 (gradient,
-  // leaf, merge) walks the particles still extending at its start, which the
-  // previous merge listed, so its cost shrinks with the active set; the lists
-  // alternate between two buffers. The first doubling, where nearly every
-  // particle is active, runs in natural order. The time-domain models keep the
-  // natural order in the leaf and merge launches and the longest-first order
-  // in the gradient: their short launches pay more for the list's extra
-  // dependent load than they save, and their chunked gradient balances
-  // better longest-first (measured on the pulse NUTS workload).
-  const size_t nlist = (size_t)std::max<int64_t>(p->n_max, 1);
+  if (p->fd) {
+    // every particle's trajectory runs on its own, in one launch; there is
+    // nothing to capture and nothing for the host to wait for
+    na.count = nullptr;
+    e = smcx::launch_fd_trajectory(a, na, p->nuts_count, st);
+    if (e != hipSuccess) return hip_fail(e, "NUTS trajectory launch");
+    return SMCX_OK;
+  }
+
+  // The time-domain models advance in lockstep. The leaf and merge launches
+  // take the particles in natural order, the gradient longest-first, where
+  // its chunks balance better.
   auto doubling = [&](int j, hipStream_t s) -> hipError_t {
-    smcx::NutsArgs nj = na;
-    smcx::PopArgs aj = a;
-    // From the third doubling on few particles are still extending (trees
-    // end after one or two doublings for most): on the frequency-domain
-    // model the leaf, merge and gradient launches step through them on fixed
-    // grids, which removes the floor of grids sized to the population. The
-    // time-domain workloads' populations are smaller, and there the
-    // one-pass kernels (half the registers) measured faster.
-    nj.stride_grid = aj.stride_grid = p->fd && j >= 2 ? 1 : 0;
-    if (p->fd) {
-      nj.list_next = p->nuts_list + (size_t)((j + 1) & 1) * nlist;
-      if (j > 0) {
-        nj.list = p->nuts_list + (size_t)(j & 1) * nlist;
-        nj.nlist = p->nuts_count + j;
-        aj.order = nj.list;
-        aj.n_active = nj.nlist;
-      }
-    }
     for (int n = 0; n < (1 << j); ++n) {
-      hipError_t err = smcx::launch_fused(p->model, t, aj, s);
-      if (err == hipSuccess) err = smcx::launch_nuts_leaf(nj, j, n, s);
+      hipError_t err = smcx::launch_fused(p->model, t, a, s);
+      if (err == hipSuccess) err = smcx::launch_nuts_leaf(na, j, n, s);
       if (err != hipSuccess) return err;
     }
-    return smcx::launch_nuts_merge(nj, j, s);
+    return smcx::launch_nuts_merge(na, j, s);
   };
 
   uint64_t key = 0;

@@ -21,9 +21,11 @@
 // d logL / d theta = beta (4 / (T_obs S)) (T_obs / 64) Re sum_j conj(w_j) dz_j.
 // Everything is FP64: a source concentrates its signal in a few bins, where
 // an FP32 template would not hold the likelihood to 1e-6.
-#include "smcx_internal.h"
+#include "smcx_nuts.h"
 
 #include <math.h>
+
+#include <algorithm>
 
 // The library is built without floating-point contraction so that the
 // time-domain kernels round as written. These FP64 kernels are held to a
@@ -179,15 +181,22 @@ __device__ __forceinline__ Src src_load(const double* c, int qslot) {
   return s;
 }
 
-__device__ __forceinline__ Src make_src(const double* th, double T_obs) {
+// The constants from the parameters with the sines and cosines given.
+__device__ __forceinline__ Src make_src_from(const double* th, double T_obs, double sb, double cb,
+                                             double sl, double cl, double s2p, double c2p, double si,
+                                             double ci) {
   Src s;
   s.f0 = th[0];
   s.fd = th[1];
   s.A = exp10(th[2] + 21.0);
-  sincos(th[3], &s.sb, &s.cb);
-  sincos(th[4], &s.sl, &s.cl);
-  sincos(2.0 * th[5], &s.s2p, &s.c2p);
-  sincos(th[6], &s.si, &s.ci);
+  s.sb = sb;
+  s.cb = cb;
+  s.sl = sl;
+  s.cl = cl;
+  s.s2p = s2p;
+  s.c2p = c2p;
+  s.si = si;
+  s.ci = ci;
   s.cyc0 = th[7] / kTwoPi;
   s.n = {s.cb * s.cl, s.cb * s.sl, s.sb};
   s.u = {s.sb * s.cl, s.sb * s.sl, -s.cb};
@@ -221,6 +230,15 @@ __device__ __forceinline__ Src make_src(const double* th, double T_obs) {
   s.wnv[3] = n.z * v.x;
   s.wnv[4] = n.z * v.y;
   return s;
+}
+
+__device__ __forceinline__ Src make_src(const double* th, double T_obs) {
+  double sb, cb, sl, cl, s2p, c2p, si, ci;
+  sincos(th[3], &sb, &cb);
+  sincos(th[4], &sl, &cl);
+  sincos(2.0 * th[5], &s2p, &c2p);
+  sincos(th[6], &si, &ci);
+  return make_src_from(th, T_obs, sb, cb, sl, cl, s2p, c2p, si, ci);
 }
 
 // Envelope of one source at this lane's sample, both channels (no (-1)^j).
@@ -871,11 +889,10 @@ struct FdItem {
   int K;
 };
 
-// Listed work items of a launch: the entries of a compact list, the ranks of
-// the ordering pass (valid particles with K > 0, or all valid ones for
-// birth/death), else N.
+// Work items of a launch: the ranks of the ordering pass (valid particles with
+// K > 0, or all valid ones for birth/death), else N.
 __device__ __forceinline__ int64_t fd_count(const PopArgs& a) {
-  return !a.order ? a.N : (a.n_active ? (int64_t)*a.n_active : a.n_ranks);
+  return a.order ? a.n_ranks : a.N;
 }
 
 // Work item at rank < fd_count(a); false for an empty rank and for a particle
@@ -902,6 +919,64 @@ constexpr int resid_row() { return kNs * NR + 2; }
 template <int NR>
 constexpr int resid_words() { return 4 * resid_row<NR>(); }
 
+// The residual into the wave's LDS copy ([re, im of A, re, im of E][band
+// position]).
+template <int NR>
+__device__ __forceinline__ void stage_resid(const Resid<NR>& R, int lane, double* rl) {
+  constexpr int Bp = kNs * NR, rs = resid_row<NR>();
+  wave_lds_sync();
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      rl[(2 * c) * rs + lane + kNs * r] = R.re[c][r];
+      rl[(2 * c + 1) * rs + lane + kNs * r] = R.im[c][r];
+    }
+  if (lane < 4) rl[lane * rs + Bp] = 0.0;
+  wave_lds_sync();
+}
+
+// The gradient of a source from the residual in LDS: lane 8p + 7 ends with
+// parameter p's.
+template <int NR>
+__device__ __forceinline__ double fd_adjoint(const FdSide& sd, const Src& s, int lane, double wc,
+                                             const double* rl) {
+  constexpr int Bp = kNs * NR, rs = resid_row<NR>();
+  // the window bins this lane gathers, in the split layout of the inverse
+  // transform: channel lane >> 5, bins m0 and m0 + 32
+  const int wc0 = (lane >> 5) * 2, m0 = bitrev5(lane & 31);
+  // residual window of the source in the inverse transform's input order
+  const int lo = window_start(s.q, sd);  // band index of window bin 0
+  double wr[2], wi[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int bw = lo + m0 + 32 * h;  // band index this lane gathers
+    const int bi = (unsigned)bw < (unsigned)sd.B ? bw : Bp;  // the zero word outside the band
+    wr[h] = rl[wc0 * rs + bi];
+    wi[h] = rl[(wc0 + 1) * rs + bi];
+  }
+  fft_inv<true>(wr, wi, sd.tw + 6 * 128, lane);
+  // w_j = sum_m R[q + m] e^{2 pi i m j / 64} = (-1)^j times the inverse DFT
+  // of the window (indexed from q - 32); the sign goes with the factor 1/2
+  // Re(conj(w) dz) per parameter
+  const Env e = envelope(s, sd.g, sd.trig, lane);
+  double gp[8];
+  grad_terms(s, sd.g, e, wr, wi, (lane & 1) ? -0.5 : 0.5, gp);
+  return transposed_sum8(gp, lane) * (wc * sd.scale);
+}
+
+// Stores it for source row m, added to the first side's after it, with the
+// closing kick of a leapfrog step (he) after the last side.
+__device__ __forceinline__ void store_gradient(const PopArgs& a, int64_t m, int lane, double gv, double he,
+                                               bool first, bool last) {
+  if ((lane & 7) == 7) {
+    const int64_t x = m * 8 + (lane >> 3);
+    if (!first && a.grad) gv += a.grad[x];
+    if (a.grad) a.grad[x] = gv;
+    if (last && a.p_half) a.p_out[x] = fma(he, gv, a.p_half[x]);
+  }
+}
+
 // One particle on one data set, weighted by w; the first side writes the
 // outputs, a second one adds to them, and the leapfrog kick (p_half set)
 // follows the last side's gradient. rl: the wave's residual copy in LDS
@@ -909,8 +984,7 @@ constexpr int resid_words() { return 4 * resid_row<NR>(); }
 template <int MODE, int NR>
 __device__ __forceinline__ void fd_particle(const PopArgs& a, const FdSide& sd, const FdItem& it,
                                             int lane, double w, bool first, bool last,
-                                            const double* __restrict__ src, double* rl,
-                                            int k_first = 0, int k_step = 1) {
+                                            const double* __restrict__ src, double* rl) {
   const int64_t i = it.i;
   const double wc = w * sd.cnorm;  // weight * 4 / (T_obs S)
   const LaneGeom g = sd.g;
@@ -956,57 +1030,19 @@ __device__ __forceinline__ void fd_particle(const PopArgs& a, const FdSide& sd, 
 #pragma unroll
     for (int r = 0; r < NR; ++r) ss = fma(R.re[c][r], R.re[c][r], fma(R.im[c][r], R.im[c][r], ss));
   ss = wave_sum(ss, lane);
-  if (lane == 0 && k_first == 0 && a.logl) {
+  if (lane == 0 && a.logl) {
     const double v = -0.5 * wc * ss;
     a.logl[i] = first ? v : a.logl[i] + v;
   }
   if constexpr (MODE == 1) {
     const double he = a.p_half ? 0.5 * a.eps * (a.dir ? (double)a.dir[i] : 1.0) : 0.0;
-    // the window bins this lane gathers, in the split layout of the inverse
-    // transform: channel lane >> 5, bins m0 and m0 + 32
-    const int wc0 = (lane >> 5) * 2, m0 = bitrev5(lane & 31);
-    // The residual goes to the wave's LDS copy ([re, im of A, re, im of E]
-    // [band position]); the loop gathers each source's window from there,
-    // and its registers are free for the adjoint.
-    constexpr int Bp = kNs * NR, rs = resid_row<NR>();
-    wave_lds_sync();
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        rl[(2 * c) * rs + lane + kNs * r] = R.re[c][r];
-        rl[(2 * c + 1) * rs + lane + kNs * r] = R.im[c][r];
-      }
-    if (lane < 4) rl[lane * rs + Bp] = 0.0;
-    wave_lds_sync();
-    for (int k = k_first; k < it.K; k += k_step) {
+    // the loop gathers each source's window from the wave's LDS copy of the
+    // residual, whose registers are free for the adjoint
+    stage_resid<NR>(R, lane, rl);
+    for (int k = 0; k < it.K; ++k) {
       const int row = __builtin_amdgcn_readfirstlane((int)(it.m0 + k));
-      const Src s = src_load(src + (int64_t)row * kSrcWords, sd.qslot);
-      // residual window of the source in the inverse transform's input order
-      const int lo = window_start(s.q, sd);  // band index of window bin 0
-      double wr[2], wi[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int bw = lo + m0 + 32 * h;  // band index this lane gathers
-        const int bi = (unsigned)bw < (unsigned)sd.B ? bw : Bp;  // the zero word outside the band
-        wr[h] = rl[wc0 * rs + bi];
-        wi[h] = rl[(wc0 + 1) * rs + bi];
-      }
-      fft_inv<true>(wr, wi, sd.tw + 6 * 128, lane);
-      // w_j = sum_m R[q + m] e^{2 pi i m j / 64} = (-1)^j times the inverse DFT
-      // of the window (indexed from q - 32); the sign goes with the factor 1/2
-      // Re(conj(w) dz) per parameter
-      const Env e = envelope(s, g, sd.trig, lane);
-      double gp[8];
-      grad_terms(s, g, e, wr, wi, (lane & 1) ? -0.5 : 0.5, gp);
-      // lane 8p + 7 ends with parameter p's total
-      double gv = transposed_sum8(gp, lane) * (wc * sd.scale);
-      if ((lane & 7) == 7) {
-        const int64_t x = (it.m0 + k) * 8 + (lane >> 3);
-        if (!first && a.grad) gv += a.grad[x];
-        if (a.grad) a.grad[x] = gv;
-        if (last && a.p_half) a.p_out[x] = fma(he, gv, a.p_half[x]);
-      }
+      const double gv = fd_adjoint<NR>(sd, src_load(src + (int64_t)row * kSrcWords, sd.qslot), lane, wc, rl);
+      store_gradient(a, it.m0 + k, lane, gv, he, first, last);
     }
   }
 }
@@ -1017,77 +1053,501 @@ __device__ __forceinline__ void fd_particle(const PopArgs& a, const FdSide& sd, 
 // data sets.
 template <int MODE, int NR>
 __device__ __forceinline__ void fd_run(const PopArgs& a, const FdTables& tabs, const FdItem& it,
-                                       int lane, const double* __restrict__ src, double* rl,
-                                       int k_first, int k_step) {
+                                       int lane, const double* __restrict__ src, double* rl) {
   const double b = a.beta ? a.beta[it.i] : 1.0;
   if (a.fd_bridge) {
-    fd_particle<MODE, NR>(a, partner_side(a, tabs, lane), it, lane, 1.0 - b, true, false, src,
-                          rl, k_first, k_step);
-    fd_particle<MODE, NR>(a, own_side(a, tabs, lane), it, lane, b, false, true, src, rl, k_first,
-                          k_step);
+    fd_particle<MODE, NR>(a, partner_side(a, tabs, lane), it, lane, 1.0 - b, true, false, src, rl);
+    fd_particle<MODE, NR>(a, own_side(a, tabs, lane), it, lane, b, false, true, src, rl);
   } else {
-    fd_particle<MODE, NR>(a, own_side(a, tabs, lane), it, lane, b, true, true, src, rl, k_first,
-                          k_step);
+    fd_particle<MODE, NR>(a, own_side(a, tabs, lane), it, lane, b, true, true, src, rl);
   }
 }
 
-// STRIDED (the leapfrog gradient of late NUTS doublings on the 128-bin band):
-// a grid smaller than the population whose workgroups step through the
-// listed particles. Otherwise one pass, one particle per wave, as in full
-// passes, where the hardware hands the workgroups out in the K-sorted order
-// (measured faster than the loop, whose form also keeps more registers live
-// in the other variants).
-template <int MODE, int NR, bool STRIDED>
+// One particle per wave; the hardware hands the workgroups out in the K-sorted
+// order.
+template <int MODE, int NR>
 __global__ __launch_bounds__(256) void fd_kernel(PopArgs a, const double* __restrict__ src) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  const int64_t n = fd_count(a);
   FdTables tabs;
   FdItem it;
-  if constexpr (!STRIDED) {
-    const int64_t rank = (int64_t)blockIdx.x * waves + wave;
-    const bool work = rank < n && fd_active_at(a, rank, it);
-    // a workgroup without an active particle leaves at once
-    if (!__syncthreads_or(work)) return;
-    double* rl = stage_tables(tabs, a.fd_table, a.fd_bridge ? a.fd2_table : nullptr) +
-                 wave * resid_words<NR>();
-    if (work) fd_run<MODE, NR>(a, tabs, it, lane, src, rl, 0, 1);
-  } else {
-    // Few listed particles (late NUTS leaves): the waves of a workgroup
-    // share one particle. Each builds the whole residual and takes every
-    // waves-th source of the gradient pass, so the results are those of one
-    // wave per particle while the latency of a particle drops to about half
-    // and four times as many SIMDs hold work.
-    const bool split = a.order && a.fd_split > 0 && n <= a.fd_split;
-    const int64_t per = split ? 1 : waves;  // particles of one workgroup pass
-    const int64_t stride = (int64_t)gridDim.x * per;
-    const int k_first = split ? wave : 0, k_step = split ? waves : 1;
-    // this wave's first active item, found before the tables are staged (a
-    // workgroup without one leaves at once); the next is looked for after
-    // each particle
-    int64_t r0 = (int64_t)blockIdx.x * per;
-    bool have = false;
-    for (; r0 < n && !have; r0 += stride) {
-      const int64_t rank = split ? r0 : r0 + wave;
-      have = rank < n && fd_active_at(a, rank, it);
+  const int64_t rank = (int64_t)blockIdx.x * waves + wave;
+  const bool work = rank < fd_count(a) && fd_active_at(a, rank, it);
+  // a workgroup without an active particle leaves at once
+  if (!__syncthreads_or(work)) return;
+  double* rl = stage_tables(tabs, a.fd_table, a.fd_bridge ? a.fd2_table : nullptr) +
+               wave * resid_words<NR>();
+  if (work) fd_run<MODE, NR>(a, tabs, it, lane, src, rl);
+}
+
+// ---------------------------------------------------------------- NUTS trajectories
+// A whole No-U-Turn transition: a wave takes a particle from the queue and runs
+// its trajectory to the end, leaf by leaf, without a barrier. A trajectory is a
+// chain of dependent gradients; most end after one doubling while a few of
+// small K take fifty steps. In lockstep (a launch each for source rows, gradient
+// and leaf over the particles still extending) the late leaves cost 20 to 37 us
+// of launches for little work, and the host had to read after each doubling
+// whether any were left. Here the long chains, taken first (smallest K
+// first), overlap the short ones. Every value is formed by the operations of
+// the lockstep steps (smcx_nuts.h) in their order. 24000 particles, K on 1..10,
+// depth 6: 1210 us and six host reads in lockstep, 456 here, 250 to 330 of them the
+// longest trajectories' latency.
+//
+// One workgroup of traj_waves waves per compute unit: two waves per SIMD hide
+// most of each other's latency, and more would not fit the LDS. (A workgroup
+// of four waves per particle, sharing its sources, took 714 us: most leaves
+// have fewer sources than waves, and three waves wait for the leaf step.)
+//
+// A particle of at most kResK sources, one coordinate per lane, keeps its
+// frontier on chip from leaf to leaf: through global memory (the general form,
+// the steps of smcx_nuts.h) a leaf waits for one dependent round trip after
+// another, 16000 of its 28000 cycles. The ends of the trajectory and the
+// subtree's proposal, which a leaf does not read, stay in the state vectors;
+// the trajectory's proposal is written to the caller's arrays at once.
+constexpr int kResK = 8;
+constexpr int kResCk = 3;     // checkpoint levels in LDS
+constexpr int kWPitch = 9;    // words per row of W in LDS
+constexpr int kTrajRows = 16;  // source rows in LDS at a time, general form
+template <int NR>
+struct TrajLds {              // of one wave
+  double rl[resid_words<NR>()];
+  double q[64], h[64], g[64];
+  double ck[kResCk][2][64];
+  double rows[kResK * kSrcWords];
+  double w[64 * kWPitch];     // the general form's further rows
+};
+static_assert(kResK * kSrcWords + 64 * kWPitch >= kTrajRows * kSrcWords, "rows of the general form");
+static_assert(sizeof(TrajLds<2>::q) + sizeof(TrajLds<2>::h) >= 8 * kNutsMetricMax, "vector of the general form");
+template <int NR>
+constexpr int traj_waves() { return NR == 2 ? 8 : 6; }
+
+struct TrajArgs {
+  PopArgs a;
+  NutsArgs na;
+  int* queue;
+};
+
+// The kernel's arguments, read again from the kernarg segment by each phase:
+// held across phases they would spill by the hundred. The lane index goes
+// through opaque_lane for the same reason (table addresses derived from it).
+__device__ __forceinline__ TrajArgs traj_args() {
+#ifdef __HIP_DEVICE_COMPILE__  // (the host pass has no address spaces to convert between)
+  using Arg = const __attribute__((address_space(4))) TrajArgs;
+  Arg* p = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+#else
+  return TrajArgs();
+#endif
+}
+__device__ __forceinline__ int opaque_lane(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// v of lane 4 (lane / 4) + T.
+template <int T>
+__device__ __forceinline__ double quad_lane(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return join_words((unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, 0x55 * T, 0xF, 0xF, true),
+                    (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), 0x55 * T, 0xF, 0xF, true));
+}
+
+// The rows of n <= kTrajRows sources with parameters th[n][8] into LDS, four
+// lanes per source, each with one of the four angles.
+__device__ __forceinline__ void traj_rows(const double* th, int n, int lane, double* rows) {
+  static_assert(4 * kTrajRows <= 64, "lanes of the rows");
+  if (lane < 4 * n) {  // whole quads
+    const TrajArgs z = traj_args();
+    const int t = lane & 3;
+    const double* c = th + (lane >> 2) * 8;
+    double sn, cs;
+    sincos(t == 2 ? 2.0 * c[5] : c[t == 3 ? 6 : 3 + t], &sn, &cs);
+    const Src s = make_src_from(c, z.a.fd_T_obs, quad_lane<0>(sn), quad_lane<0>(cs), quad_lane<1>(sn),
+                                quad_lane<1>(cs), quad_lane<2>(sn), quad_lane<2>(cs), quad_lane<3>(sn),
+                                quad_lane<3>(cs));
+    if (t == 0) {
+      double* w = rows + (lane >> 2) * kSrcWords;
+      src_store(w, s);
+      w[kQPartner] =
+          z.a.fd_bridge ? __builtin_bit_cast(double, (int64_t)floor(s.f0 * z.a.fd2_T_obs)) : w[kQOwn];
     }
-    if (!__syncthreads_or(have)) return;
-    double* rl = stage_tables(tabs, a.fd_table, a.fd_bridge ? a.fd2_table : nullptr) +
-                 wave * resid_words<NR>();
-    while (have) {
-      // the lane index, opaque to the compiler in each pass: nothing derived
-      // from it (table addresses, lane geometry) stays live from one
-      // particle to the next, which would cost a wave per SIMD
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-      fd_run<MODE, NR>(a, tabs, it, ln, src, rl, k_first, k_step);
-      have = false;
-      for (; r0 < n && !have; r0 += stride) {
-        const int64_t rank = split ? r0 : r0 + wave;
-        have = rank < n && fd_active_at(a, rank, it);
+  }
+  wave_lds_sync();
+}
+
+// Likelihood (returned, added to logl) and gradient of the particle on one
+// data set, as fd_particle<1>: RES with the rows in LDS and the gradient into L.g,
+// else with the rows made here, kTrajRows at a time, and the gradient into
+// global memory with the closing kick.
+template <int NR, bool RES>
+__device__ __forceinline__ double traj_side(const FdTables& tabs, const FdItem& it, int lane, double w,
+                                            bool partner, bool first, bool last, double logl,
+                                            TrajLds<NR>& L) {
+  const TrajArgs z = traj_args();
+  const auto side = [&](int ln) { return partner ? partner_side(z.a, tabs, ln) : own_side(z.a, tabs, ln); };
+  constexpr int kRows = RES ? kResK : kTrajRows;
+  const double* th = z.a.theta + it.m0 * 8;
+  const double wc = w * side(lane).cnorm;
+  Resid<NR> R;
+  load_resid<NR>(side(lane), lane, R);
+  for (int c0 = 0; c0 < it.K; c0 += kRows) {
+    const int n = it.K - c0 < kRows ? it.K - c0 : kRows;
+    if (!RES) traj_rows(th + c0 * 8, n, lane, L.rows);
+    for (int k = 0; k < n; ++k) {
+      const int ln = opaque_lane(lane);
+      const FdSide sd = side(ln);
+      subtract_source<NR>(sd, src_load(L.rows + k * kSrcWords, sd.qslot), sd.g, ln, R, 1.0);
+    }
+  }
+  double ss = 0.0;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) ss = fma(R.re[c][r], R.re[c][r], fma(R.im[c][r], R.im[c][r], ss));
+  ss = wave_sum(ss, lane);
+  const double v = -0.5 * wc * ss;
+  logl = first ? v : logl + v;
+  stage_resid<NR>(R, lane, L.rl);
+  const double he = !RES && z.a.p_half ? 0.5 * z.a.eps * (double)z.a.dir[it.i] : 0.0;
+  for (int c0 = 0; c0 < it.K; c0 += kRows) {
+    const int n = it.K - c0 < kRows ? it.K - c0 : kRows;
+    if (!RES && it.K > kRows) traj_rows(th + c0 * 8, n, lane, L.rows);
+    for (int k = 0; k < n; ++k) {
+      const int ln = opaque_lane(lane);
+      const FdSide sd = side(ln);
+      const double gv = fd_adjoint<NR>(sd, src_load(L.rows + k * kSrcWords, sd.qslot), ln, wc, L.rl);
+      if constexpr (RES) {
+        double* g = L.g + k * 8 + (ln >> 3);
+        if ((ln & 7) == 7) *g = first ? gv : gv + *g;
+      } else {
+        store_gradient(z.a, it.m0 + c0 + k, ln, gv, he, first, last);
       }
     }
   }
+  wave_lds_sync();
+  return logl;
+}
+
+template <int NR, bool RES>
+__device__ __forceinline__ double traj_gradient(const FdTables& tabs, const FdItem& it, int lane,
+                                                TrajLds<NR>& L) {
+  const TrajArgs z = traj_args();
+  const double b = z.a.beta ? z.a.beta[it.i] : 1.0;
+  double logl = 0.0;
+  if (RES) traj_rows(L.q, it.K, opaque_lane(lane), L.rows);
+  for (int side = z.a.fd_bridge ? 0 : 1; side < 2; ++side)
+    logl = traj_side<NR, RES>(tabs, it, opaque_lane(lane), side ? b : 1.0 - b, !side,
+                              !side || !z.a.fd_bridge, side != 0, logl, L);
+  return logl;
+}
+
+// y[0] = (W x)_c, or (W^T x)_c, at c = lane < n, as nuts::wmul.
+template <int NR, bool TRANS>
+__device__ __forceinline__ double resident_mul(const NutsArgs& a, const nuts::View& v, const TrajLds<NR>& L,
+                                               const double* x, int n) {
+  double s = 0.0;
+  if (v.lane < n) {
+    if (a.w_blocks) {
+      const int r = v.lane & 7, b = v.lane - r;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        s = fma(TRANS ? L.w[(b + k) * kWPitch + r] : L.w[v.lane * kWPitch + k], x[b + k], s);
+    } else {
+      double y[2];
+      nuts::wmul<TRANS>(nuts::wblock(a, v), n, 0, x, v.lane, y);
+      s = y[0];
+    }
+  }
+  return s;
+}
+
+// The transition of a particle of at most kResK sources (nuts::init_step, the
+// leaves and merges, nuts::finalize_step), a coordinate per lane.
+template <int NR>
+__device__ __forceinline__ void resident_trajectory(const FdTables& tabs, const FdItem& it, int lane,
+                                                    TrajLds<NR>& L) {
+#pragma clang fp contract(off)
+  const int n = it.K * 8;
+  const bool in = lane < n;
+  const int64_t x = it.m0 * 8 + lane, i = it.i;
+  nuts::View v;
+  v.lane = lane;
+  v.i = i;
+  v.x0 = it.m0 * 8;
+  v.x1 = v.x0 + n;
+  v.K = it.K;
+  v.ok = true;
+  double q = 0.0, p = 0.0, g = 0.0, wg, lo = -INFINITY, hi = INFINITY;
+  double H0, lw_tree, lw_sub = -INFINITY, logl_prop, logl_sub, e;
+  int d;
+  bool move = true, bad_w = false, box;
+  {
+    const NutsArgs a = traj_args().na;
+    if (in) {
+      q = a.q[x];
+      p = a.momentum[x];
+      g = a.grad[x];
+    }
+    logl_prop = a.logl[i];
+    d = a.dirs[i * a.D];
+    box = a.prior_lo != nullptr;
+    if (box) {
+      lo = a.prior_lo[lane & 7];
+      hi = a.prior_hi[lane & 7];
+    }
+    if (a.w_blocks) {
+      const double* W = nuts::wblock(a, v);
+#pragma unroll
+      for (int u = 0; u < kResK; ++u) {
+        const int c = lane + 64 * u;
+        if (u < it.K) L.w[(c >> 3) * kWPitch + (c & 7)] = W[c];
+      }
+    } else if (a.wmat) {
+      const int64_t w0 = a.w_off[i], w1 = a.w_off[i + 1];
+      bad_w = w1 - w0 != (int64_t)n * n || w0 < 0 || w1 > a.w_size;
+      if (bad_w && lane == 0) atomicOr(a.flag, kFlagOffsets);
+    }
+    if (bad_w || (a.mask && !a.mask[i])) {
+      if (bad_w && lane == 0 && a.status_out) a.status_out[i] = -1;
+      move = false;
+    }
+  }
+  logl_sub = logl_prop;
+  L.g[lane] = g;
+  wave_lds_sync();
+  {
+    const double pp = wave_sum(p * p, lane);
+    const bool out = __any(in && box && !(q >= lo && q <= hi));
+    H0 = -logl_prop + 0.5 * pp;
+    lw_tree = -H0;
+    if (move && !(!out && (H0 == H0) && fabs(H0) < INFINITY)) {
+      const NutsArgs a = traj_args().na;
+      if (lane == 0 && a.status_out) a.status_out[i] = 2;
+      move = false;
+    }
+  }
+  if (!move) return;
+
+  const auto times_w = [&]() {  // W g of the gradient in L.g (g itself without a metric)
+    const NutsArgs a = traj_args().na;
+    return a.wmat ? resident_mul<NR, false>(a, v, L, L.g, n) : g;
+  };
+  // h = p + (e/2) W g, q += e W^T h
+  const auto drift = [&]() {
+    const NutsArgs a = traj_args().na;
+    const double h = fma(0.5 * e, wg, p);
+    L.h[lane] = h;
+    wave_lds_sync();
+    q = fma(e, a.wmat ? resident_mul<NR, true>(a, v, L, L.h, n) : h, q);
+    L.q[lane] = q;
+    wave_lds_sync();
+  };
+  e = traj_args().na.eps * (double)d;
+  wg = times_w();
+  drift();
+
+  int steps = 0, status = 4, depth = 0;
+  while (status == 4) {  // doubling at depth j
+    const int j = depth;
+    double rs = 0.0, ut, u64;
+    int dn;
+    bool take = false;
+    {
+      const NutsArgs a = traj_args().na;
+      ut = a.u_tree[i * a.D + j];
+      dn = j + 1 < a.D ? a.dirs[i * a.D + j + 1] : 1;
+    }
+    for (int m0 = 0; m0 < (1 << j) && status == 4; ++m0) {  // leaf m0
+      const bool end = m0 == (1 << j) - 1;
+      if ((m0 & 63) == 0) {  // the next 64 leaves' uniforms, one per lane
+        const NutsArgs a = traj_args().na;
+        u64 = m0 + lane < (1 << j) ? a.u_leaf[i * ((1ll << a.D) - 1) + ((1ll << j) - 1) + m0 + lane] : 0.0;
+      }
+      const double lf = traj_gradient<NR, true>(tabs, it, lane, L);
+      g = in ? L.g[lane] : 0.0;
+      wg = times_w();
+      p = in ? fma(0.5 * e, wg, L.h[lane]) : 0.0;
+      const double pp = wave_sum(p * p, lane);
+      const bool out = __any(in && box && !(q >= lo && q <= hi));
+      const double H = out ? INFINITY : -lf + 0.5 * pp;
+      ++steps;
+      if (!(H - H0 <= 1000.0)) {  // divergence (also NaN)
+        status = 2;
+        break;
+      }
+      const double lw = -H;
+      const double lws = nuts::logaddexp(lw_sub, lw);
+      take = __shfl(u64, m0 & 63) < exp(lw - lws);
+      lw_sub = lws;
+      logl_sub = take ? lf : logl_sub;
+      const double before = rs;
+      rs = before + p;
+      const NutsArgs a = traj_args().na;
+      if (in && take && !end) {
+        nuts::slot(a, nuts::qS)[x] = q;
+        nuts::slot(a, nuts::gS)[x] = g;
+      }
+      // checkpoints of the blocks of 2^m leaves that start here, and the
+      // U-turn tests of those that end here
+      for (int m = 1; m <= j && (m0 & ((1 << m) - 1)) == 0; ++m) {
+        if (m <= kResCk) {
+          L.ck[m - 1][0][lane] = p;
+          L.ck[m - 1][1][lane] = before;
+        } else if (in) {
+          nuts::slot(a, nuts::kFirstCk + (m - 1))[x] = p;
+          nuts::slot(a, nuts::kFirstCk + a.D + (m - 1))[x] = before;
+        }
+      }
+      for (int m = 1; m <= j && ((m0 + 1) & ((1 << m) - 1)) == 0; ++m) {
+        double ckp = 0.0, ckr = 0.0;
+        if (m <= kResCk) {
+          ckp = L.ck[m - 1][0][lane];
+          ckr = L.ck[m - 1][1][lane];
+        } else if (in) {
+          ckp = nuts::slot(a, nuts::kFirstCk + (m - 1))[x];
+          ckr = nuts::slot(a, nuts::kFirstCk + a.D + (m - 1))[x];
+        }
+        const double rb = rs - ckr;
+        const double dl = wave_sum(rb * ckp, lane), dr = wave_sum(rb * p, lane);
+        if (dl <= 0.0 || dr <= 0.0) {
+          status = 1;
+          break;
+        }
+      }
+      if (status == 4 && !end) drift();
+    }
+    if (status != 4) break;
+    // merge the subtree into the trajectory
+    const NutsArgs a = traj_args().na;
+    const int e0 = d > 0 ? nuts::qR : nuts::qL, e1 = d > 0 ? nuts::qL : nuts::qR;  // this end, the other
+    // the other end: the start point in the first doubling
+    double oq = 0.0, op = 0.0, og = 0.0, rt = 0.0, sq = q, sg = g;
+    if (in) {
+      oq = j ? nuts::slot(a, e1)[x] : a.q[x];
+      op = j ? nuts::slot(a, e1 + 1)[x] : a.momentum[x];
+      og = j ? nuts::slot(a, e1 + 2)[x] : a.grad[x];
+      rt = j ? nuts::slot(a, nuts::rhoT)[x] : op;
+      if (!take) {
+        sq = nuts::slot(a, nuts::qS)[x];
+        sg = nuts::slot(a, nuts::gS)[x];
+      }
+    }
+    const bool take_tree = ut < exp(lw_sub - lw_tree);
+    lw_tree = nuts::logaddexp(lw_tree, lw_sub);
+    if (take_tree) logl_prop = logl_sub;
+    rt = rt + rs;
+    const double da = wave_sum(rt * op, lane), db = wave_sum(rt * p, lane);
+    ++depth;
+    if (da <= 0.0 || db <= 0.0) status = 1;
+    else if (depth == a.D) status = 3;
+    if (in && take_tree) {
+      a.q[x] = sq;
+      a.grad[x] = sg;
+    }
+    if (status != 4) break;
+    if (in) {
+      nuts::slot(a, nuts::rhoT)[x] = rt;
+      nuts::slot(a, e0)[x] = q;
+      nuts::slot(a, e0 + 1)[x] = p;
+      nuts::slot(a, e0 + 2)[x] = g;
+      if (j == 0) {
+        nuts::slot(a, e1)[x] = oq;
+        nuts::slot(a, e1 + 1)[x] = op;
+        nuts::slot(a, e1 + 2)[x] = og;
+      }
+    }
+    lw_sub = -INFINITY;
+    if ((dn > 0) != (d > 0)) {  // the next doubling goes on from the other end
+      q = oq;
+      p = op;
+      g = og;
+      L.g[lane] = g;
+      wave_lds_sync();
+      wg = times_w();
+    }
+    d = dn;
+    e = a.eps * (double)dn;
+    drift();
+  }
+  const NutsArgs a = traj_args().na;
+  if (lane == 0) {
+    a.logl[i] = logl_prop;
+    if (a.depth_out) a.depth_out[i] = depth;
+    if (a.steps_out) a.steps_out[i] = steps;
+    if (a.status_out) a.status_out[i] = status;
+  }
+}
+
+// The transition of any particle, its state in global memory.
+template <int NR>
+__device__ __forceinline__ void general_trajectory(const FdTables& tabs, const FdItem& it, int lane,
+                                                   TrajLds<NR>& L) {
+  nuts::View v;
+  v.lane = lane;
+  v.i = it.i;
+  v.x0 = it.m0 * 8;
+  v.x1 = v.x0 + it.K * 8;
+  v.K = it.K;
+  v.ok = true;
+  bool on = nuts::init_step(traj_args().na, v, L.q);
+  for (int j = 0; on; ++j) {
+    for (int n = 0; n < (1 << j) && on; ++n) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // the drift, for the rows' lanes
+      const double lf = traj_gradient<NR, false>(tabs, it, lane, L);
+      const NutsArgs a = traj_args().na;
+      a.logl_front[v.i] = lf;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // the gradient, for its coordinates' lanes
+      on = nuts::leaf_step(a, v, j, n, L.q);
+      if (on && n == (1 << j) - 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // lane 0's state
+        on = nuts::merge_step(a, v, j, L.q);
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  nuts::finalize_step(traj_args().na, v);
+}
+
+template <int NR>
+__global__ __launch_bounds__(64 * traj_waves<NR>(), 1) void fd_trajectory_kernel(TrajArgs t) {
+  const int lane = threadIdx.x & 63;
+  FdTables tabs;
+  double* lds = stage_tables(tabs, t.a.fd_table, t.a.fd_bridge ? t.a.fd2_table : nullptr);
+  TrajLds<NR>& L = ((TrajLds<NR>*)lds)[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
+  for (;;) {
+    const TrajArgs z = traj_args();
+    const int cnt = (int)(z.a.order ? z.a.n_ranks : z.a.N);
+    int r = 0;
+    if (lane == 0) r = atomicAdd(z.queue, 1);
+    r = __builtin_amdgcn_readfirstlane(r);
+    if (r >= cnt) return;
+    FdItem it;
+    // the order's last rank first: smallest K
+    if (!fd_item_at(z.a, cnt - 1 - r, it) || it.K == 0) continue;
+    it.i = __builtin_amdgcn_readfirstlane((int)it.i);  // particles and rows are below 2^31
+    it.m0 = __builtin_amdgcn_readfirstlane((int)it.m0);
+    it.K = __builtin_amdgcn_readfirstlane(it.K);
+    if (it.K <= kResK)
+      resident_trajectory<NR>(tabs, it, lane, L);
+    else
+      general_trajectory<NR>(tabs, it, lane, L);
+  }
+}
+
+// The outputs of the particles without a trajectory (no components, or
+// invalid: status -1) and of those that do not move, and the queue's start.
+__global__ __launch_bounds__(256) void fd_settle_kernel(NutsArgs a, int* queue) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) *queue = 0;
+  if (i >= a.N) return;
+  const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
+  const bool ok = o0 >= 0 && o1 >= o0 && o1 <= a.M;
+  const bool bad_k = ok && o1 - o0 > a.k_max;
+  if (bad_k) atomicOr(a.flag, kFlagKMax);
+  if (a.depth_out) a.depth_out[i] = 0;
+  if (a.steps_out) a.steps_out[i] = 0;
+  if (a.status_out) a.status_out[i] = !ok || bad_k ? -1 : 0;
 }
 
 // Per-source Gauss-Newton metric: block k of particle i is
@@ -1246,20 +1706,9 @@ __global__ __launch_bounds__(256) void fd_src_kernel(PopArgs a, double T2) {
   }
 }
 
-// With a.stride_grid, grids of a fixed size per compute unit whose
-// workgroups step through the listed particles: a grid as large as the
-// population costs a dispatch per workgroup even when few particles are
-// listed (late NUTS doublings). Full passes keep one workgroup per group of
-// particles, which the hardware hands out in the K-sorted order.
-unsigned fd_grid(const PopArgs& a, int64_t per_block, int64_t blocks_per_cu) {
-  const int64_t need = (launch_ranks(a) + per_block - 1) / per_block;
-  const int64_t cap = blocks_per_cu * (a.n_cu > 0 ? a.n_cu : 256);
-  return (unsigned)std::max<int64_t>(1, a.stride_grid ? std::min(need, cap) : need);
-}
-
 hipError_t launch_src_pass(const PopArgs& a, hipStream_t st) {
   if (a.N == 0) return hipSuccess;
-  hipLaunchKernelGGL(fd_src_kernel, dim3(fd_grid(a, 256 / kSrcGroup, 8)), dim3(256), 0, st, a,
+  hipLaunchKernelGGL(fd_src_kernel, dim3((unsigned)((launch_ranks(a) + 256 / kSrcGroup - 1) / (256 / kSrcGroup))), dim3(256), 0, st, a,
                      a.fd_bridge ? a.fd2_T_obs : 0.0);
   return hipGetLastError();
 }
@@ -1279,16 +1728,11 @@ hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
   // LDS bytes: the tables, and for the gradient a residual copy per wave
   const size_t lds2 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<2>() : 0);
   const size_t lds4 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<4>() : 0);
-  if (MODE == 1 && a.stride_grid && nr2) {
-    // three workgroups fit a compute unit at once: two rounds of them
-    hipLaunchKernelGGL((fd_kernel<1, 2, true>), dim3(fd_grid(a, 4, 6)), block, lds2, st, a, a.fd_src);
-    return hipGetLastError();
-  }
   const dim3 grid((unsigned)((launch_ranks(a) + 3) / 4));
   if (nr2)
-    hipLaunchKernelGGL((fd_kernel<MODE, 2, false>), grid, block, lds2, st, a, a.fd_src);
+    hipLaunchKernelGGL((fd_kernel<MODE, 2>), grid, block, lds2, st, a, a.fd_src);
   else
-    hipLaunchKernelGGL((fd_kernel<MODE, 4, false>), grid, block, lds4, st, a, a.fd_src);
+    hipLaunchKernelGGL((fd_kernel<MODE, 4>), grid, block, lds4, st, a, a.fd_src);
   return hipGetLastError();
 }
 
@@ -1306,6 +1750,26 @@ hipError_t launch_fd(int mode, const PopArgs& a, hipStream_t st) {
   }
 }
 
+template <int NR>
+hipError_t launch_trajectories(const TrajArgs& t, hipStream_t st) {
+  constexpr int nw = traj_waves<NR>();
+  const int64_t n_cu = t.a.n_cu > 0 ? t.a.n_cu : 256;
+  const dim3 grid((unsigned)std::min<int64_t>(t.a.N, n_cu));
+  hipLaunchKernelGGL(fd_trajectory_kernel<NR>, grid, dim3(64 * nw),
+                     8 * fd_lds_words(t.a.fd_bridge != 0, nw, sizeof(TrajLds<NR>) / 8), st, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_fd_trajectory(const PopArgs& a, const NutsArgs& na, int* queue, hipStream_t st) {
+  if (a.fd_B < 1 || a.fd_B > 4 * kNs) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(fd_settle_kernel, dim3((unsigned)((a.N + 255) / 256)), dim3(256), 0, st, na, queue);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const bool nr2 = a.fd_B <= 2 * kNs && !(a.fd_bridge && a.fd2_B > 2 * kNs);
+  const TrajArgs t{a, na, queue};
+  return nr2 ? launch_trajectories<2>(t, st) : launch_trajectories<4>(t, st);
+}
+
 hipError_t launch_fd_metric(const PopArgs& a, const int64_t* f_offsets, int64_t f_size, double* F,
                             int blocks, hipStream_t st) {
   if (a.N == 0) return hipSuccess;
@@ -1313,7 +1777,6 @@ hipError_t launch_fd_metric(const PopArgs& a, const int64_t* f_offsets, int64_t 
   // a.active (or nullptr) selects the particles it evaluates
   PopArgs all = a;
   all.order = nullptr;
-  all.stride_grid = 0;
   hipError_t e = launch_src_pass(all, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fd_metric_kernel, dim3((unsigned)((a.N + 3) / 4)), dim3(256),

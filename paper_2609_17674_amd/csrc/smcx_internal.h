@@ -83,7 +83,6 @@ struct PopArgs {
   int64_t split;           // posterior-start bridge: samples s < split are untempered
                            // (weight 1), later ones weighted by beta; 0 (or <= s_lo) = off
   const int32_t* order;    // particles longest-K first, or nullptr: particle order
-  const int32_t* n_active; // device scalar: entries of a compact order, or nullptr: n_ranks
   int64_t n_ranks;         // ranks of the ordering pass's order (prep_ranks), -1 where empty
   int strict;              // particle order: offsets that do not span [0, M] make every
                            // particle invalid (as the ordering pass has it)
@@ -118,15 +117,9 @@ struct PopArgs {
   int64_t fd_B;            // bins in the band
   double fd_T_obs;         // observation time [s]
   double fd_scale;         // T_obs / 64
-  int64_t fd_split;        // gradient launches over at most this many listed particles
-                           // give each particle a whole workgroup (0: never); at most
-                           // the launch's workgroups
   int n_cu;                // compute units of the device (grid sizes)
   int persist;             // 1: the population kernel's grid holds what the device runs
                            // at once and each wave steps through the work items
-  int stride_grid;         // 1: launches whose kernels step through the listed particles
-                           // take a fixed grid per compute unit (few listed), 0: a
-                           // workgroup per group of particles
   int fd_src_ready;        // 1: the caller has written fd_src for this launch's particles
   // bridge between two records (eq. reuse_bridge): the partner handle's data
   int fd_bridge;           // 1: target (1 - beta) logL_partner + beta logL_own
@@ -216,7 +209,7 @@ struct NutsArgs {
   double* logl_front;      // [N]
   uint8_t* active;         // [N]
   int8_t* dir;             // [N]
-  int* count;              // [D + 1]
+  int* count;              // [D + 1] particles that reach each doubling, or nullptr
   // mass matrix (W^T W)^{-1}: per-particle n x n row-major blocks W at
   // wmat + w_off[i] (n = K P <= kNutsMetricMax), or with w_blocks one P x P
   // block per source row m at wmat + m P P (W block diagonal), or
@@ -225,17 +218,7 @@ struct NutsArgs {
   const int64_t* w_off;    // [N + 1]
   int64_t w_size;          // entries of wmat
   int w_blocks;
-  // The particles still extending at the start of the current doubling,
-  // list[0 .. *nlist) in no particular order (or nullptr: natural order),
-  // and the list the merge fills for the next doubling (or nullptr), counting
-  // in count[depth]. Particles only leave the set within a doubling.
-  const int32_t* list;
-  const int* nlist;
-  int32_t* list_next;
   int* flag;
-  int n_cu;                // compute units of the device (grid sizes)
-  int stride_grid;         // 1: leaf and merge take a fixed grid per compute unit
-                           // (few listed particles), 0: a workgroup per particle
 };
 constexpr int kNutsMetricMax = 128;  // coordinates per particle with a metric (two per lane)
 constexpr int kNutsMaxDepth = 10;
@@ -253,7 +236,7 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
 int64_t prep_slices(int64_t N);
 int64_t prep_ranks(int64_t N);
 // Ranks a launch over the work list has to cover.
-inline int64_t launch_ranks(const PopArgs& a) { return a.order && !a.n_active ? a.n_ranks : a.N; }
+inline int64_t launch_ranks(const PopArgs& a) { return a.order ? a.n_ranks : a.N; }
 
 // Gauss-Newton metric on the matrix cores (smcx_metric.hip); k_max * P <= 128.
 // blocks: write only the P x P block of each component, at F + m P P for its
@@ -303,6 +286,9 @@ hipError_t launch_fd(int mode, const PopArgs& a, hipStream_t st);
 // The source constants of the particles a launch of launch_fd works on
 // (launch_fd runs it first unless a.fd_src_ready).
 hipError_t launch_fd_src(const PopArgs& a, hipStream_t st);
+// A whole NUTS transition of the frequency-domain model, every particle's
+// trajectory on its own; queue is a device counter (any value).
+hipError_t launch_fd_trajectory(const PopArgs& a, const NutsArgs& na, int* queue, hipStream_t st);
 hipError_t launch_fd_spectrum(const PopArgs& a, int64_t K, double* out, hipStream_t st);
 hipError_t launch_fd_metric(const PopArgs& a, const int64_t* f_offsets, int64_t f_size, double* F,
                             int blocks, hipStream_t st);

@@ -717,12 +717,6 @@ struct Item {
   int K;       // components
 };
 
-// Ranks of the work list: those of the ordering pass, or the entries of a
-// compact list.
-__device__ __forceinline__ int64_t rank_count(const PopArgs& a) {
-  return a.n_active ? (int64_t)*a.n_active : a.n_ranks;
-}
-
 // Whether offsets[0] != 0 or offsets[N] != M.
 __device__ __forceinline__ bool bad_offsets(const PopArgs& a) {
   return a.offsets[0] != 0 || a.offsets[a.N] != a.M;
@@ -740,7 +734,7 @@ __device__ __forceinline__ bool bad_offsets(const PopArgs& a) {
 __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int lane, int P,
                                             bool with_k0, Item& it) {
   if (a.order) {
-    if (item >= rank_count(a) * a.nch) return false;
+    if (item >= a.n_ranks * a.nch) return false;
     const int64_t rank = item / a.nch;
     it.c = (int)(item - rank * a.nch);
     it.i = a.order[rank];
@@ -806,7 +800,7 @@ __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int 
 __device__ __forceinline__ bool combine_item(const PopArgs& a, int64_t rank, bool with_k0,
                                              Item& it) {
   if (a.order) {
-    if (rank >= rank_count(a)) return false;
+    if (rank >= a.n_ranks) return false;
     it.i = a.order[rank];
     if (it.i < 0) return false;
   } else {
@@ -1152,7 +1146,7 @@ __global__ __launch_bounds__(256, (pop_waves_per_simd<MODEL, S, GRAD>())) void p
     pop_item<MODEL, S, GRAD>(a, first, lane, wid, lds);
     return;
   }
-  const int64_t n = (a.order ? rank_count(a) : a.N) * a.nch;
+  const int64_t n = (a.order ? a.n_ranks : a.N) * a.nch;
   const int64_t stride = (int64_t)gridDim.x * wpb;
   for (int64_t item = first; item < n; item += stride) {
     pop_item<MODEL, S, GRAD>(a, item, lane, wid, lds);
