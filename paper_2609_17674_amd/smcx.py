@@ -127,26 +127,30 @@ def _check(rc: int):
         raise SmcxError(rc, last_error())
 
 
-def _stream(stream=None) -> ctypes.c_void_p:
+# The smallest calls take as long as their marshalling (6.4 us of kernel under
+# 11 us of host for 64 pulse particles), so these three stay lean: the raw stream
+# of the current device rather than a torch.cuda.Stream built from it, and
+# plain integers, which the void* argument types convert.
+def _stream(stream=None) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor, dtype, name: str, shape=None) -> torch.Tensor:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     return t
 
