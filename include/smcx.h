@@ -295,6 +295,13 @@ int reweight_extend(smcx_problem* prob, int64_t T1, int64_t T2, int64_t N, const
 int smcx_template_sum(int model, int64_t K, const double* theta, int64_t T, double t_start,
                       double dt, double* out, void* hip_stream);
 
+/* Chain rule through the per-particle outputs: out[m][.] = w[i w_stride] grad[m][.]
+ * for the rows m of particle i (w_stride = 0: one factor for all).
+ *   w [N] FP64 at a stride of w_stride entries, grad, out [M][P] FP64 (out may
+ *   be grad); rows outside [0, M) are ignored. Capture-safe, one launch. */
+int smcx_scale_rows(int64_t N, const int64_t* offsets, int64_t M, int32_t P, const double* w,
+                    int64_t w_stride, const double* grad, double* out, void* hip_stream);
+
 /* Plain reference form of logl_grad_batch, the comparison point for the
  * batched kernels: one particle per pair of launches (a forward kernel that
  * stores the FP64 residual, then an adjoint kernel), FP64 arithmetic and

@@ -869,6 +869,18 @@ int smcx_template_sum(int model, int64_t K, const double* theta, int64_t T, doub
   return SMCX_OK;
 }
 
+int smcx_scale_rows(int64_t N, const int64_t* offsets, int64_t M, int32_t P, const double* w,
+                    int64_t w_stride, const double* grad, double* out, void* hip_stream) {
+  g_last_error.clear();
+  if (N < 0 || M < 0 || P < 1) return fail(SMCX_EINVAL, "bad size");
+  if (N == 0 || M == 0) return SMCX_OK;
+  if (!offsets || !w || !grad || !out) return fail(SMCX_EINVAL, "an array is NULL");
+  hipError_t e = smcx::launch_scale_rows(N, offsets, M, P, w, w_stride, grad, out,
+                                         (hipStream_t)hip_stream);
+  if (e != hipSuccess) return hip_fail(e, "scale_rows launch");
+  return SMCX_OK;
+}
+
 int smcx_plain_logl_grad(smcx_problem* p, int64_t N, const int64_t* offsets_host, int64_t M,
                          const double* theta, const double* beta, double* logl, double* grad,
                          void* hip_stream) {

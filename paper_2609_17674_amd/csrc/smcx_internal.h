@@ -279,6 +279,8 @@ hipError_t launch_rj_apply(const SmcWork& w, int model, int32_t k_max, int64_t N
                            const double* log_u, int32_t k_lo, int32_t k_hi, double log_pd_over_pb,
                            int64_t m_cap, int64_t* offsets_out, double* theta_out,
                            int8_t* accepted, int* flag, hipStream_t st);
+hipError_t launch_scale_rows(int64_t N, const int64_t* offsets, int64_t M, int32_t P, const double* w,
+                             int64_t w_stride, const double* grad, double* out, hipStream_t st);
 hipError_t launch_forward(int model, const Tiling& t, const PopArgs& a, hipStream_t st);
 // Frequency-domain model (smcx_gblisa.hip): mode 0 logL, 1 logL + gradient
 // (leapfrog kick when p_half is set), 2 birth / death changes.

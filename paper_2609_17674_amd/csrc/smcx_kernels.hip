@@ -1542,6 +1542,18 @@ __global__ __launch_bounds__(kRwBlock) void rw_weights_kernel(RwArgs a) {
   }
 }
 
+// Rows of each particle scaled by its factor, 16 lanes per particle (latency
+// bound: the rows of most particles are read in one to four steps).
+__global__ __launch_bounds__(256) void scale_rows_kernel(int64_t N, const int64_t* offsets, int64_t M,
+                                                         int32_t P, const double* w, int64_t w_stride,
+                                                         const double* grad, double* out) {
+  const int64_t i = (int64_t)blockIdx.x * 16 + threadIdx.x / 16;
+  if (i >= N) return;
+  const int64_t x0 = max(offsets[i], (int64_t)0) * P, x1 = min(offsets[i + 1], M) * P;
+  const double f = w[i * w_stride];
+  for (int64_t x = x0 + threadIdx.x % 16; x < x1; x += 16) out[x] = grad[x] * f;
+}
+
 // ---------------------------------------------------------------- leapfrog drift
 // First half of a leapfrog step, one wave per particle over its K*P values:
 //   p_half = p + (eps_i/2) g,  q' = q + eps_i p_half;
@@ -1684,6 +1696,13 @@ int64_t prep_slices(int64_t N) { return N > 0 ? (N + kPrepSlice - 1) / kPrepSlic
 int64_t prep_ranks(int64_t N) {
   const int64_t S = prep_slices(N);
   return S * prep_slice_len(N, S);
+}
+
+hipError_t launch_scale_rows(int64_t N, const int64_t* offsets, int64_t M, int32_t P, const double* w,
+                             int64_t w_stride, const double* grad, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(scale_rows_kernel, dim3((unsigned)((N + 15) / 16)), dim3(256), 0, st, N, offsets, M,
+                     P, w, w_stride, grad, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_forward(int model, const Tiling& t, const PopArgs& a, hipStream_t st) {
