@@ -329,8 +329,9 @@ int smcx_plain_logl_grad(smcx_problem* prob, int64_t N, const int64_t* offsets_h
  *   q_in, p_in, g_in     [M][P] FP64 state at the start
  *   q_out, p_out, g_out  [M][P] FP64 state after the step (must not overlap
  *              the inputs); logl_out [N] tempered logL at q'
- * Other arguments as logl_grad_batch. Capture-safe: two kernel launches
- * (three with the ordering pass), no allocation, no host synchronisation. */
+ * Other arguments as logl_grad_batch. Capture-safe: two kernel launches (the
+ * drift shares the ordering pass's, where there is one) and the combination of
+ * long records' chunks, no allocation, no host synchronisation. */
 int smcx_leapfrog(smcx_problem* prob, int64_t N, const int64_t* offsets, int64_t M,
                   const double* beta, double eps, const int8_t* dir, const uint8_t* active,
                   const double* q_in, const double* p_in, const double* g_in, double* q_out,

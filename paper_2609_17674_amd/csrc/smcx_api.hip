@@ -931,9 +931,9 @@ int smcx_leapfrog(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
         return fail(SMCX_EINVAL, "input and output state arrays overlap");
   if (N == 0) return SMCX_OK;
   hipStream_t st = (hipStream_t)hip_stream;
-  hipError_t e = smcx::launch_drift(p->model, N, M, offsets, eps, dir, active, q_in, p_in, g_in,
-                                    q_out, p_out, g_out, st);
-  if (e != hipSuccess) return hip_fail(e, "drift launch");
+  const smcx::DriftArgs drift{p->P, p->k_max, N, M, offsets, eps, dir, active, q_in, p_in, g_in,
+                              q_out, p_out, g_out};
+  hipError_t e;
   const double k0 = k0_tempered(p);
   const Tiling t = call_tiling(p, p->tiling[kGrad], N);
   if (t.sorted) {
@@ -941,9 +941,11 @@ int smcx_leapfrog(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
     pa.k0_lo = k0_untempered(p);
     pa.logl = logl_out;
     pa.grad = g_out;
-    e = smcx::launch_prep(pa, st);
-    if (e != hipSuccess) return hip_fail(e, "prep launch");
+    e = smcx::launch_prep(pa, st, &drift);
+  } else {
+    e = smcx::launch_drift(drift, st);
   }
+  if (e != hipSuccess) return hip_fail(e, "drift launch");
   smcx::PopArgs a = base_args(p, N, offsets, M, q_out, beta, t, 0, p->T, k0);
   a.split = p->split;
   a.k0_lo = k0_untempered(p);

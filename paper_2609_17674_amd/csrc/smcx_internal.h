@@ -170,6 +170,19 @@ struct PrepArgs {
   int include_k0;      // 1: K = 0 particles stay in the work list (birth pass)
 };
 
+// First half of a leapfrog step (launch_drift, or with the ordering pass).
+struct DriftArgs {
+  int P;
+  int32_t k_max;
+  int64_t N, M;
+  const int64_t* offsets;
+  double eps;
+  const int8_t* dir;       // [N] or nullptr
+  const uint8_t* active;   // [N] or nullptr
+  const double *q_in, *p_in, *g_in;
+  double *q_out, *p_out, *g_out;
+};
+
 // Per-particle scalars of a NUTS transition.
 struct NutsState {
   double H0;         // energy at the start point
@@ -230,7 +243,8 @@ hipError_t launch_nuts_merge(const NutsArgs& a, int j, hipStream_t st);
 hipError_t launch_nuts_finalize(const NutsArgs& a, hipStream_t st);
 
 // Host launchers (defined in smcx_kernels.hip / smcx_plain.hip).
-hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
+// drift: the first half of a leapfrog step in the same launch (no birth/death).
+hipError_t launch_prep(const PrepArgs& a, hipStream_t st, const DriftArgs* drift = nullptr);
 // Number of particle slices of the ordering pass, and of ranks of its order (at
 // most N + prep_slices(N) - 1).
 int64_t prep_slices(int64_t N);
@@ -301,10 +315,7 @@ hipError_t launch_delta(int model, const Tiling& t, const PopArgs& a, hipStream_
 hipError_t launch_reweight_reduce(int64_t N, double delta_beta, const double* logl_ext,
                                   const double* logw_prev, double* logw, double* w_norm,
                                   double* scalars, double* part, size_t part_cap, hipStream_t st);
-hipError_t launch_drift(int model, int64_t N, int64_t M, const int64_t* offsets, double eps,
-                        const int8_t* dir, const uint8_t* active, const double* q_in,
-                        const double* p_in, const double* g_in, double* q_out, double* p_out,
-                        double* g_out, hipStream_t st);
+hipError_t launch_drift(const DriftArgs& a, hipStream_t st);
 hipError_t launch_template_sum(int model, int64_t K, const double* theta, int64_t T,
                                double t_start, double dt, double* out, hipStream_t st);
 hipError_t launch_plain_particle(int model, const double* d64, int64_t T, double t_start,
