@@ -210,6 +210,15 @@ struct ProfScope {
   }
 };
 
+// The ordering pass of a call, with the source constants of a frequency-domain
+// call in the same launch where it works on all particles (a mask may leave
+// few: then the constants of those alone come with the call's launches).
+hipError_t order_pass(const smcx_problem* p, const smcx::PrepArgs& pa, smcx::PopArgs& a, hipStream_t st) {
+  if (!p->fd || a.active) return smcx::launch_prep(pa, st);
+  a.fd_src_ready = 1;
+  return smcx::launch_fd_prep(pa, a, st);
+}
+
 // A batched launch under the profiling events. On the frequency-domain model
 // the pass that writes the source constants runs before the first event
 // when profiling is on, so that the events time the likelihood kernel alone.
@@ -218,7 +227,7 @@ struct ProfScope {
 template <class Launch>
 hipError_t profiled(smcx_problem* p, smcx::PopArgs a, hipStream_t st, Launch launch,
                     bool pop = false) {
-  if (p->fd && p->prof_on) {
+  if (p->fd && p->prof_on && !a.fd_src_ready) {
     hipError_t e = smcx::launch_fd_src(a, st);
     if (e != hipSuccess) return e;
     a.fd_src_ready = 1;
@@ -694,18 +703,18 @@ int logl_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
   hipStream_t st = (hipStream_t)hip_stream;
   const double k0 = k0_tempered(p);
   const Tiling t = call_tiling(p, p->tiling[kFwd], N);
+  smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, k0);
+  a.split = p->split;
+  a.k0_lo = k0_untempered(p);
+  a.logl = logl;
   hipError_t e = hipSuccess;
   if (t.sorted) {
     smcx::PrepArgs pa = prep_args(p, N, offsets, M, beta, k0, 1);
     pa.k0_lo = k0_untempered(p);
     pa.logl = logl;
-    e = smcx::launch_prep(pa, st);
+    e = order_pass(p, pa, a, st);
     if (e != hipSuccess) return hip_fail(e, "prep launch");
   }
-  smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, k0);
-  a.split = p->split;
-  a.k0_lo = k0_untempered(p);
-  a.logl = logl;
   e = profiled(p, a, st, [&](const smcx::PopArgs& b) {
     return smcx::launch_forward(p->model, t, b, st);
   }, true);
@@ -723,21 +732,21 @@ static int grad_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64_
   hipStream_t st = (hipStream_t)hip_stream;
   const double k0 = k0_tempered(p);
   const Tiling t = call_tiling(p, p->tiling[kGrad], N);
-  hipError_t e = hipSuccess;
-  if (t.sorted) {
-    smcx::PrepArgs pa = prep_args(p, N, offsets, M, beta, k0, 1);
-    pa.k0_lo = k0_untempered(p);
-    pa.logl = logl;
-    pa.grad = grad;
-    e = smcx::launch_prep(pa, st);
-    if (e != hipSuccess) return hip_fail(e, "prep launch");
-  }
   smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, k0);
   a.split = p->split;
   a.k0_lo = k0_untempered(p);
   a.logl = logl;
   a.grad = grad;
   a.active = mask;
+  hipError_t e = hipSuccess;
+  if (t.sorted) {
+    smcx::PrepArgs pa = prep_args(p, N, offsets, M, beta, k0, 1);
+    pa.k0_lo = k0_untempered(p);
+    pa.logl = logl;
+    pa.grad = grad;
+    e = order_pass(p, pa, a, st);
+    if (e != hipSuccess) return hip_fail(e, "prep launch");
+  }
   e = profiled(p, a, st, [&](const smcx::PopArgs& b) {
     return smcx::launch_fused(p->model, t, b, st);
   }, true);
@@ -772,16 +781,6 @@ static int delta_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64
   if (p->k_max + 1 > 513) return fail(SMCX_EINVAL, "k_max too large for the birth slot");
   hipStream_t st = (hipStream_t)hip_stream;
   const Tiling t = call_tiling(p, p->tiling[kDelta], N);
-  hipError_t e = hipSuccess;
-  if (t.sorted) {
-    smcx::PrepArgs pa = prep_args(p, N, offsets, M, beta, 0.0, 1);
-    pa.include_k0 = 1;
-    pa.death_idx = death_idx;
-    pa.dlogl_birth = theta_birth ? dlogl_birth : nullptr;
-    pa.dlogl_death = death_idx ? dlogl_death : nullptr;
-    e = smcx::launch_prep(pa, st);
-    if (e != hipSuccess) return hip_fail(e, "prep launch");
-  }
   smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, 0.0);
   a.split = p->split;
   a.k0_lo = k0_untempered(p);
@@ -790,6 +789,16 @@ static int delta_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64
   a.dlogl_birth = dlogl_birth;
   a.dlogl_death = dlogl_death;
   a.active = mask;
+  hipError_t e = hipSuccess;
+  if (t.sorted) {
+    smcx::PrepArgs pa = prep_args(p, N, offsets, M, beta, 0.0, 1);
+    pa.include_k0 = 1;
+    pa.death_idx = death_idx;
+    pa.dlogl_birth = theta_birth ? dlogl_birth : nullptr;
+    pa.dlogl_death = death_idx ? dlogl_death : nullptr;
+    e = order_pass(p, pa, a, st);
+    if (e != hipSuccess) return hip_fail(e, "prep launch");
+  }
   e = profiled(p, a, st, [&](const smcx::PopArgs& b) {
     return smcx::launch_delta(p->model, t, b, st);
   });

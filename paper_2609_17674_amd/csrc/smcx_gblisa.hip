@@ -22,6 +22,7 @@
 // Everything is FP64: a source concentrates its signal in a few bins, where
 // an FP32 template would not hold the likelihood to 1e-6.
 #include "smcx_nuts.h"
+#include "smcx_prep.h"
 
 #include <math.h>
 
@@ -1051,11 +1052,11 @@ __device__ __forceinline__ void fd_particle(const PopArgs& a, const FdSide& sd, 
 // is set); 2: birth / death changes. Under a bridge (fd_bridge) the target
 // is (1 - beta) logL_partner + beta logL_own, so each particle runs on both
 // data sets.
-template <int MODE, int NR>
+template <int MODE, int NR, bool BRIDGE>
 __device__ __forceinline__ void fd_run(const PopArgs& a, const FdTables& tabs, const FdItem& it,
                                        int lane, const double* __restrict__ src, double* rl) {
   const double b = a.beta ? a.beta[it.i] : 1.0;
-  if (a.fd_bridge) {
+  if constexpr (BRIDGE) {
     fd_particle<MODE, NR>(a, partner_side(a, tabs, lane), it, lane, 1.0 - b, true, false, src, rl);
     fd_particle<MODE, NR>(a, own_side(a, tabs, lane), it, lane, b, false, true, src, rl);
   } else {
@@ -1063,10 +1064,19 @@ __device__ __forceinline__ void fd_run(const PopArgs& a, const FdTables& tabs, c
   }
 }
 
+// Waves per SIMD the kernel is compiled for. The gradient's LDS (a residual copy
+// per wave) holds four; the likelihood alone gains from more (128 bins, 40000
+// particles, K on 0..10: 168 us at four, 159 at five, 154 at six), and more
+// waves still would leave few particles' latency exposed (eight: 41 us for 1000
+// particles, K on 0..16, against 35 at six and 33 at four).
+template <int MODE, int NR, bool BRIDGE>
+constexpr int fd_occupancy() { return MODE == 0 && NR == 2 && !BRIDGE ? 6 : 4; }
+
 // One particle per wave; the hardware hands the workgroups out in the K-sorted
-// order.
-template <int MODE, int NR>
-__global__ __launch_bounds__(256) void fd_kernel(PopArgs a, const double* __restrict__ src) {
+// order. (BRIDGE apart: the two sides' constants together spill.)
+template <int MODE, int NR, bool BRIDGE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+    fd_occupancy<MODE, NR, BRIDGE>(), fd_occupancy<MODE, NR, BRIDGE>()))) void fd_kernel(PopArgs a, const double* __restrict__ src) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   FdTables tabs;
@@ -1075,9 +1085,8 @@ __global__ __launch_bounds__(256) void fd_kernel(PopArgs a, const double* __rest
   const bool work = rank < fd_count(a) && fd_active_at(a, rank, it);
   // a workgroup without an active particle leaves at once
   if (!__syncthreads_or(work)) return;
-  double* rl = stage_tables(tabs, a.fd_table, a.fd_bridge ? a.fd2_table : nullptr) +
-               wave * resid_words<NR>();
-  if (work) fd_run<MODE, NR>(a, tabs, it, lane, src, rl);
+  double* rl = stage_tables(tabs, a.fd_table, BRIDGE ? a.fd2_table : nullptr) + wave * resid_words<NR>();
+  if (work) fd_run<MODE, NR, BRIDGE>(a, tabs, it, lane, src, rl);
 }
 
 // ---------------------------------------------------------------- NUTS trajectories
@@ -1654,6 +1663,53 @@ __global__ __launch_bounds__(64) void fd_spectrum_kernel(PopArgs a, int64_t K, d
     }
 }
 
+// The source rows of all of theta, one lane per row, by workgroup `block`: a
+// launch without a mask works on (nearly) all of them, and a lane per row
+// keeps every lane busy where a group of lanes per particle (below) leaves two
+// thirds idle at K = 5.5. Rows go out through LDS in two halves, so that a store
+// covers consecutive words. The rows share the ordering pass's launch, which
+// reads nothing of them. Bound by the 368 bytes written per row: 40000
+// particles, K on 1..10, 81 MB: 29 + 6 us -> 25, of which 16 at the rate of a copy.
+__device__ __forceinline__ void fd_src_rows(int64_t block, const double* theta, int64_t M, double T1,
+                                            double T2, double* out) {
+  constexpr int kHalf = kSrcWords / 2;  // odd: rows start in different banks
+  __shared__ double stage[4][64 * kHalf];
+  const int lane = threadIdx.x & 63;
+  double* st = stage[threadIdx.x >> 6];
+  const int64_t m0 = block * 256 + (threadIdx.x & ~63);
+  const int rows = (int)min(M - m0, (int64_t)64);
+  if (rows <= 0) return;
+  double w[kSrcWords];
+  if (lane < rows) {
+    const Src s = make_src(theta + (m0 + lane) * 8, T1);
+    src_store(w, s);
+    w[kQPartner] = T2 > 0.0 ? __builtin_bit_cast(double, (int64_t)floor(s.f0 * T2)) : w[kQOwn];
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (lane < rows) {
+#pragma unroll
+      for (int x = 0; x < kHalf; ++x) st[lane * kHalf + x] = w[h * kHalf + x];
+    }
+    wave_lds_sync();
+    for (int x = lane; x < rows * kHalf; x += 64) {
+      const int r = x / kHalf, c = x - r * kHalf;
+      out[(m0 + r) * kSrcWords + h * kHalf + c] = st[x];
+    }
+    wave_lds_sync();
+  }
+}
+
+template <bool DEATH>
+__global__ __launch_bounds__(kPrepBlock) void fd_prep_kernel(PrepArgs p, int64_t S, const double* theta,
+                                                             double T1, double T2, double* out) {
+  static_assert(kPrepBlock == 256, "source rows per workgroup");
+  if (blockIdx.x < S)
+    prep_block<DEATH>(p, S);
+  else
+    fd_src_rows(blockIdx.x - S, theta, p.M, T1, T2, out);
+}
+
 // The source rows of the particles the following launch works on (the same
 // work items and activity mask): constants with the carrier bins of both
 // records (T2 = 0: no partner, word 33 repeats word 32). A group of
@@ -1708,7 +1764,8 @@ __global__ __launch_bounds__(256) void fd_src_kernel(PopArgs a, double T2) {
 
 hipError_t launch_src_pass(const PopArgs& a, hipStream_t st) {
   if (a.N == 0) return hipSuccess;
-  hipLaunchKernelGGL(fd_src_kernel, dim3((unsigned)((launch_ranks(a) + 256 / kSrcGroup - 1) / (256 / kSrcGroup))), dim3(256), 0, st, a,
+  constexpr int per = 256 / kSrcGroup;
+  hipLaunchKernelGGL(fd_src_kernel, dim3((unsigned)((launch_ranks(a) + per - 1) / per)), dim3(256), 0, st, a,
                      a.fd_bridge ? a.fd2_T_obs : 0.0);
   return hipGetLastError();
 }
@@ -1729,16 +1786,33 @@ hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
   const size_t lds2 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<2>() : 0);
   const size_t lds4 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<4>() : 0);
   const dim3 grid((unsigned)((launch_ranks(a) + 3) / 4));
-  if (nr2)
-    hipLaunchKernelGGL((fd_kernel<MODE, 2>), grid, block, lds2, st, a, a.fd_src);
+  if (nr2 && br)
+    hipLaunchKernelGGL((fd_kernel<MODE, 2, true>), grid, block, lds2, st, a, a.fd_src);
+  else if (nr2)
+    hipLaunchKernelGGL((fd_kernel<MODE, 2, false>), grid, block, lds2, st, a, a.fd_src);
+  else if (br)
+    hipLaunchKernelGGL((fd_kernel<MODE, 4, true>), grid, block, lds4, st, a, a.fd_src);
   else
-    hipLaunchKernelGGL((fd_kernel<MODE, 4>), grid, block, lds4, st, a, a.fd_src);
+    hipLaunchKernelGGL((fd_kernel<MODE, 4, false>), grid, block, lds4, st, a, a.fd_src);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_fd_src(const PopArgs& a, hipStream_t st) { return launch_src_pass(a, st); }
+
+hipError_t launch_fd_prep(const PrepArgs& p, const PopArgs& a, hipStream_t st) {
+  if (p.k_max + 1 > 4 * kPrepBlock) return hipErrorInvalidValue;
+  const int64_t S = prep_slices(p.N);
+  const dim3 grid((unsigned)(S + (p.M + 255) / 256)), block(kPrepBlock);
+  const size_t lds = (size_t)(p.k_max + 1) * sizeof(int);
+  const double T2 = a.fd_bridge ? a.fd2_T_obs : 0.0;
+  if (p.dlogl_death && p.death_idx)
+    hipLaunchKernelGGL(fd_prep_kernel<true>, grid, block, lds, st, p, S, a.theta, a.fd_T_obs, T2, a.fd_src);
+  else
+    hipLaunchKernelGGL(fd_prep_kernel<false>, grid, block, lds, st, p, S, a.theta, a.fd_T_obs, T2, a.fd_src);
+  return hipGetLastError();
+}
 
 hipError_t launch_fd(int mode, const PopArgs& a, hipStream_t st) {
   if (a.fd_B < 1 || a.fd_B > 4 * kNs) return hipErrorInvalidValue;

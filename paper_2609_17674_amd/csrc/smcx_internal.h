@@ -302,6 +302,8 @@ hipError_t launch_fd(int mode, const PopArgs& a, hipStream_t st);
 // The source constants of the particles a launch of launch_fd works on
 // (launch_fd runs it first unless a.fd_src_ready).
 hipError_t launch_fd_src(const PopArgs& a, hipStream_t st);
+// The ordering pass and the source constants of all rows in one launch.
+hipError_t launch_fd_prep(const PrepArgs& p, const PopArgs& a, hipStream_t st);
 // A whole NUTS transition of the frequency-domain model, every particle's
 // trajectory on its own; queue is a device counter (any value).
 hipError_t launch_fd_trajectory(const PopArgs& a, const NutsArgs& na, int* queue, hipStream_t st);
