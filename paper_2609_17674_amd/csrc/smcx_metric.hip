@@ -35,6 +35,7 @@
 // Error: FP16 rounding of J~ (2^-11 relative) bounds |dF~_ac| by about
 // 2^-10 sqrt(F~_aa F~_cc), plus FP32 accumulation over 512 steps.
 #include "smcx_internal.h"
+#include "smcx_prep.h"
 
 #include <algorithm>
 
@@ -673,6 +674,7 @@ struct FactorArgs {
   int block;        // 0: the whole block; b: its block-diagonal part in b x b blocks
   int* flag;
   const uint8_t* mask;  // [N] or nullptr: particles with mask[i] == 0 are skipped
+  const int32_t* order;  // [prep_ranks(N)] particles, largest K first (-1: none), or nullptr
 };
 
 __device__ __forceinline__ int tri(int r, int c) { return r * (r + 1) / 2 + c; }
@@ -773,22 +775,27 @@ __global__ __launch_bounds__(64) void factor_kernel(FactorArgs a) {
 // ---- blocks of up to 64 rows, in registers
 // factor_block's LDS form spends its time in serial LDS chains: 577 us for 8192
 // blocks of 3 K coordinates, K uniform on 0..20, whose bytes take 31 us. This
-// form takes 150 us, bound by the latency of a step (about 0.8 us at n = 63,
-// the LDS round trip and the chain from pivot to pivot); one wave per
-// workgroup, so that a long block holds no other's slot (178 us with four).
+// form takes 96 us (85 repeated), bound by the latency of its chains; one wave
+// per workgroup, so that a long block holds no other's slot, and the long
+// blocks first.
 // Here lane r keeps row r of the block in registers and one sweep over the
 // columns both eliminates and inverts, in place: with F + diag(ridge) =
 // U^{-1} D U^{-T} (U unit lower triangular), step j takes m_r = -A_rj / A_jj
-// in every lane r > j and adds m_r times one broadcast vector b to the whole
-// row, where b_c is A_cj (the column, held by the lanes) for c > j and U_jc
-// (lane j's finished row) for c < j; column j then becomes U_rj = m_r. At the
-// end W = D^{-1/2} U. The vector goes through LDS once per step and comes
-// back 16 entries to a register, one per lane of a row of 16, from where
-// v_fmac_f64 broadcasts each entry by itself (DPP row_newbcast): one
-// instruction per entry and step, where a read of every entry by all lanes
-// would keep the LDS busy longer than the FMAs take.
+// in every lane r > j and adds m_r times one vector b to the whole row, where
+// b_c is A_cj (the column, held by the lanes) for c > j and U_jc (lane j's
+// finished row) for c < j; column j then becomes U_rj = m_r. At the end
+// W = D^{-1/2} U.
+// Eight steps at a time: on the block's own eight columns step by step, the
+// vector from lane to scalar registers; on the others all at once, since the
+// eight columns of U that the steps leave are just the row's multiples of the
+// eight vectors as they were before (150 us with every step on every column,
+// an LDS round trip and a row written by one lane in each). Those go through LDS
+// once per eight steps and come back 16 entries to a register, one per lane
+// of a row of 16, from where v_fmac_f64 broadcasts each entry by itself (DPP
+// row_newbcast): one instruction per entry and step, where a read of every
+// entry by all lanes would keep the LDS busy longer than the FMAs take.
 // The register array is rotated by eight columns after every eight steps,
-// so that the step's column sits at a fixed place: register i of block jb
+// so that the block's columns sit at a fixed place: register i of block jb
 // holds column (jb + i) mod NR.
 #define SMCX_FMAC8(r, o, b, m, c0, c1, c2, c3, c4, c5, c6, c7)                                     \
   asm("s_nop 1\n\t" /* b may come from a register copy: two wait states before DPP */            \
@@ -822,22 +829,53 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
   double r[NR];
   const int sub = lane & 15;
   // rows in whole lines, 16 columns at a time through LDS; only the lower
-  // triangle is read
+  // triangle is read, all of it in flight together (the row registers are
+  // not live yet): group g, its t-th set of four rows, at entry kAt(g) + t
+  constexpr auto kAt = [](int g) { return g * (NR / 4) - 4 * (g * (g - 1) / 2); };
+  constexpr int kGroups = (NR + 15) / 16;
+  double in[kAt(kGroups)];
 #pragma unroll
-  for (int c0 = 0; c0 < NR; c0 += 16) {
-    const int c = c0 + sub;
-    for (int row = c0 + (lane >> 4); row < n; row += 4)
-      sh[row * kRowPad + sub] =
-          c <= row ? Fi[row * n + c] + (c == row ? a.ridge[c % a.P] : 0.0) : 0.0;
+  for (int g = 0; g < kGroups; ++g)
+#pragma unroll
+    for (int t = 0; t < (NR - 16 * g) / 4; ++t) {
+      const int row = 16 * g + 4 * t + (lane >> 4), c = 16 * g + sub;
+      in[kAt(g) + t] = row < n && c <= row ? Fi[row * n + c] : 0.0;
+    }
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    const int c0 = 16 * g, c = c0 + sub;
+    const double ridge = a.ridge[c % a.P];
+#pragma unroll
+    for (int t = 0; t < (NR - c0) / 4; ++t) {
+      const int row = c0 + 4 * t + (lane >> 4);
+      sh[row * kRowPad + sub] = in[kAt(g) + t] + (c == row && row < n ? ridge : 0.0);
+    }
     wave_lds_order();
 #pragma unroll
     for (int u = 0; u < 16; ++u)
-      if (c0 + u < NR) r[c0 + u] = lane >= c0 && lane < n ? sh[lane * kRowPad + u] : 0.0;
+      if (c0 + u < NR) r[c0 + u] = sh[min(lane, NR - 1) * kRowPad + u];
     wave_lds_order();
   }
   double pivot = 1.0;
+  bool good = true;
 #pragma unroll 1
   for (int jb = 0; jb < NR; jb += 8) {
+    // the block's rows before its steps, for the update of the other columns:
+    // entry i of row u is A_c,jb+u (the column, held by the lanes) for a column
+    // still to come, the finished row's entry for one before the block
+    if constexpr (NR > 8) {
+      if (lane >= jb + 8 && lane < NR)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sh[u * NR + lane - jb] = r[u];
+      if (lane >= jb && lane < jb + 8)
+#pragma unroll
+        for (int g = 8; g < NR; g += 8)
+          if (g >= NR - jb)
+#pragma unroll
+            for (int i = g; i < g + 8; ++i) sh[(lane - jb) * NR + i] = r[i];
+      wave_lds_order();
+    }
+    // the eight steps on the block's own columns, r[0..7]
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int j = jb + u;
@@ -845,34 +883,42 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
         const double x = r[u];
         const double d = lane_value(x, j);
         if (!(d > 0.0)) return false;
-        // b: lane j's row (its columns before j), then the column below j
-        if (lane == j) {
-          pivot = d;
+        if (lane == j) pivot = d;
+        double e[8];
 #pragma unroll
-          for (int g = 0; g < NR; g += 8)
-            if (g == 0 || g >= NR - jb)
+        for (int v = 0; v < 8; ++v)
+          if (v != u) e[v] = v > u ? lane_value(x, jb + v) : lane_value(r[v], j);
+        double t = x * (-1.0 / d);
+        asm("" : "+v"(t));  // in every lane, without a branch around the division
+        const double m = lane > j && lane < n ? t : 0.0;
 #pragma unroll
-              for (int i = g; i < g + 8; ++i) sh[i] = r[i];
-        }
-        if (lane > j && lane < NR) sh[lane - jb] = x;
-        wave_lds_order();
-        double b[(NR + 15) / 16];
-#pragma unroll
-        for (int q = 0; q < (NR + 15) / 16; ++q) b[q] = sh[16 * q + sub];
-        wave_lds_order();
-        const double m = lane > j && lane < n ? -(x * (1.0 / d)) : 0.0;
-#pragma unroll
-        for (int q = 0; q < (NR + 15) / 16; ++q) {
-          SMCX_FMAC8(r, 16 * q, b[q], m, 0, 1, 2, 3, 4, 5, 6, 7);
-          if constexpr (NR % 16 == 0) {
-            SMCX_FMAC8(r, 16 * q + 8, b[q], m, 8, 9, 10, 11, 12, 13, 14, 15);
-          } else {
-            if (16 * q + 8 < NR)
-              SMCX_FMAC8(r, (16 * q + 8 < NR ? 16 * q + 8 : 0), b[q], m, 8, 9, 10, 11, 12, 13, 14, 15);
-          }
-        }
+        for (int v = 0; v < 8; ++v)
+          if (v != u) r[v] = fma(m, e[v], r[v]);
         r[u] = lane == j ? 1.0 : m;
       }
+    }
+    // the other columns: a lane's steps are its entries of U against the rows as
+    // they were
+    if constexpr (NR > 8) {
+      // a row's entry group is read again, for the next row, right after its use
+      constexpr int kQ = (NR + 15) / 16;
+      double b[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) b[q] = sh[16 * q + sub];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double m = lane > jb + u ? r[u] : 0.0;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          if (q > 0) SMCX_FMAC8(r, 16 * q, b[q], m, 0, 1, 2, 3, 4, 5, 6, 7);
+          if (16 * q + 8 < NR)
+            SMCX_FMAC8(r, (16 * q + 8 < NR ? 16 * q + 8 : 0), b[q], m, 8, 9, 10, 11, 12, 13, 14, 15);
+          __builtin_amdgcn_sched_barrier(0);
+          if (u < 7) b[q] = sh[(u + 1) * NR + 16 * q + sub];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      wave_lds_order();
     }
     double t[8];
 #pragma unroll
@@ -882,6 +928,7 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
 #pragma unroll
     for (int u = 0; u < 8; ++u) r[NR - 8 + u] = t[u];
   }
+  if (!good) return false;
   const double s = 1.0 / sqrt(pivot);
 #pragma unroll
   for (int c0 = 0; c0 < NR; c0 += 16) {
@@ -898,12 +945,57 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
   return true;
 }
 
+// Particles largest K first, as the ordering pass of the likelihood calls (every
+// slice of kPrepSlice sorted by itself, the slices' p-th particles in turn), but
+// of every particle: the factor validates for itself. With blocks of n = 3 to 60
+// in particle order the last, long ones left the device idle for a quarter of
+// the time (113 us repeated, against 85; the mean over populations of one size is 80).
+constexpr int kFactorKeys = 65;  // K of the register form: k_max P <= 64
+
+__global__ __launch_bounds__(kPrepBlock) void factor_order_kernel(const int64_t* offsets, int64_t N,
+                                                                  int64_t S, int32_t* order) {
+  __shared__ int hist[kFactorKeys];
+  const int tid = threadIdx.x;
+  const int64_t len = prep_slice_len(N, S), base = blockIdx.x * len;
+  const int64_t end = base + len < N ? base + len : N;
+  if (tid < kFactorKeys) hist[tid] = 0;
+  __syncthreads();
+  int key[kPrepUnroll];
+#pragma unroll
+  for (int u = 0; u < kPrepUnroll; ++u) {
+    const int64_t i = base + (int64_t)u * kPrepBlock + tid, j = i < N ? i : N - 1;
+    const int64_t K = offsets[j + 1] - offsets[j];
+    key[u] = i < end ? (int)min(max(K, (int64_t)0), (int64_t)(kFactorKeys - 1)) : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < kPrepUnroll; ++u)
+    if (key[u] >= 0) atomicAdd(&hist[key[u]], 1);
+  __syncthreads();
+  if (tid < 64) {  // places of the keys 64, 63, ..: an exclusive prefix (key 0 follows them)
+    const int own = hist[kFactorKeys - 1 - tid];
+    int run = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(run, o);
+      if (tid >= o) run += y;
+    }
+    hist[kFactorKeys - 1 - tid] = run - own;
+    if (tid == 63) hist[0] = run;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPrepUnroll; ++u)
+    if (key[u] >= 0)
+      order[atomicAdd(&hist[key[u]], 1) * S + blockIdx.x] = (int32_t)(base + (int64_t)u * kPrepBlock + tid);
+  for (int64_t p = max(end - base, (int64_t)0) + tid; p < len; p += kPrepBlock) order[p * S + blockIdx.x] = -1;
+}
+
 // One wave per particle, CAP >= k_max P rows at most.
 template <int CAP>
 __global__ __launch_bounds__(64, (CAP <= 32 ? 5 : 3)) void factor_rows_kernel(FactorArgs a) {
   __shared__ double sh[CAP * kRowPad];
   const int lane = threadIdx.x;
-  const int64_t i = blockIdx.x;
+  const int64_t i = a.order ? a.order[blockIdx.x] : (int64_t)blockIdx.x;
+  if (i < 0) return;
   const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
   if (!(o0 >= 0 && o1 >= o0 && o1 <= a.M && o1 - o0 <= a.k_max)) {
     if (lane == 0) atomicOr(a.flag, kFlagOffsets);
@@ -1099,7 +1191,8 @@ size_t factor_lds_bytes(int nmax) { return (size_t)nmax * (nmax + 1) / 2 * sizeo
 hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
                                 const int64_t* offsets, const int64_t* f_offsets, int64_t f_size,
                                 const double* F, const double* ridge, int block, double* W,
-                                int* flag, hipStream_t st, const uint8_t* mask) {
+                                int* flag, int32_t* order, int n_cu, hipStream_t st,
+                                const uint8_t* mask) {
   FactorArgs a{};
   a.P = P;
   a.N = N;
@@ -1119,7 +1212,16 @@ hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
   // larger ones do not fit a row per lane, and the block mode's small blocks
   // leave most lanes of either form idle
   if (block == 0 && k_max * P <= 64) {
-    const dim3 grid((unsigned)N);
+    // more particles than the device holds at once (three waves per SIMD of
+    // the 64-row form): longest first, 5 us for a quarter of the time
+    int64_t ranks = N;
+    if (N > 12 * (int64_t)n_cu) {
+      const int64_t S = prep_slices(N);
+      ranks = prep_ranks(N);
+      hipLaunchKernelGGL(factor_order_kernel, dim3((unsigned)S), dim3(kPrepBlock), 0, st, offsets, N, S, order);
+      a.order = order;
+    }
+    const dim3 grid((unsigned)ranks);
     if (k_max * P <= 32)
       hipLaunchKernelGGL(factor_rows_kernel<32>, grid, dim3(64), 0, st, a);
     else
