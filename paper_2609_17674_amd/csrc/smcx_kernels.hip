@@ -944,8 +944,10 @@ __device__ __forceinline__ PopArgs late_args() {
 #endif
 }
 
-// One work item of the population kernel (a wave-uniform index).
-template <int MODEL, int S, bool GRAD>
+// One work item of the population kernel (a wave-uniform index). TILES: by a
+// workgroup of a wave per tile of the item's chunk, whose first wave adds the
+// others' sums in tile order and writes the outputs.
+template <int MODEL, int S, bool GRAD, bool TILES>
 __device__ __forceinline__ void pop_item(const PopArgs& a, int64_t item, int lane, int wid,
                                          unsigned char* lds) {
   using M = Model<MODEL>;
@@ -984,9 +986,13 @@ __device__ __forceinline__ void pop_item(const PopArgs& a, int64_t item, int lan
     for (int k = lane; k < K; k += 64) M::linearize(cst[k], S);
   wave_sync();
 
-  const int64_t cs = a.s_lo + (int64_t)c * a.chunk_len;
-  const int64_t ce = min(cs + a.chunk_len, a.s_hi);
-  const bool split = a.split > a.s_lo;  // posterior-start bridge target
+  int64_t cs = a.s_lo + (int64_t)c * a.chunk_len;
+  int64_t ce = min(cs + a.chunk_len, a.s_hi);
+  if constexpr (TILES) {
+    cs += (int64_t)wid * 64 * S;
+    ce = min(cs + 64 * S, ce);
+  }
+  const bool split = !TILES && a.split > a.s_lo;  // posterior-start bridge target
   const double b = a.beta ? a.beta[i] : 1.0;
   double ss = 0.0, ss_lo = 0.0;  // tempered and (with a split) untempered sums of r^2
   if constexpr (MODEL != SMCX_GBSINE) {
@@ -996,6 +1002,19 @@ __device__ __forceinline__ void pop_item(const PopArgs& a, int64_t item, int lan
       pop_tiles<MODEL, S, GRAD, true>(a, cst, acc, K, lane, cs, ce, split, b, ss, ss_lo);
     else
       pop_tiles<MODEL, S, GRAD, false>(a, cst, acc, K, lane, cs, ce, split, b, ss, ss_lo);
+  }
+  if constexpr (TILES) {
+    const int nw = blockDim.x >> 6;
+    const size_t per = lds_wave_bytes(MODEL, a.k_max, GRAD);
+    double* sums = reinterpret_cast<double*>(lds + nw * per);  // [nw][64]
+    if (wid > 0) sums[wid * 64 + lane] = ss;
+    __syncthreads();
+    if (wid > 0) return;
+    for (int v = 1; v < nw; ++v) {
+      ss += sums[v * 64 + lane];
+      if constexpr (GRAD)
+        for (int idx = lane; idx < K * P; idx += 64) acc[idx] += acc[v * (per / sizeof(double)) + idx];
+    }
   }
   const PopArgs z = late_args();
   ss = lane63_d(wave_sum_d(ss));
@@ -1053,15 +1072,33 @@ __global__ __launch_bounds__(256, (pop_waves_per_simd<MODEL, S, GRAD>())) void p
   const int wpb = blockDim.x >> 6;
   const int64_t first = (int64_t)blockIdx.x * wpb + wid;
   if constexpr (!PERSIST) {
-    pop_item<MODEL, S, GRAD>(a, first, lane, wid, lds);
+    pop_item<MODEL, S, GRAD, false>(a, first, lane, wid, lds);
     return;
   }
   const int64_t n = (a.order ? a.n_ranks : a.N) * a.nch;
   const int64_t stride = (int64_t)gridDim.x * wpb;
   for (int64_t item = first; item < n; item += stride) {
-    pop_item<MODEL, S, GRAD>(a, item, lane, wid, lds);
+    pop_item<MODEL, S, GRAD, false>(a, item, lane, wid, lds);
     wave_sync();  // the wave's LDS is reused by its next item
   }
+}
+
+// Few work items: a workgroup per item, a wave per tile of its chunk (at most
+// kPopTiles). Each wave builds the constants for itself; a wave's sums over one
+// tile are what one wave adds to its sums for that tile, so the results are
+// bitwise those of pop_kernel. (Not under a split, where the sums run from
+// sample to sample.) A wave's serial pass over its tiles is what few particles
+// wait for. Gradients: 100 pulse particles, K on 0..20, T = 4096: 42 -> 25 us;
+// 300, K on 0..10, T = 16384: 54 -> 23; 64 sinusoid particles, K on 0..20, T =
+// 8000: 57 -> 20.
+constexpr int kPopTiles = 4;
+
+template <int MODEL, int S, bool GRAD>
+__global__ __launch_bounds__(64 * kPopTiles, (pop_waves_per_simd<MODEL, S, GRAD>())) void pop_tile_kernel(
+    PopArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  pop_item<MODEL, S, GRAD, true>(a, blockIdx.x, threadIdx.x & 63,
+                                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lds);
 }
 
 // Combine chunk partials in chunk order; one wave per particle.
@@ -1499,6 +1536,21 @@ const void* pop_fn(bool persist) {
                  : (const void*)pop_kernel<MODEL, S, GRAD, false>;
 }
 
+// A population kernel, the profiling event after it, and the combination of
+// chunks.
+template <int MODEL, bool GRAD>
+hipError_t launch_pop_fn(const void* fn, int64_t blocks, int threads, size_t lds, int64_t ranks,
+                         const PopArgs& a, hipStream_t st) {
+  void* args[] = {const_cast<PopArgs*>(&a)};
+  hipError_t e = hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(threads), args, lds, st);
+  if (e == hipSuccess) e = hipGetLastError();
+  if (e == hipSuccess && a.prof_stop) e = hipEventRecord((hipEvent_t)a.prof_stop, st);
+  if (e != hipSuccess || a.nch == 1) return e;
+  const dim3 fgrid((unsigned)((ranks + 3) / 4));
+  hipLaunchKernelGGL((finalize_kernel<MODEL, GRAD>), fgrid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
 template <int MODEL, bool GRAD>
 hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   const int wpb = waves_per_block(MODEL, a.k_max, GRAD);
@@ -1507,6 +1559,25 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   if (items == 0) return a.prof_stop ? hipEventRecord((hipEvent_t)a.prof_stop, st) : hipSuccess;
   int64_t blocks = (items + wpb - 1) / wpb;
   const void* fn;
+  // tiles of the longest chunk, one wave each where the items are few: while
+  // the waves of a likelihood pass fit the device at once (32 per unit; 8000
+  // pulse particles, K on 0..5, T = 3000: 19.0 us against 19.6), and for the
+  // gradient, whose items are longer, up to twice that (8000, K on 0..20, T =
+  // 4096: 85.5 against 82.2; 16384: 149.0 against 149.4)
+  const int64_t len = std::min(a.chunk_len, a.s_hi - a.s_lo);
+  const int nt = (int)std::min<int64_t>((len + 64 * t.S - 1) / (64 * t.S), kPopTiles + 1);
+  const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, GRAD) + 64 * sizeof(double));
+  if (!a.persist && a.split <= a.s_lo && nt >= 2 && nt <= kPopTiles && tile_lds <= 65536 &&
+      items * nt <= (GRAD ? 64 : 32) * (int64_t)(a.n_cu > 0 ? a.n_cu : 256)) {
+    switch (t.S) {
+      case 8: fn = (const void*)pop_tile_kernel<MODEL, 8, GRAD>; break;
+      case 16: fn = (const void*)pop_tile_kernel<MODEL, 16, GRAD>; break;
+      case 32: fn = (const void*)pop_tile_kernel<MODEL, 32, GRAD>; break;
+      case 64: fn = (const void*)pop_tile_kernel<MODEL, 64, GRAD>; break;
+      default: return hipErrorInvalidValue;
+    }
+    return launch_pop_fn<MODEL, GRAD>(fn, items, 64 * nt, tile_lds, ranks, a, st);
+  }
   switch (t.S) {
     case 8: fn = pop_fn<MODEL, 8, GRAD>(a.persist); break;
     case 16: fn = pop_fn<MODEL, 16, GRAD>(a.persist); break;
@@ -1521,16 +1592,7 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
     if (e != hipSuccess) return e;
     blocks = std::min<int64_t>(blocks, (int64_t)std::max(per_cu, 1) * (a.n_cu > 0 ? a.n_cu : 256));
   }
-  const dim3 grid((unsigned)blocks);
-  const dim3 block(64 * wpb);
-  void* args[] = {const_cast<PopArgs*>(&a)};
-  hipError_t e = hipLaunchKernel(fn, grid, block, args, lds, st);
-  if (e == hipSuccess) e = hipGetLastError();
-  if (e == hipSuccess && a.prof_stop) e = hipEventRecord((hipEvent_t)a.prof_stop, st);
-  if (e != hipSuccess || a.nch == 1) return e;
-  const dim3 fgrid((unsigned)((ranks + 3) / 4));
-  hipLaunchKernelGGL((finalize_kernel<MODEL, GRAD>), fgrid, dim3(256), 0, st, a);
-  return hipGetLastError();
+  return launch_pop_fn<MODEL, GRAD>(fn, blocks, 64 * wpb, lds, ranks, a, st);
 }
 
 template <int MODEL>
