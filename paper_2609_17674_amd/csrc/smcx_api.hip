@@ -97,12 +97,11 @@ Tiling smcx::default_tiling(int model, int kind, int64_t T) {
     const int64_t tile = 64 * (int64_t)t.S;
     if (kind == kDelta) {
       // birth/death: short chunks on long records, where a wave's serial pass
-      // over its components and tiles is what few particles wait for (100
-      // particles at T = 8192: 66 -> 28 us, 4000 at 16000: 199 -> 121 us); at
-      // most 64 chunks, and none split up to 4096 samples, where the batches
-      // are large and the combine launch costs more (8192 particles: 66 us
-      // whole, 71 split; 100 particles would gain, 38 to 26, but the split
-      // may not depend on the batch)
+      // over its components and tiles is what few particles wait for (4000 at
+      // T = 16000: 199 -> 121 us); at most 64 chunks, and none split up to
+      // 4096 samples, whose four tiles few particles spread over waves anyhow
+      // and where the combine launch costs more (8192 particles: 66 us whole,
+      // 71 split)
       const int64_t len = std::max<int64_t>(2048, (T + 63) / 64);
       t.chunk_len = round_up(T <= 4096 ? T : len, tile);
     } else {

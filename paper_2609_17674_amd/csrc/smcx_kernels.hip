@@ -1184,7 +1184,9 @@ __device__ __forceinline__ void delta_sums(const PopArgs& a, const typename Mode
   }
 }
 
-// The tiles of one birth/death work item: the four inner products of the lane.
+// The tiles of one birth/death work item: the four inner products of the lane, a
+// tile's sums by themselves and then to the item's (so that it does not matter
+// which wave forms them).
 template <int MODEL, int S, bool LIN>
 __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MODEL>::C* cst,
                                             int K, int j_death, bool birth, int lane, int64_t cs,
@@ -1194,6 +1196,7 @@ __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MOD
   const int shared = j_death < 0 ? K : j_death;  // components the two residuals share
   for (int64_t tile = cs; tile < ce; tile += 64 * S) {
     float rf[S], rn[S];
+    double tx = 0.0, ty = 0.0;
     const float* dp = a.d32 + tile + lane;
 #pragma unroll
     for (int jj = 0; jj < S; ++jj) rf[jj] = dp[64 * jj];
@@ -1208,9 +1211,16 @@ __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MOD
       } else {
         for (int k = j_death + 1; k < K; ++k) M::template sub1<S, LIN>(cst[k], tile, lane, rn);
       }
-      delta_sums<MODEL, S, LIN>(a, cst[j_death], tile, lane, ce, split, bw, rn, xd, yd);
+      delta_sums<MODEL, S, LIN>(a, cst[j_death], tile, lane, ce, split, bw, rn, tx, ty);
+      xd += tx;
+      yd += ty;
     }
-    if (birth) delta_sums<MODEL, S, LIN>(a, cst[K], tile, lane, ce, split, bw, rf, xb, yb);
+    if (birth) {
+      tx = ty = 0.0;
+      delta_sums<MODEL, S, LIN>(a, cst[K], tile, lane, ce, split, bw, rf, tx, ty);
+      xb += tx;
+      yb += ty;
+    }
   }
 }
 
@@ -1219,16 +1229,13 @@ constexpr int delta_waves_per_simd() {  // what the registers allow without spil
   return S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 5);
 }
 
-template <int MODEL, int S>
-__global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta_kernel(PopArgs a) {
+// One birth/death work item; TILES as pop_item.
+template <int MODEL, int S, bool TILES>
+__device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int lane, int wid,
+                                           unsigned char* lds) {
   using M = Model<MODEL>;
   using C = typename M::C;
   constexpr int P = M::P;
-  extern __shared__ __align__(16) unsigned char lds[];
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wpb = blockDim.x >> 6;
-  const int64_t item = (int64_t)blockIdx.x * wpb + wid;
   Item it;
   if (!decode_item(a, item, lane, P, true, it)) return;
   // one wave per item: make the item's fields scalar
@@ -1249,8 +1256,12 @@ __global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta
   if (birth && lane == 0) cst[K] = M::make(a.theta_birth + (int64_t)i * P, a, S);
   wave_sync();
 
-  const int64_t cs = a.s_lo + (int64_t)c * a.chunk_len;
-  const int64_t ce = min(cs + a.chunk_len, a.s_hi);
+  int64_t cs = a.s_lo + (int64_t)c * a.chunk_len;
+  int64_t ce = min(cs + a.chunk_len, a.s_hi);
+  if constexpr (TILES) {
+    cs += (int64_t)wid * 64 * S;
+    ce = min(cs + 64 * S, ce);
+  }
   const bool split = a.split > a.s_lo;  // posterior-start bridge target
   const double bw = a.beta ? a.beta[i] : 1.0;
   double xb = 0.0, yb = 0.0, xd = 0.0, yd = 0.0;
@@ -1259,6 +1270,26 @@ __global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta
   // other components (or candidates) the two calls see
   delta_tiles<MODEL, S, MODEL != SMCX_GBSINE>(a, cst, K, j_death, birth, lane, cs, ce, split, bw,
                                               xb, yb, xd, yd);
+  if constexpr (TILES) {
+    const int nw = blockDim.x >> 6;
+    double* sums = reinterpret_cast<double*>(lds + nw * lds_wave_bytes(MODEL, a.k_max, false));  // [nw][4][64]
+    if (wid > 0) {
+      double* mine = sums + wid * 256 + lane;
+      mine[0] = xb;
+      mine[64] = yb;
+      mine[128] = xd;
+      mine[192] = yd;
+    }
+    __syncthreads();
+    if (wid > 0) return;
+    for (int v = 1; v < nw; ++v) {
+      const double* other = sums + v * 256 + lane;
+      xb += other[0];
+      yb += other[64];
+      xd += other[128];
+      yd += other[192];
+    }
+  }
   const PopArgs z = late_args();
   if (birth) {
     xb = lane63_d(wave_sum_d(xb));
@@ -1280,6 +1311,23 @@ __global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta
     dst[2] = xd;
     dst[3] = yd;
   }
+}
+
+template <int MODEL, int S>
+__global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta_kernel(PopArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  delta_item<MODEL, S, false>(a, (int64_t)blockIdx.x * (blockDim.x >> 6) + wid, threadIdx.x & 63, wid, lds);
+}
+
+// Few work items, as pop_tile_kernel: 100 pulse particles, K on 0..20, T = 4096:
+// 38 -> 15 us; 1500: 48 -> 22; 64 sinusoid particles, T = 8000: 33 -> 14.
+template <int MODEL, int S>
+__global__ __launch_bounds__(64 * kPopTiles, (delta_waves_per_simd<MODEL, S>())) void delta_tile_kernel(
+    PopArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  delta_item<MODEL, S, true>(a, blockIdx.x, threadIdx.x & 63,
+                             __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lds);
 }
 
 __global__ __launch_bounds__(256) void delta_finalize_kernel(PopArgs a) {
@@ -1601,12 +1649,26 @@ hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st)
   const size_t lds = pop_lds_bytes_per_wave(MODEL, a.k_max, false) * wpb;
   const int64_t ranks = launch_ranks(a), items = ranks * a.nch;
   if (items == 0) return hipSuccess;
-  const dim3 grid((unsigned)((items + wpb - 1) / wpb));
-  const dim3 block(64 * wpb);
-  switch (t.S) {
-    case 8: hipLaunchKernelGGL((delta_kernel<MODEL, 8>), grid, block, lds, st, a); break;
-    case 16: hipLaunchKernelGGL((delta_kernel<MODEL, 16>), grid, block, lds, st, a); break;
-    default: return hipErrorInvalidValue;
+  const int64_t len = std::min(a.chunk_len, a.s_hi - a.s_lo);
+  const int nt = (int)std::min<int64_t>((len + 64 * t.S - 1) / (64 * t.S), kPopTiles + 1);
+  const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, false) + 256 * sizeof(double));
+  // (48 waves per unit: 3000 pulse particles, T = 4096, 12000 waves: 49 us against
+  // 33; 1000 at T = 16000, 16000 waves: 44 against 49)
+  if (nt >= 2 && nt <= kPopTiles && tile_lds <= 65536 &&
+      items * nt <= 48 * (int64_t)(a.n_cu > 0 ? a.n_cu : 256)) {
+    const dim3 grid((unsigned)items), block(64 * nt);
+    switch (t.S) {
+      case 8: hipLaunchKernelGGL((delta_tile_kernel<MODEL, 8>), grid, block, tile_lds, st, a); break;
+      case 16: hipLaunchKernelGGL((delta_tile_kernel<MODEL, 16>), grid, block, tile_lds, st, a); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    const dim3 grid((unsigned)((items + wpb - 1) / wpb)), block(64 * wpb);
+    switch (t.S) {
+      case 8: hipLaunchKernelGGL((delta_kernel<MODEL, 8>), grid, block, lds, st, a); break;
+      case 16: hipLaunchKernelGGL((delta_kernel<MODEL, 16>), grid, block, lds, st, a); break;
+      default: return hipErrorInvalidValue;
+    }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.nch == 1) return e;
