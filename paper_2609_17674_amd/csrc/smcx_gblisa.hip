@@ -920,6 +920,17 @@ constexpr int resid_row() { return kNs * NR + 2; }
 template <int NR>
 constexpr int resid_words() { return 4 * resid_row<NR>(); }
 
+// |R|^2 over the band and both channels.
+template <int NR>
+__device__ __forceinline__ double resid_square(const Resid<NR>& R, int lane) {
+  double ss = 0.0;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) ss = fma(R.re[c][r], R.re[c][r], fma(R.im[c][r], R.im[c][r], ss));
+  return wave_sum(ss, lane);
+}
+
 // The residual into the wave's LDS copy ([re, im of A, re, im of E][band
 // position]).
 template <int NR>
@@ -978,6 +989,42 @@ __device__ __forceinline__ void store_gradient(const PopArgs& a, int64_t m, int 
   }
 }
 
+// The change of logL by the particle's birth candidate, and by the death of a
+// component, from its residual.
+template <int NR>
+__device__ __forceinline__ void fd_birth(const PopArgs& a, const FdSide& sd, const FdItem& it, int lane,
+                                         const Resid<NR>& R, double wc, bool first) {
+  const int64_t i = it.i;
+  if (a.theta_birth && a.dlogl_birth) {
+    const Src s = make_src(a.theta_birth + i * 8, sd.T_obs);
+    double rh, hh;
+    overlap<NR>(sd, s, sd.g, lane, R, &rh, &hh);
+    const double v = wc * (rh - 0.5 * hh);
+    if (lane == 0) a.dlogl_birth[i] = first ? v : a.dlogl_birth[i] + v;
+  }
+}
+
+template <int NR>
+__device__ __forceinline__ void fd_death(const PopArgs& a, const FdSide& sd, const FdItem& it, int lane,
+                                         const Resid<NR>& R, double wc, bool first,
+                                         const double* __restrict__ src) {
+  const int64_t i = it.i;
+  if (a.death_idx && a.dlogl_death) {
+    const int j = a.death_idx[i];
+    if (j >= 0 && j < it.K) {
+      const int row = __builtin_amdgcn_readfirstlane((int)(it.m0 + j));
+      const Src s = src_load(src + (int64_t)row * kSrcWords, sd.qslot);
+      double rh, hh;
+      overlap<NR>(sd, s, sd.g, lane, R, &rh, &hh);
+      const double v = -(wc * (rh + 0.5 * hh));
+      if (lane == 0) a.dlogl_death[i] = first ? v : a.dlogl_death[i] + v;
+    } else if (lane == 0 && first) {
+      a.dlogl_death[i] = j == -1 ? 0.0 : __builtin_nan("");
+      if (j != -1) atomicOr(a.flag, kFlagDeath);
+    }
+  }
+}
+
 // One particle on one data set, weighted by w; the first side writes the
 // outputs, a second one adds to them, and the leapfrog kick (p_half set)
 // follows the last side's gradient. rl: the wave's residual copy in LDS
@@ -1002,35 +1049,11 @@ __device__ __forceinline__ void fd_particle(const PopArgs& a, const FdSide& sd, 
     subtract_source<NR>(sd, src_load(src + (int64_t)row * kSrcWords, sd.qslot), gk, lane, R, 1.0);
   }
   if constexpr (MODE == 2) {
-    if (a.theta_birth && a.dlogl_birth) {
-      const Src s = make_src(a.theta_birth + i * 8, sd.T_obs);
-      double rh, hh;
-      overlap<NR>(sd, s, g, lane, R, &rh, &hh);
-      const double v = wc * (rh - 0.5 * hh);
-      if (lane == 0) a.dlogl_birth[i] = first ? v : a.dlogl_birth[i] + v;
-    }
-    if (a.death_idx && a.dlogl_death) {
-      const int j = a.death_idx[i];
-      if (j >= 0 && j < it.K) {
-        const int row = __builtin_amdgcn_readfirstlane((int)(it.m0 + j));
-        const Src s = src_load(src + (int64_t)row * kSrcWords, sd.qslot);
-        double rh, hh;
-        overlap<NR>(sd, s, g, lane, R, &rh, &hh);
-        const double v = -(wc * (rh + 0.5 * hh));
-        if (lane == 0) a.dlogl_death[i] = first ? v : a.dlogl_death[i] + v;
-      } else if (lane == 0 && first) {
-        a.dlogl_death[i] = j == -1 ? 0.0 : __builtin_nan("");
-        if (j != -1) atomicOr(a.flag, kFlagDeath);
-      }
-    }
+    fd_birth<NR>(a, sd, it, lane, R, wc, first);
+    fd_death<NR>(a, sd, it, lane, R, wc, first, src);
     return;
   }
-  double ss = 0.0;
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int r = 0; r < NR; ++r) ss = fma(R.re[c][r], R.re[c][r], fma(R.im[c][r], R.im[c][r], ss));
-  ss = wave_sum(ss, lane);
+  const double ss = resid_square<NR>(R, lane);
   if (lane == 0 && a.logl) {
     const double v = -0.5 * wc * ss;
     a.logl[i] = first ? v : a.logl[i] + v;
@@ -1087,6 +1110,104 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   if (!__syncthreads_or(work)) return;
   double* rl = stage_tables(tabs, a.fd_table, BRIDGE ? a.fd2_table : nullptr) + wave * resid_words<NR>();
   if (work) fd_run<MODE, NR, BRIDGE>(a, tabs, it, lane, src, rl);
+}
+
+// Few particles: a workgroup of four waves per particle, the sources shared out.
+// Waves take the window spectra of four sources at a time; each then subtracts
+// them, in source order, from its quarter of the band (channel, real or
+// imaginary part); the adjoint, or the two candidates' overlaps, go wave by
+// wave again. Every value is formed by the operations of fd_kernel in their
+// order. A wave's serial pass over its sources is what few particles wait for:
+// 300 particles, K on 0..10: gradient 33 -> 20 us, likelihood 23 -> 16,
+// birth/death 25 -> 18.
+template <int MODE, int NR>
+__device__ __forceinline__ void fd_split_side(const PopArgs& a, const FdSide& sd, const FdItem& it, int lane,
+                                              int wave, double w, bool first, bool last,
+                                              const double* __restrict__ src, double* rl, double* spec) {
+  constexpr int Bp = kNs * NR, rs = resid_row<NR>();
+  const double wc = w * sd.cnorm;
+  const double* row0 = src + (int64_t)__builtin_amdgcn_readfirstlane((int)it.m0) * kSrcWords;
+  double q[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+    q[r] = sd.data[((wave >> 1) * kFdBandStride + lane + kNs * r) * 2 + (wave & 1)];
+  for (int c0 = 0; c0 < it.K; c0 += 4) {
+    const int n = it.K - c0 < 4 ? it.K - c0 : 4;
+    if (c0) __syncthreads();  // the spectra have been read
+    if (wave < n) {
+      double re[2], im[2];
+      window_spectrum(src_load(row0 + (c0 + wave) * kSrcWords, sd.qslot), sd.g, sd.tw, sd.trig, sd.scale,
+                      lane, re, im);
+      double* o = spec + wave * 4 * kNs + lane;
+      o[0] = re[0];
+      o[kNs] = im[0];
+      o[2 * kNs] = re[1];
+      o[3 * kNs] = im[1];
+    }
+    __syncthreads();
+    for (int k = 0; k < n; ++k) {
+      const int lo =
+          window_start(__builtin_bit_cast(int64_t, row0[(c0 + k) * kSrcWords + sd.qslot]), sd);
+      const double* o = spec + (k * 4 + wave) * kNs;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int b = lane + kNs * r, m = b - lo;
+        const double f = ((unsigned)m < (unsigned)kNs && b < (int)sd.B) ? -1.0 : 0.0;
+        q[r] = fma(f, o[bin_lane(m & (kNs - 1))], q[r]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) rl[wave * rs + lane + kNs * r] = q[r];
+  if (lane == 0) rl[wave * rs + Bp] = 0.0;
+  __syncthreads();
+  if (MODE == 2 ? wave < 2 : wave == 3) {  // the whole residual
+    Resid<NR> R;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        R.re[c][r] = rl[2 * c * rs + lane + kNs * r];
+        R.im[c][r] = rl[(2 * c + 1) * rs + lane + kNs * r];
+      }
+    if constexpr (MODE == 2) {
+      if (wave == 0) fd_birth<NR>(a, sd, it, lane, R, wc, first);
+      else fd_death<NR>(a, sd, it, lane, R, wc, first, src);
+    } else {
+      const double ss = resid_square<NR>(R, lane);
+      if (lane == 0 && a.logl) {
+        const double v = -0.5 * wc * ss;
+        a.logl[it.i] = first ? v : a.logl[it.i] + v;
+      }
+    }
+  }
+  if constexpr (MODE == 1) {
+    const double he = a.p_half ? 0.5 * a.eps * (a.dir ? (double)a.dir[it.i] : 1.0) : 0.0;
+    for (int k = wave; k < it.K; k += 4) {
+      const double gv = fd_adjoint<NR>(sd, src_load(row0 + k * kSrcWords, sd.qslot), lane, wc, rl);
+      store_gradient(a, it.m0 + k, lane, gv, he, first, last);
+    }
+  }
+}
+
+template <int MODE, int NR, bool BRIDGE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void fd_split_kernel(
+    PopArgs a, const double* __restrict__ src) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  FdTables tabs;
+  FdItem it;
+  if (!((int64_t)blockIdx.x < fd_count(a) && fd_active_at(a, blockIdx.x, it))) return;
+  double* rl = stage_tables(tabs, a.fd_table, BRIDGE ? a.fd2_table : nullptr);
+  double* spec = rl + resid_words<NR>();
+  const double b = a.beta ? a.beta[it.i] : 1.0;
+  if constexpr (BRIDGE) {
+    fd_split_side<MODE, NR>(a, partner_side(a, tabs, lane), it, lane, wave, 1.0 - b, true, false, src, rl, spec);
+    __syncthreads();
+    fd_split_side<MODE, NR>(a, own_side(a, tabs, lane), it, lane, wave, b, false, true, src, rl, spec);
+  } else {
+    fd_split_side<MODE, NR>(a, own_side(a, tabs, lane), it, lane, wave, b, true, true, src, rl, spec);
+  }
 }
 
 // ---------------------------------------------------------------- NUTS trajectories
@@ -1209,12 +1330,7 @@ __device__ __forceinline__ double traj_side(const FdTables& tabs, const FdItem& 
       subtract_source<NR>(sd, src_load(L.rows + k * kSrcWords, sd.qslot), sd.g, ln, R, 1.0);
     }
   }
-  double ss = 0.0;
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int r = 0; r < NR; ++r) ss = fma(R.re[c][r], R.re[c][r], fma(R.im[c][r], R.im[c][r], ss));
-  ss = wave_sum(ss, lane);
+  const double ss = resid_square<NR>(R, lane);
   const double v = -0.5 * wc * ss;
   logl = first ? v : logl + v;
   stage_resid<NR>(R, lane, L.rl);
@@ -1770,6 +1886,11 @@ hipError_t launch_src_pass(const PopArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Particles up to which a launch gives each a workgroup: one wave per SIMD (1000
+// particles, K on 0..10: gradient 35 against 27 us, likelihood 24 / 21,
+// birth/death 26 / 25; 2000: 38 / 44, 25 / 31, 28 / 41).
+int64_t fd_split_max(const PopArgs& a) { return 4 * (int64_t)(a.n_cu > 0 ? a.n_cu : 256); }
+
 template <int MODE>
 hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
   if (a.N == 0) return hipSuccess;
@@ -1785,6 +1906,20 @@ hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
   // LDS bytes: the tables, and for the gradient a residual copy per wave
   const size_t lds2 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<2>() : 0);
   const size_t lds4 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<4>() : 0);
+  if (a.N <= fd_split_max(a)) {
+    const size_t s2 = 8 * fd_lds_words(br, 1, resid_words<2>() + 4 * 4 * kNs);
+    const size_t s4 = 8 * fd_lds_words(br, 1, resid_words<4>() + 4 * 4 * kNs);
+    const dim3 each((unsigned)launch_ranks(a));
+    if (nr2 && br)
+      hipLaunchKernelGGL((fd_split_kernel<MODE, 2, true>), each, block, s2, st, a, a.fd_src);
+    else if (nr2)
+      hipLaunchKernelGGL((fd_split_kernel<MODE, 2, false>), each, block, s2, st, a, a.fd_src);
+    else if (br)
+      hipLaunchKernelGGL((fd_split_kernel<MODE, 4, true>), each, block, s4, st, a, a.fd_src);
+    else
+      hipLaunchKernelGGL((fd_split_kernel<MODE, 4, false>), each, block, s4, st, a, a.fd_src);
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)((launch_ranks(a) + 3) / 4));
   if (nr2 && br)
     hipLaunchKernelGGL((fd_kernel<MODE, 2, true>), grid, block, lds2, st, a, a.fd_src);
