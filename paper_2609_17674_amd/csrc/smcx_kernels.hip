@@ -1101,8 +1101,27 @@ __global__ __launch_bounds__(64 * kPopTiles, (pop_waves_per_simd<MODEL, S, GRAD>
                                  __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lds);
 }
 
-// Combine chunk partials in chunk order; one wave per particle.
-template <int MODEL, bool GRAD>
+// Combine the chunk partials of logL in chunk order, a thread per particle in
+// particle order, so that a chunk's partials are read in whole lines (a wave
+// per particle in the work list's order: 85 us for the 65536 particles of a
+// data extension by 8192 samples, this 6).
+__global__ __launch_bounds__(256) void finalize_logl_kernel(PopArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.N || ((a.order || a.strict) && bad_offsets(a))) return;
+  const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
+  if (!(o0 >= 0 && o1 > o0 && o1 <= a.M && o1 - o0 <= a.k_max)) return;  // settled by the passes before
+  if (!a.logl || (a.active && !a.active[i])) return;
+  // with a split the chunk partials already carry the per-sample tempering
+  const double outer = a.split > a.s_lo ? 1.0 : (a.beta ? a.beta[i] : 1.0);
+  double ss = 0.0;
+#pragma unroll 8
+  for (int c = 0; c < a.nch; ++c) ss += a.part[(size_t)c * a.N + i];
+  a.logl[i] = outer * (-0.5 * ss * a.inv_sigma2);
+}
+
+// Combine chunk partials of logL and the gradient in chunk order; one wave per
+// particle.
+template <int MODEL>
 __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
   using M = Model<MODEL>;
   constexpr int P = M::P;
@@ -1122,23 +1141,21 @@ __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
     for (int c = 0; c < a.nch; ++c) ss += a.part[(size_t)c * a.N + i];
     a.logl[i] = outer * (-0.5 * ss * a.inv_sigma2);
   }
-  if constexpr (GRAD) {
-    const double bs = outer * a.inv_sigma2;
-    for (int k = lane; k < K; k += 64) {
-      double sums[P];
-      for (int p = 0; p < P; ++p) sums[p] = 0.0;
-      for (int c = 0; c < a.nch; ++c) {
-        const double* src = a.part_g + ((size_t)c * a.m_max + m0 + k) * P;
-        for (int p = 0; p < P; ++p) sums[p] += src[p];
-      }
-      double g[P];
-      M::scale(a.theta + (m0 + k) * P, sums, bs, a, g);
-      for (int p = 0; p < P; ++p) a.grad[(m0 + k) * P + p] = g[p];
-      if (a.p_half) {
-        const double he = 0.5 * a.eps * (a.dir ? (double)a.dir[i] : 1.0);
-        for (int p = 0; p < P; ++p)
-          a.p_out[(m0 + k) * P + p] = fma(he, g[p], a.p_half[(m0 + k) * P + p]);
-      }
+  const double bs = outer * a.inv_sigma2;
+  for (int k = lane; k < K; k += 64) {
+    double sums[P];
+    for (int p = 0; p < P; ++p) sums[p] = 0.0;
+    for (int c = 0; c < a.nch; ++c) {
+      const double* src = a.part_g + ((size_t)c * a.m_max + m0 + k) * P;
+      for (int p = 0; p < P; ++p) sums[p] += src[p];
+    }
+    double g[P];
+    M::scale(a.theta + (m0 + k) * P, sums, bs, a, g);
+    for (int p = 0; p < P; ++p) a.grad[(m0 + k) * P + p] = g[p];
+    if (a.p_half) {
+      const double he = 0.5 * a.eps * (a.dir ? (double)a.dir[i] : 1.0);
+      for (int p = 0; p < P; ++p)
+        a.p_out[(m0 + k) * P + p] = fma(he, g[p], a.p_half[(m0 + k) * P + p]);
     }
   }
 }
@@ -1477,10 +1494,12 @@ __global__ __launch_bounds__(kRwBlock) void rw_max_kernel(RwArgs a) {
 __global__ __launch_bounds__(kRwBlock) void rw_sum_kernel(RwArgs a) {
   __shared__ double sh[kRwBlock / 64];
   double m = -INFINITY, mp = -INFINITY;
-  for (int g = 0; g < a.G; ++g) {
+  for (int g = threadIdx.x; g < a.G; g += kRwBlock) {
     m = fmax(m, a.part[5 * g]);
     mp = fmax(mp, a.part[5 * g + 1]);
   }
+  m = rw_block<true>(m, sh);
+  mp = rw_block<true>(mp, sh);
   const int64_t base = (int64_t)blockIdx.x * kRwSlice;
   double s1 = 0.0, s2 = 0.0, sp = 0.0;
 #pragma unroll
@@ -1505,22 +1524,23 @@ __global__ __launch_bounds__(kRwBlock) void rw_sum_kernel(RwArgs a) {
 }
 
 __global__ __launch_bounds__(kRwBlock) void rw_weights_kernel(RwArgs a) {
-  __shared__ double tot[5];
-  if (threadIdx.x == 0) {
-    double m = -INFINITY, mp = -INFINITY, s1 = 0.0, s2 = 0.0, sp = 0.0;
-    for (int g = 0; g < a.G; ++g) {
-      m = fmax(m, a.part[5 * g]);
-      mp = fmax(mp, a.part[5 * g + 1]);
-      s1 += a.part[5 * g + 2];
-      s2 += a.part[5 * g + 3];
-      sp += a.part[5 * g + 4];
-    }
-    tot[0] = m;
-    tot[1] = mp;
-    tot[2] = s1;
-    tot[3] = s2;
-    tot[4] = sp;
+  __shared__ double tot[5], ch[kRwBlock][5];
+  // the ranges' partials come in by all threads; thread c < 5 combines column
+  // c in range order (one thread that also loaded them took 15 us with 64 ranges,
+  // this 5)
+  double v = threadIdx.x < 2 ? -INFINITY : 0.0;
+  for (int g0 = 0; g0 < a.G; g0 += kRwBlock) {
+    const int n = min(a.G - g0, kRwBlock);
+    if (g0) __syncthreads();
+    if ((int)threadIdx.x < n)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) ch[threadIdx.x][c] = a.part[5 * (g0 + threadIdx.x) + c];
+    __syncthreads();
+    if (threadIdx.x < 5)
+      for (int g = 0; g < n; ++g)
+        v = threadIdx.x < 2 ? fmax(v, ch[g][threadIdx.x]) : v + ch[g][threadIdx.x];
   }
+  if (threadIdx.x < 5) tot[threadIdx.x] = v;
   __syncthreads();
   const double s1 = tot[2];
   const int64_t base = (int64_t)blockIdx.x * kRwSlice;
@@ -1594,8 +1614,10 @@ hipError_t launch_pop_fn(const void* fn, int64_t blocks, int threads, size_t lds
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess && a.prof_stop) e = hipEventRecord((hipEvent_t)a.prof_stop, st);
   if (e != hipSuccess || a.nch == 1) return e;
-  const dim3 fgrid((unsigned)((ranks + 3) / 4));
-  hipLaunchKernelGGL((finalize_kernel<MODEL, GRAD>), fgrid, dim3(256), 0, st, a);
+  if constexpr (GRAD)
+    hipLaunchKernelGGL(finalize_kernel<MODEL>, dim3((unsigned)((ranks + 3) / 4)), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(finalize_logl_kernel, dim3((unsigned)((a.N + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
