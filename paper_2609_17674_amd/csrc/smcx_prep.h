@@ -12,9 +12,12 @@ namespace {
 // outside the birth pass, invalid ones) and lists the rest longest-K first.
 // One launch: each workgroup sorts a slice of at most kPrepSlice particles
 // by itself (a counting sort in LDS), and the work list takes the slices'
-// p-th particles in turn (rank p S + b for slice b of S), which hands the long
-// particles out first as one sorted list would: a slice of thousands holds
-// about the same mix of K as the next. A slice with fewer than its share
+// p-th particles in turn (rank p S + (b + p) mod S for slice b of S), which hands
+// the long particles out first as one sorted list would: a slice of thousands
+// holds about the same mix of K as the next. The turn by p keeps a slice from
+// falling to the same dies (workgroups go round the eight) every time, whose work
+// would differ as the slices' does: logL of 65536 sinusoid particles, K on 0..50,
+// 65536 samples: 8.68 ms without it, 8.60 with. A slice with fewer than its share
 // of particles to list leaves its last ranks empty (-1). (Two launches, a
 // histogram per slice and then one global order, took 5.3 + 5.0 us at N =
 // 16384.) Each thread loads all of its particles before it uses any, so the
@@ -53,6 +56,11 @@ __device__ __forceinline__ int prep_key(const PrepArgs& a, int64_t i, int64_t o0
     return -1;
   }
   return (int)K;
+}
+
+// Rank of the p-th listed particle of this workgroup's slice.
+__device__ __forceinline__ int64_t prep_rank(int p, int64_t S) {
+  return p * S + (blockIdx.x + (uint32_t)p) % (uint32_t)S;
 }
 
 // Particles per slice: S slices of (almost) equal size.
@@ -139,9 +147,9 @@ __device__ __forceinline__ void prep_block(const PrepArgs& a, int64_t S) {
 #pragma unroll
   for (int u = 0; u < kPrepUnroll; ++u)
     if (key[u] >= 0)
-      a.order[atomicAdd(&hist[key[u]], 1) * S + blockIdx.x] =
+      a.order[prep_rank(atomicAdd(&hist[key[u]], 1), S)] =
           (int32_t)(base + (int64_t)u * kPrepBlock + tid);
-  for (int64_t p = total + tid; p < len; p += kPrepBlock) a.order[p * S + blockIdx.x] = -1;
+  for (int64_t p = total + tid; p < len; p += kPrepBlock) a.order[prep_rank((int)p, S)] = -1;
 }
 
 }  // namespace
