@@ -88,8 +88,8 @@ SLOTS = {(0, "grad"): 10.0, (1, "grad"): 2.75 + 5.5, (0, "fwd"): 4.0, (1, "fwd")
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs, scaled by the same counters' readings for a device copy of
 # known size. Valid only for the kernel source they were taken on (its hash).
-PMC_TRAFFIC = {("gb_grad", "32,16384,1"): {"bytes": 2.4607e+07, "kernels_sha1": "bca9d37ca926281b"},
-               ("pulse_batch", "64,4096,1"): {"bytes": 1.3133e+07, "kernels_sha1": "bca9d37ca926281b"}}
+PMC_TRAFFIC = {("gb_grad", "32,16384,1"): {"bytes": 2.3862e+07, "kernels_sha1": "050803494bb8a5d4"},
+               ("pulse_batch", "64,4096,1"): {"bytes": 1.3463e+07, "kernels_sha1": "050803494bb8a5d4"}}
 
 
 def kernels_sha1():
@@ -487,26 +487,27 @@ def bench_metric(args, w, dev, smcx, np, torch):
     prob.device_status()
     K = np.diff(w.offsets)
     n = K * w.P
-    nb = 1 if w.k_max * w.P <= 32 else (2 if w.k_max * w.P <= 64 else 4)
     useful = float(np.sum(n.astype(np.float64) ** 2) * w.T * 2)        # sum_i n_i^2 T (FMA = 2)
-    issued = float(np.count_nonzero(K) * (w.T / 8) * nb * (nb + 1) / 2 * 2 * 32 * 32 * 8)
-    jvals = float(np.count_nonzero(K) * 32 * nb * w.T)                  # J~ entries formed
+    # one 32x32x8 product per pair of parameters and 8 samples, on groups of 32
+    # components (counted full; the packing fills about 93% of the rows)
+    pairs = w.P * (w.P + 1) // 2
+    issued = float(w.M / 32 * (w.T / 8) * pairs * 2 * 32 * 32 * 8)
+    cs = float(w.M) * w.T                                              # component-samples
     tf = issued / (ms * 1e-3) / 1e12
     value = w.N / (ms * 1e-3)
-    # the J entries are synthesised on the vector units, 8 FP32-FMA slots each
-    # (sub 1/2, fma 1, mul 1/2, exp2 2, two fma 2, mul 1/2, f16 convert 1,
-    # select 1/2), which is what bounds the kernel; the matrix cores carry the
-    # contraction
-    slots_tf = 2.0 * 8 * jvals / (ms * 1e-3) / 1e12
+    # a component's three partials are formed on the vector units, 7 FP32-FMA
+    # slots per sample (add 1/2, fma 1, mul 1/2, exp2 1, two muls 1/2 each, three
+    # products rounded to FP16 1 each); the matrix cores carry the contraction
+    slots_tf = 2.0 * 7 * cs / (ms * 1e-3) / 1e12
     log(f"[bench] metric {ms:.4f} ms/step, {value:.4e} particles/s, MFMA {tf:.1f} TFLOP/s issued")
     return dict(metric="particle Gauss-Newton metrics/sec (FP16 matrix cores, FP64 output)",
                 value=value, unit="particles/s", ms_per_step=ms,
                 config={"workload": "metric_pulse_batch", "T": w.T, "N": w.N, "M": w.M,
-                        "K": f"U{{0..{w.k_max}}}", "coordinate_blocks": nb},
+                        "K": f"U{{0..{w.k_max}}}"},
                 roofline={"bound": "alu", "achieved": round(slots_tf, 3), "peak": PEAK_FP32_TFLOPS,
                           "unit": "TFLOP/s", "frac": round(slots_tf / PEAK_FP32_TFLOPS, 4),
-                          "traffic": None, "kernel": "metric_kernel", "kernel_ms": round(ms, 5),
-                          "work": f"{jvals:.4e} J entries x 8 FP32-FMA slots x 2 flops",
+                          "traffic": None, "kernel": "metric_group_wave_kernel", "kernel_ms": round(ms, 5),
+                          "work": f"{cs:.4e} component-samples x 7 FP32-FMA slots x 2 flops",
                           "mfma_issued_tflops": round(tf, 2), "mfma_peak_fp16_tflops": 2500.0,
                           "mfma_frac": round(tf / 2500.0, 4),
                           "useful_tflops": round(useful / (ms * 1e-3) / 1e12, 2)})
