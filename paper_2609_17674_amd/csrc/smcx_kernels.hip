@@ -1104,7 +1104,7 @@ __global__ __launch_bounds__(64 * kPopTiles, (pop_waves_per_simd<MODEL, S, GRAD>
 // Combine the chunk partials of logL in chunk order, a thread per particle in
 // particle order, so that a chunk's partials are read in whole lines (a wave
 // per particle in the work list's order: 85 us for the 65536 particles of a
-// data extension by 8192 samples, this 6).
+// data extension by 131072 samples, this 6).
 __global__ __launch_bounds__(256) void finalize_logl_kernel(PopArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= a.N || ((a.order || a.strict) && bad_offsets(a))) return;
