@@ -1662,12 +1662,15 @@ __global__ __launch_bounds__(64 * traj_waves<NR>(), 1) void fd_trajectory_kernel
 
 // The outputs of the particles without a trajectory (no components, or
 // invalid: status -1) and of those that do not move, and the queue's start.
+// Offsets that do not span [0, M] make every particle invalid, as in the
+// ordering pass, which lists none then.
 __global__ __launch_bounds__(256) void fd_settle_kernel(NutsArgs a, int* queue) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i == 0) *queue = 0;
   if (i >= a.N) return;
   const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
-  const bool ok = o0 >= 0 && o1 >= o0 && o1 <= a.M;
+  const bool span = a.offsets[0] == 0 && a.offsets[a.N] == a.M;
+  const bool ok = span && o0 >= 0 && o1 >= o0 && o1 <= a.M;
   const bool bad_k = ok && o1 - o0 > a.k_max;
   if (bad_k) atomicOr(a.flag, kFlagKMax);
   if (a.depth_out) a.depth_out[i] = 0;
