@@ -133,12 +133,10 @@ Tiling with_range(Tiling t, int64_t len) {
 
 namespace {
 
-// Bytes of the work list: at most one empty rank per slice of the ordering pass.
-// (A slot per slice and K: what a handle takes stays what a workspace cap was
-// set for.)
-size_t order_bytes(int64_t n_max, int32_t k_max) {
-  const int64_t n = std::max<int64_t>(n_max, 1);
-  return ((size_t)n + 1 + (size_t)smcx::prep_slices(n) * (k_max + 1)) * sizeof(int32_t);
+// Bytes of the work list, its empty ranks (at most one per slice of the ordering
+// pass) among them; prep_ranks does not fall with N.
+size_t order_bytes(int64_t n_max) {
+  return (size_t)smcx::prep_ranks(std::max<int64_t>(n_max, 1)) * sizeof(int32_t);
 }
 
 void free_problem(smcx_problem* p) {
@@ -165,7 +163,6 @@ void free_problem(smcx_problem* p) {
   (void)hipFree(p->smc.skip);
   (void)hipFree(p->smc.append);
   (void)hipFree(p->smc.count);
-  (void)hipFree(p->smc.tiles);
   (void)hipFree(p->flag);
   (void)hipFree(p->part);
   (void)hipFree(p->part_g);
@@ -489,14 +486,13 @@ int smcx_problem_create(int model, const double* d_dev, int64_t T, double t_star
   struct { void** ptr; size_t bytes; } allocs[] = {
       {(void**)&p->d32, T_pad * sizeof(float)},
       {(void**)&p->d64, T * sizeof(double)},
-      {(void**)&p->order, order_bytes(n_max, k_max)},
+      {(void**)&p->order, order_bytes(n_max)},
       {(void**)&p->smc.cum, n1 * sizeof(int64_t)},
       {(void**)&p->smc.src_row, n1 * sizeof(int64_t)},
       {(void**)&p->smc.src_len, n1 * sizeof(int32_t)},
       {(void**)&p->smc.skip, n1 * sizeof(int32_t)},
       {(void**)&p->smc.append, n1 * sizeof(int32_t)},
       {(void**)&p->smc.count, n1 * sizeof(int64_t)},
-      {(void**)&p->smc.tiles, 2 * smcx::kScanTiles * sizeof(int64_t)},
       {(void**)&p->flag, sizeof(int)},
       {(void**)&p->part, part_elems * sizeof(double)},
       {(void**)&p->part_g, partg_elems * sizeof(double)},
@@ -590,14 +586,13 @@ int smcx_problem_create_fd(int model, const double* d_dev, int64_t k0, int64_t B
       {(void**)&p->fd_data, 4 * Bp * sizeof(double)},
       {(void**)&p->fd_src, (size_t)std::max<int64_t>(m_max, 1) * smcx::kFdSrcWords * sizeof(double)},
       {(void**)&p->fd_table, tab.size() * sizeof(double)},
-      {(void**)&p->order, order_bytes(n_max, k_max)},
+      {(void**)&p->order, order_bytes(n_max)},
       {(void**)&p->smc.cum, n1 * sizeof(int64_t)},
       {(void**)&p->smc.src_row, n1 * sizeof(int64_t)},
       {(void**)&p->smc.src_len, n1 * sizeof(int32_t)},
       {(void**)&p->smc.skip, n1 * sizeof(int32_t)},
       {(void**)&p->smc.append, n1 * sizeof(int32_t)},
       {(void**)&p->smc.count, n1 * sizeof(int64_t)},
-      {(void**)&p->smc.tiles, 2 * smcx::kScanTiles * sizeof(int64_t)},
       {(void**)&p->flag, sizeof(int)},
       {(void**)&p->part, n1 * 4 * sizeof(double)},
       {(void**)&p->part_g, sizeof(double)},

@@ -24,8 +24,6 @@ enum : int {
   kFlagNotPD = 128,   // a metric block is not positive definite (its factor is NaN)
 };
 
-constexpr int kScanTiles = 1024;  // most tiles of a prefix sum over particles
-
 // Per-particle workspace of the SMC steps (resampling, birth/death rebuild).
 struct SmcWork {
   int64_t* cum;      // [n_max] integer weight prefix sums within tiles
@@ -34,7 +32,6 @@ struct SmcWork {
   int32_t* skip;     // [n_max] source row left out (-1 none)
   int32_t* append;   // [n_max] 1: a row of theta_add follows
   int64_t* count;    // [n_max] rows of the output particles before it in its tile
-  int64_t* tiles;    // [2][kScanTiles] integer weight, and output rows, of each tile
 };
 
 // Workspace of the time-domain metric: the particles in groups.

@@ -51,6 +51,7 @@ __device__ void block_sum2(double& a, double& b, double* sh) {
 // loads of 16 waves to hide its latency: 40000 items took 39 and 50 us per
 // prefix pass; these launches take 3 to 7.)
 constexpr int kScanBlock = 256;
+constexpr int kScanTiles = 1024;
 
 __host__ __device__ inline int64_t scan_tile(int64_t N) {
   const int64_t per = (int64_t)kScanBlock * kScanTiles;
@@ -476,7 +477,9 @@ __global__ __launch_bounds__(kBlock) void nb_weights_kernel(NbMultiArgs a) {
 // ---------------------------------------------------------------- CSR rebuild
 // Output particle j takes rows src_row[j] .. src_row[j] + src_len[j] - 1 of
 // theta, without row skip[j] (local index, -1 = none), followed by row j of
-// theta_add when append[j] != 0.
+// theta_add when append[j] != 0. Resampling neither skips nor appends (skip and
+// append null), and the tiles' sums lie in an array that the call has no other
+// use for, so that they add nothing to what a handle holds.
 struct RebuildArgs {
   int64_t N, M;
   int P;
@@ -485,10 +488,10 @@ struct RebuildArgs {
   const double* theta;
   int64_t* src_row;   // [N] workspace
   int32_t* src_len;   // [N]
-  int32_t* skip;      // [N]
-  int32_t* append;    // [N]
+  int32_t* skip;      // [N] or nullptr
+  int32_t* append;    // [N] or nullptr
   int64_t* first;     // [N] first output row of particle j within its tile
-  int64_t* rows;      // [tiles] output rows of each tile
+  int32_t* rows;      // [tiles] output rows of each tile (of at most 2^20 particles)
   const double* theta_add;  // [N][P] rows appended (births)
   int64_t* offsets_out;     // [N + 1]
   double* theta_out;        // [m_cap][P]
@@ -542,8 +545,8 @@ __global__ __launch_bounds__(kScanBlock) void csr_gather_kernel(RebuildArgs a) {
     start = a.first[j];
     row = a.src_row[j];
     len = a.src_len[j];
-    skip = a.skip[j];
-    add = a.append[j];
+    if (a.skip) skip = a.skip[j];
+    if (a.append) add = a.append[j];
   }
   // the rows are one run of values: the first batch comes in under the base
   const int P = a.P;
@@ -602,7 +605,6 @@ struct ResampleArgs {
   const double* w_norm;
   double u;
   int64_t* cum;       // [N] prefix sums, through i, of its tile's integer weights
-  int64_t* units;     // [tiles] integer weight of each tile
   int32_t* ancestors; // [N]
 };
 
@@ -622,7 +624,6 @@ __global__ __launch_bounds__(kScanBlock) void resample_prefix_kernel(ResampleArg
     if (i < N) a.cum[i] = carry + through;
     carry += sum;
   }
-  if (threadIdx.x == 0) a.units[blockIdx.x] = carry;
 }
 
 // Offspring j: position U_j = floor(((j + u) C) / N), ancestor = first i whose
@@ -638,7 +639,8 @@ __global__ __launch_bounds__(kScanBlock) void resample_ancestor_kernel(ResampleA
   for (int g0 = 0; g0 < G; g0 += kScanBlock) {
     const int g = g0 + threadIdx.x;
     int64_t sum;
-    const int64_t x = block_scan(g < G ? a.units[g] : 0, sum, wsum);
+    const int64_t end = (g + 1) * tile < N ? (g + 1) * tile : N;
+    const int64_t x = block_scan(g < G ? a.cum[end - 1] : 0, sum, wsum);
     if (g < G) through[g] = total + x;
     total += sum;
   }
@@ -672,12 +674,10 @@ __global__ __launch_bounds__(kScanBlock) void resample_ancestor_kernel(ResampleA
       source_rows(a.r, anc, row, len);
       a.r.src_row[j] = row;
       a.r.src_len[j] = len;
-      a.r.skip[j] = -1;
-      a.r.append[j] = 0;
     }
     place_rows(a.r, j, len, carry, wsum);
   }
-  if (threadIdx.x == 0) a.r.rows[blockIdx.x] = carry;
+  if (threadIdx.x == 0) a.r.rows[blockIdx.x] = (int32_t)carry;
 }
 
 // ---------------------------------------------------------------- birth/death
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kScanBlock) void rj_decide_kernel(RjArgs a) {
     }
     place_rows(a.r, i, n, carry, wsum);
   }
-  if (threadIdx.x == 0) a.r.rows[blockIdx.x] = carry;
+  if (threadIdx.x == 0) a.r.rows[blockIdx.x] = (int32_t)carry;
 }
 
 hipError_t launch_gather(const RebuildArgs& r, hipStream_t st) {
@@ -779,12 +779,11 @@ hipError_t launch_resample(const SmcWork& w, int model, int32_t k_max, int64_t N
                            const double* w_norm, double u, int64_t m_cap, int32_t* ancestors,
                            int64_t* offsets_out, double* theta_out, int* flag, hipStream_t st) {
   ResampleArgs a;
-  a.r = RebuildArgs{N, M, n_params(model), k_max, offsets, theta, w.src_row, w.src_len, w.skip,
-                    w.append, w.count, w.tiles + kScanTiles, nullptr, offsets_out, theta_out, m_cap, flag};
+  a.r = RebuildArgs{N, M, n_params(model), k_max, offsets, theta, w.src_row, w.src_len, nullptr,
+                    nullptr, w.count, w.skip, nullptr, offsets_out, theta_out, m_cap, flag};
   a.w_norm = w_norm;
   a.u = u;
   a.cum = w.cum;
-  a.units = w.tiles;
   a.ancestors = ancestors;
   hipLaunchKernelGGL(resample_prefix_kernel, dim3(scan_tiles(N)), dim3(kScanBlock), 0, st, a);
   hipError_t e = hipGetLastError();
@@ -804,7 +803,7 @@ hipError_t launch_rj_apply(const SmcWork& w, int model, int32_t k_max, int64_t N
                            int8_t* accepted, int* flag, hipStream_t st) {
   RjArgs a;
   a.r = RebuildArgs{N, M, n_params(model), k_max, offsets, theta, w.src_row, w.src_len, w.skip,
-                    w.append, w.count, w.tiles + kScanTiles, theta_birth, offsets_out, theta_out, m_cap, flag};
+                    w.append, w.count, (int32_t*)w.cum, theta_birth, offsets_out, theta_out, m_cap, flag};
   a.move = move;
   a.death_idx = death_idx;
   a.dlogl_birth = dlogl_birth;
