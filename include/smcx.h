@@ -432,7 +432,9 @@ int smcx_nuts_transition_metric_blocks(smcx_problem* prob, int64_t N, const int6
  *              chunks ceil(T / chunk_len) must fit the workspace sized at
  *              create (at most min(64, ceil(T/1024)) chunks, and for GRAD
  *              with more than one chunk at most min(32, ceil(T/4096)))
- *   sorted     1: an ordering pass schedules particles longest-K first;
+ *   sorted     1: an ordering pass schedules particles longest-K first (a handle
+ *              whose tiling was never set leaves the pass out of calls with so
+ *              few work items that each has a SIMD to itself);
  *              0: particles are scheduled in index order; 2: longest-K first
  *              on a persistent grid (SMCX_KIND_LOGL and SMCX_KIND_GRAD: as
  *              many workgroups as the device holds at once, each wave taking

@@ -398,15 +398,15 @@ smcx::PrepArgs prep_args(smcx_problem* p, int64_t N, const int64_t* offsets, int
 }
 
 // The tiling of one call: where every work item has a SIMD to itself the order
-// in which they are handed out does not matter, and the call runs in particle
-// order without the ordering pass (pulses, K on 0..20, T = 1000: logL of 64
+// in which they are handed out does not matter, and with the default tiling the
+// call runs in particle order without the ordering pass (pulses, K on 0..20, T = 1000: logL of 64
 // particles 14.4 -> 12.2 us a call, gradient of 1000 22.9 -> 18.9; beyond two
 // items per SIMD the ordering pass wins: birth/death of 2000 particles, T =
 // 4096, 41 us against 49). Results do not depend on the order. The
 // frequency-domain kernels leave the settling of K = 0 and invalid
 // particles to the ordering pass.
 Tiling call_tiling(const smcx_problem* p, Tiling t, int64_t N) {
-  if (t.sorted == 1 && !p->fd && N * t.nch <= 4 * (int64_t)p->n_cu) {
+  if (t.sorted == 1 && !t.asked && !p->fd && N * t.nch <= 4 * (int64_t)p->n_cu) {
     t.sorted = 0;
     t.strict = 1;
   }
@@ -1290,6 +1290,7 @@ int smcx_set_tiling(smcx_problem* p, int32_t kind, int32_t S, int64_t chunk_len,
   t.chunk_len = chunk_len;
   t.nch = (int)((p->T + chunk_len - 1) / chunk_len);
   t.sorted = sorted;
+  t.asked = 1;
   if (t.nch > p->max_nch) return fail(SMCX_EINVAL, "%d chunks exceed the workspace (%d)", t.nch, p->max_nch);
   if (kind == kGrad && t.nch > 1 && t.nch > p->max_nch_grad)
     return fail(SMCX_EINVAL, "%d gradient chunks exceed the workspace (%d)", t.nch, p->max_nch_grad);

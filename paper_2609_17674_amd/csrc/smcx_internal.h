@@ -58,6 +58,7 @@ struct Tiling {
   int nch;            // chunks covering [s_lo, s_hi)
   int sorted;         // 1: items ordered by K descending (ordering pass), 0: particle order,
                       // 2: as 1 on a persistent grid (waves step through the items)
+  int asked = 0;      // 1: set by smcx_set_tiling, whose order is kept for every N
   int strict = 0;     // particle order that stands in for an ordering pass (PopArgs::strict)
 };
 
