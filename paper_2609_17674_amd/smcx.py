@@ -16,6 +16,7 @@ from typing import Optional
 
 import numpy as np
 import torch
+from torch.autograd import forward_ad
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsmcx.so")
@@ -708,9 +709,11 @@ def rj_apply(prob: Problem, offsets, theta, move, theta_birth, death_idx, dlogl_
 
 def _plain(t, dtype) -> bool:
     """An ordinary device tensor of this dtype: its memory holds its values (no
-    subclass, no vmap wrapper of either kind, no lazy negation or zero)."""
+    subclass, no vmap wrapper of either kind, no lazy negation or zero), and it
+    carries no tangent."""
     return (type(t) is torch.Tensor and t.is_cuda and t.dtype == dtype
             and torch._C._has_storage(t) and not t.is_neg() and not t._is_zerotensor()
+            and forward_ad.unpack_dual(t).tangent is None
             and not torch._C._functorch.is_functorch_wrapped_tensor(t))
 
 
@@ -724,9 +727,9 @@ class LogLGrad(torch.autograd.Function):
     a gradient (no_grad, or requires_grad False) only the forward kernel runs.
 
     The scaling is one kernel (smcx_scale_rows) where plain device tensors come
-    in and nothing is recorded; under create_graph, batched gradients, tracing
-    or a dispatch mode it is written with torch operations, which take part in
-    those (seven launches; 256 particles, forward and backward: 111 -> 90 us).
+    in and nothing is recorded; under create_graph, batched gradients, tangents of
+    forward mode or a dispatch mode it is written with torch operations, which
+    take part in those (seven launches; 256 particles, forward and backward: 111 -> 90 us).
     """
 
     @staticmethod
