@@ -132,10 +132,14 @@ def _check(rc: int):
 # The smallest calls take as long as their marshalling (6.4 us of kernel under
 # 11 us of host for 64 pulse particles), so these three stay lean: the raw stream
 # of the current device rather than a torch.cuda.Stream built from it, and
-# plain integers, which the void* argument types convert.
+# plain integers, which the void* argument types convert. Torch's private names
+# may go with a release; the public way stands behind each.
 def _stream(stream=None) -> int:
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 
@@ -707,13 +711,24 @@ def rj_apply(prob: Problem, offsets, theta, move, theta_birth, death_idx, dlogl_
     return acc, off, th
 
 
+def _one_kernel(g_logl, grad, offsets) -> bool:
+    """Whether LogLGrad's chain rule is plain arithmetic on plain tensors, with no
+    level of forward mode open whose tangents they could carry (False too where
+    this torch cannot tell)."""
+    try:
+        return (_plain(g_logl, torch.float64) and _plain(grad, torch.float64)
+                and _plain(offsets, torch.int64) and grad.is_contiguous() and offsets.is_contiguous()
+                and not torch.is_grad_enabled() and forward_ad._current_level < 0
+                and torch._C._len_torch_dispatch_stack() == 0)
+    except AttributeError:
+        return False
+
+
 def _plain(t, dtype) -> bool:
     """An ordinary device tensor of this dtype: its memory holds its values (no
-    subclass, no vmap wrapper of either kind, no lazy negation or zero), and it
-    carries no tangent."""
+    subclass, no vmap wrapper of either kind, no lazy negation or zero)."""
     return (type(t) is torch.Tensor and t.is_cuda and t.dtype == dtype
             and torch._C._has_storage(t) and not t.is_neg() and not t._is_zerotensor()
-            and forward_ad.unpack_dual(t).tangent is None
             and not torch._C._functorch.is_functorch_wrapped_tensor(t))
 
 
@@ -729,7 +744,8 @@ class LogLGrad(torch.autograd.Function):
     The scaling is one kernel (smcx_scale_rows) where plain device tensors come
     in and nothing is recorded; under create_graph, batched gradients, tangents of
     forward mode or a dispatch mode it is written with torch operations, which
-    take part in those (seven launches; 256 particles, forward and backward: 111 -> 90 us).
+    take part in those (seven launches; 256 particles, forward and backward: 111 ->
+    90 us).
     """
 
     @staticmethod
@@ -744,9 +760,7 @@ class LogLGrad(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_logl):
         grad, offsets = ctx.saved_tensors
-        if _plain(g_logl, torch.float64) and _plain(grad, torch.float64) and _plain(offsets, torch.int64) \
-                and grad.is_contiguous() and offsets.is_contiguous() \
-                and not torch.is_grad_enabled() and torch._C._len_torch_dispatch_stack() == 0:
+        if _one_kernel(g_logl, grad, offsets):
             out = torch.empty_like(grad)
             _check(load_library().smcx_scale_rows(offsets.numel() - 1, _ptr(offsets), grad.shape[0],
                                                   grad.shape[1], _ptr(g_logl), g_logl.stride(0),
