@@ -770,9 +770,11 @@ __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int 
         if (a.death_idx && a.dlogl_death) a.dlogl_death[i] = nan;
       }
       if (a.grad && !strict_bad && (rows_ok || (a.strict && o0 >= 0))) {
-        // rows past theta, or claimed by the next valid particle, are not its own
-        int64_t end = o1 < a.M ? o1 : a.M;
-        if (!rows_ok)
+        // rows past theta are not its own, nor, where the ordering pass would have
+        // written before them, those of the nearest particles with rows in range
+        // (one broken offset makes its neighbours' rows overlap)
+        int64_t m = o0, end = o1 < a.M ? o1 : a.M;
+        if (a.strict) {
           for (int64_t j = i + 1; j < a.N; ++j) {
             const int64_t q0 = a.offsets[j], q1 = a.offsets[j + 1];
             if (q0 >= 0 && q1 >= q0 && q1 <= a.M) {
@@ -780,7 +782,15 @@ __device__ __forceinline__ bool decode_item(const PopArgs& a, int64_t item, int 
               break;
             }
           }
-        for (int64_t m = o0 + lane; m < end; m += 64)
+          for (int64_t j = i - 1; j >= 0; --j) {
+            const int64_t q0 = a.offsets[j], q1 = a.offsets[j + 1];
+            if (q0 >= 0 && q1 >= q0 && q1 <= a.M) {
+              m = q1 > m ? q1 : m;
+              break;
+            }
+          }
+        }
+        for (m += lane; m < end; m += 64)
           for (int p = 0; p < P; ++p) a.grad[m * P + p] = nan;
       }
     }
