@@ -1406,11 +1406,6 @@ int smcx_rj_apply(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
   return SMCX_OK;
 }
 
-// The metric's groups live in workspace that no pass of a metric call uses otherwise.
-static smcx::MetricWork metric_work(const smcx_problem* p) {
-  return {p->order, p->smc.count, p->smc.src_len};
-}
-
 static int gn_metric(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
                      const double* theta, const double* beta, const uint8_t* mask,
                      const int64_t* f_offsets, int64_t f_size, double* F, void* hip_stream) {
@@ -1431,7 +1426,7 @@ static int gn_metric(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t
   hipStream_t st = (hipStream_t)hip_stream;
   hipError_t e = smcx::launch_metric(p->model, p->P, N, M, p->T, p->t_start, p->dt, p->inv_sigma2,
                                      p->k_max, offsets, theta, beta, f_offsets, f_size, F,
-                                     p->split, 0, p->flag, metric_work(p), p->n_cu, st, mask);
+                                     p->split, 0, p->flag, p->n_cu, st, mask);
   if (e != hipSuccess) return hip_fail(e, "metric launch");
   return SMCX_OK;
 }
@@ -1471,7 +1466,7 @@ static int gn_metric_blocks(smcx_problem* p, int64_t N, const int64_t* offsets, 
     return fail(SMCX_EINVAL, "the metric supports k_max * P <= 128 (k_max = %d)", p->k_max);
   hipError_t e = smcx::launch_metric(p->model, p->P, N, M, p->T, p->t_start, p->dt, p->inv_sigma2,
                                      p->k_max, offsets, theta, beta, nullptr, 0, F, p->split, 1,
-                                     p->flag, metric_work(p), p->n_cu, st, mask);
+                                     p->flag, p->n_cu, st, mask);
   if (e != hipSuccess) return hip_fail(e, "metric launch");
   return SMCX_OK;
 }

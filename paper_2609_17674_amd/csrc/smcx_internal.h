@@ -34,13 +34,6 @@ struct SmcWork {
   int64_t* count;    // [n_max] rows of the output particles before it in its tile
 };
 
-// Workspace of the time-domain metric: the particles in groups.
-struct MetricWork {
-  int32_t* perm;    // [n_max] particle indices, group by group
-  int64_t* groups;  // [n_max] a group's range of perm: first | end << 32
-  int32_t* cnt;     // [n_max] groups of each block of particles
-};
-
 // Number of parameters per component.
 __host__ __device__ constexpr int n_params(int model) {
   return model == SMCX_PULSE ? 3 : (model == SMCX_GBSINE ? 4 : 8);
@@ -257,8 +250,7 @@ hipError_t launch_metric(int model, int P, int64_t N, int64_t M, int64_t T, doub
                          double dt, double inv_sigma2, int32_t k_max, const int64_t* offsets,
                          const double* theta, const double* beta, const int64_t* f_offsets,
                          int64_t f_size, double* F, int64_t split, int blocks, int* flag,
-                         const MetricWork& work, int n_cu, hipStream_t st,
-                         const uint8_t* mask = nullptr);
+                         int n_cu, hipStream_t st, const uint8_t* mask = nullptr);
 // Factor W = L^{-1} of F + diag(ridge) per particle (smcx_metric.hip); ridge is
 // a host array of P values; LDS bytes of one workgroup for k_max * P = nmax.
 // Factor of M independent P x P blocks ([M][P][P], one thread each).

@@ -7,7 +7,7 @@
 // posterior; a uniform prior adds nothing inside its box).
 //
 // A wave owns up to 32 components, those of one particle or of several small
-// ones (metric_group_kernel packs them), and walks the samples in steps of 8.
+// ones (pack_groups packs them), and walks the samples in steps of 8.
 // Lane l stands for component row l % 32 and per step forms the P partials of
 // its component at four samples, in natural units (J~ = J * s with s =
 // (1, w, w) for pulses and (1, 1/T_obs, 1/T_obs^2, 1) for sinusoids, so every
@@ -26,12 +26,12 @@
 // Few particles, and k_max P > 64, take the coordinate form instead: one wave
 // per particle, lanes over its coordinates k P + p in NB blocks of 32,
 // NB (NB + 1) / 2 products per step; see launch_metric for where the line lies.
-// What bounds the grouped form: per step about 205 cycles of vector work (8 of
-// the 41 instructions are the conversions, 9 cycles each) beside 6 x 32 of the
+// What bounds the grouped form: per step about 195 cycles of vector work (8 of
+// the 39 instructions are the conversions, 9 cycles each) beside 6 x 32 of the
 // matrix cores, overlapped to about 300 at three waves per SIMD. Measured on
-// 16384 pulse particles, K uniform on 0..20, T = 4096, dense blocks: 0.50 ms
-// against 1.30-1.36 ms for the coordinate form; sinusoids, 8000 particles,
-// K on 0..16, T = 4096: 0.47 against 1.03 ms.
+// 16384 pulse particles, K uniform on 0..20, T = 4096, dense blocks: 0.41 ms
+// a call against 1.30 ms for the coordinate form; sinusoids, 8192 particles,
+// K on 0..16, T = 4096: 0.45 against 1.02 ms.
 // Error: FP16 rounding of J~ (2^-11 relative) bounds |dF~_ac| by about
 // 2^-10 sqrt(F~_aa F~_cc), plus FP32 accumulation over 512 steps.
 #include "smcx_internal.h"
@@ -78,8 +78,8 @@ struct MetricArgs {
   int blocks;      // 1: only each component's P x P block, at F + m P P (source row m)
   const uint8_t* mask;  // [N] or nullptr: particles with mask[i] == 0 get zero blocks
   int64_t split;   // samples before it carry weight 1, later ones beta_i
-  MetricWork work; // groups of particles (metric_group_kernel)
-  int nblk;        // blocks of kGroupBlock particles
+  int nblk;        // grouped form: blocks of kGroupBlock particles,
+  int slots;       // and waves (or, with several windows, sets of waves) of each
 };
 
 // Whether particle i's rows, and its output block, are as they should be; its
@@ -99,35 +99,53 @@ __device__ __forceinline__ bool metric_particle(const MetricArgs& a, int64_t i, 
 }
 
 // ---------------------------------------------------------------- groups
-// Packs the particles of each block of kGroupBlock into groups of at most 32
+// Packs the particles of a block of kGroupBlock into groups of at most 32
 // components, first-fit decreasing: a counting sort by K, then the wave opens
 // a group and keeps adding the largest particle that still fits. A group is
-// a range of perm (particle indices); block b's groups are the first cnt[b]
-// of its kGroupBlock slots. The placing is a serial chain per particle, which
-// is what the kernel's time is made of (22 us with blocks of 128 and LDS scans
-// at N = 16384): one wave takes 64 particles and scans in registers. For K
+// a range of perm (particles of the block). The placing is a serial chain per
+// particle, which a wave takes with its scans in registers. Every wave packs its
+// block for itself, into LDS: the groups in memory, from a pass of its own, would
+// be workspace that the handle's calls on other streams share. It costs no
+// more than that pass did (16384 particles, K on 0..20, dense blocks: T = 4096
+// 468 us in two launches, 455 in one; T = 1000 172, 175; T = 8 80, 88). For K
 // uniform on 0..20 the rows are 93% filled (96% in blocks of 128, 79% when
-// neighbours are taken as they come). Particles without components are in
-// no group; with a mask those not selected get their zero blocks here.
+// neighbours are taken as they come). Particles without components, and with a
+// mask those not selected, are in no group.
 constexpr int kGroupBlock = 64;
 
-__global__ __launch_bounds__(kGroupBlock) void metric_group_kernel(MetricArgs a) {
-  __shared__ int hist[64], sorted[kGroupBlock];
-  const int lane = threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.x * kGroupBlock, i = i0 + lane;
-  hist[lane] = 0;
-  __syncthreads();
+struct GroupPack {
+  int64_t row[kGroupBlock];  // per particle of the block: its first row,
+  int64_t fo[kGroupBlock];   // its output block in F
+  int K[kGroupBlock];        // and its components
+  int perm[kGroupBlock];
+  int start[kGroupBlock + 1];  // group g is perm[start[g]] .. perm[start[g + 1] - 1]
+  int groups;
+  unsigned long long zero;   // particles that get zero blocks
+  int sorted[kGroupBlock];
+};
+
+// By one wave, for the particles from i0 on; every wave that packs a block comes
+// to the same groups (equal K in particle order). raise: flag invalid particles.
+__device__ __forceinline__ void pack_groups(const MetricArgs& a, int64_t i0, int lane, bool raise,
+                                            GroupPack& pk) {
+  const int64_t i = i0 + lane;
   int K = 0;
   bool zero = false;
   if (i < a.N) {
     int64_t o0, fo;
-    if (!metric_particle(a, i, o0, K, fo, true)) K = 0;
+    if (!metric_particle(a, i, o0, K, fo, raise)) K = 0;
     zero = K > 0 && a.mask && !a.mask[i];
+    pk.row[lane] = o0;
+    pk.fo[lane] = fo;
+    pk.K[lane] = K;
     if (zero) K = 0;
   }
-  const int rank = K > 0 ? atomicAdd(&hist[K], 1) : 0;
-  __syncthreads();
-  int left = lane > 0 ? hist[lane] : 0;  // lane k: particles with K = k still to place
+  int rank = 0, left = 0;  // lane k: particles with K = k still to place
+  for (int k = 1; k <= a.k_max; ++k) {
+    const unsigned long long same = __builtin_amdgcn_ballot_w64(K == k);
+    if (K == k) rank = __popcll(same & ((1ull << lane) - 1ull));
+    if (lane == k) left = __popcll(same);
+  }
   int pos = left;
   for (int o = 1; o < 64; o <<= 1) {
     const int y = __shfl_up(pos, o);
@@ -135,12 +153,12 @@ __global__ __launch_bounds__(kGroupBlock) void metric_group_kernel(MetricArgs a)
   }
   pos -= left;  // lane k: the first place of K = k in sorted order
   const int at = __shfl(pos, K) + rank;
-  if (K > 0) sorted[at] = (int)i - (int)i0;
-  __syncthreads();
+  if (K > 0) pk.sorted[at] = lane;
+  wave_lds_order();
   int mine = 0, o = 0, g = 0;  // lane o keeps the o-th particle of the groups
   unsigned long long any = __builtin_amdgcn_ballot_w64(left > 0);
   while (any) {
-    const int start = o;
+    if (lane == 0) pk.start[g] = o;
     int rem = 32;
     for (;;) {
       const unsigned long long fit = any & ((2ull << rem) - 1ull);
@@ -154,18 +172,16 @@ __global__ __launch_bounds__(kGroupBlock) void metric_group_kernel(MetricArgs a)
       pos += lane == k ? 1 : 0;
       any = __builtin_amdgcn_ballot_w64(left > 0);
     }
-    if (lane == 0) a.work.groups[i0 + g] = ((i0 + o) << 32) | (i0 + start);
     ++g;
   }
-  if (lane == 0) a.work.cnt[blockIdx.x] = g;
-  if (lane < o) a.work.perm[i0 + lane] = (int32_t)(i0 + sorted[mine]);
-  for (unsigned long long z = __builtin_amdgcn_ballot_w64(zero); z; z &= z - 1) {
-    int64_t o0, fo;
-    int Kz;
-    metric_particle(a, i0 + __builtin_ctzll(z), o0, Kz, fo, false);
-    const int64_t n = (int64_t)Kz * a.P, cnt = a.blocks ? n * a.P : n * n;
-    for (int64_t e = lane; e < cnt; e += kGroupBlock) a.F[fo + e] = 0.0;
+  if (lane < o) pk.perm[lane] = pk.sorted[mine];
+  if (lane == 0) {
+    pk.start[g] = o;
+    pk.groups = g;
   }
+  const unsigned long long z = __builtin_amdgcn_ballot_w64(zero);
+  if (lane == 0) pk.zero = z;
+  wave_lds_order();
 }
 
 // ---------------------------------------------------------------- grouped form
@@ -347,120 +363,147 @@ __device__ __forceinline__ void flush_group(const MetricArgs& a, const FlushTile
 // several windows of samples a group's windows run side by side and are
 // flushed in order.
 // The step loop takes the partials of the next step while the products of
-// the current one are in the matrix cores.
+// the current one are in the matrix cores, two steps to a turn, which saves the
+// copies from one to the next (39 vector instructions a step instead of 46).
+// A wave takes group `slot` of block `blk`, and with more groups than slots every
+// `slots`-th from there. The waves of a workgroup go to neighbouring blocks, so
+// that it is full wherever the blocks have about as many groups.
 template <int MODEL, int WPG>
-__global__ __launch_bounds__(256, (MODEL == SMCX_PULSE ? 3 : 2)) void metric_group_wave_kernel(MetricArgs a) {
+__global__ __launch_bounds__(256, (MODEL == SMCX_PULSE ? 3 : 2)) void metric_group_kernel(MetricArgs a) {
   constexpr int P = n_params(MODEL);
   constexpr int NP = P * (P + 1) / 2;
   __shared__ FlushTile<P> tile;
   __shared__ FlushGroup<P> groups[4];
+  __shared__ GroupPack packs[4];
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   FlushGroup<P>& gr = groups[wid];
+  GroupPack& pk = packs[wid];
   const int half = lane >> 5;  // which group of 4 samples of a step this lane feeds
   const int row = lane & 31;
-  // slot s of block b: the filled slots of all blocks come first
-  const int64_t item = ((int64_t)blockIdx.x * 4 + wid) / WPG;
-  const int blk = (int)(item % a.nblk), slot = (int)(item / a.nblk);
-  const bool have = slot < kGroupBlock && slot < a.work.cnt[blk];
-  if (!__syncthreads_or(have)) return;
-  int64_t g0 = 0;
-  int parts = 0;
-  if (have) {
-    const int64_t g = a.work.groups[(int64_t)blk * kGroupBlock + slot];
-    g0 = g & 0xffffffffll;
-    parts = (int)((g >> 32) - g0);
-  }
-  // lane l < parts holds the group's l-th particle
-  int Kl = 0, end = 0;
-  int64_t ol = 0;
-  if (lane < parts) {
-    const int64_t i = a.work.perm[g0 + lane];
-    ol = a.offsets[i];
-    Kl = (int)(a.offsets[i + 1] - ol);
-    gr.beta[lane] = a.beta ? a.beta[i] : 1.0;
-    gr.fo[lane] = a.blocks ? ol * P * P : a.f_offsets[i];
-    gr.K[lane] = Kl;
-  }
-  if (lane == 0) gr.parts = parts;
-  end = Kl;
-  for (int o = 1; o < 32; o <<= 1) {
-    const int y = __shfl_up(end, o);
-    if (lane >= o) end += y;
-  }
-  if (lane < parts) gr.r0[lane] = end - Kl;
-  // this lane's component: row `row` of the group
-  Comp<MODEL> q;
-  int64_t src = -1;  // its row of theta
-  for (int l = 0; l < parts; ++l) {
-    const int e = __builtin_amdgcn_readlane(end, l), k = __builtin_amdgcn_readlane(Kl, l);
-    const int64_t o = ((int64_t)__builtin_amdgcn_readlane((int)(ol >> 32), l) << 32) |
-                      (uint32_t)__builtin_amdgcn_readlane((int)ol, l);
-    if (row >= e - k && row < e) src = o + row - (e - k);
-  }
-  if (src >= 0) {
-    double natural[P];
-    make_comp(a, a.theta + src * P, q, natural);
-    if (half == 0)
-      for (int p = 0; p < P; ++p) gr.scale[row * P + p] = 1.0 / natural[p];
-  }
-  const float tr0 = (float)(a.t_start / a.t_obs), dtr = (float)(a.dt / a.t_obs);
-  const float nf = centre(q);
-  // windows of at most 4096 samples, none across the split
-  const int nlo = (int)((a.split + kFlushSamples - 1) / kFlushSamples);
-  const int nwin = nlo + (int)((a.T - a.split + kFlushSamples - 1) / kFlushSamples);
-  for (int w = 0; w < nwin; w += WPG) {
-    const int win = w + wid % WPG;
-    float16v acc[NP];
-#pragma unroll
-    for (int y = 0; y < NP; ++y) acc[y] = float16v{};
-    if (have && win < nwin) {
-      const bool lo = win < nlo;
-      // sample indices fit in 32 bits (T <= 2^22)
-      const int w0 = lo ? win * kFlushSamples : (int)a.split + (win - nlo) * kFlushSamples;
-      const int last = lo ? (int)a.split : (int)a.T;
-      const int w1 = w0 + kFlushSamples < last ? w0 + kFlushSamples : last;
-      const int full = w0 + (w1 - w0) / 8 * 8;
-      float x = (float)(w0 + 4 * half) - nf;  // exact: integers below 2^24
-      half4 h[P];
-      if (full > w0) {
-        step_partials<MODEL, P, false>(q, x, w0 + 4 * half, w1, tr0, dtr, h);
-#pragma unroll 1
-        for (int s = w0 + 8; s < full; s += 8) {
-          half4 hn[P];
-          x += 8.f;
-          step_partials<MODEL, P, false>(q, x, s + 4 * half, w1, tr0, dtr, hn);
-          step_products<P>(h, acc);
-#pragma unroll
-          for (int y = 0; y < NP; ++y) {
-            // one product, then a share of the next step's vector work
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x402, MODEL == SMCX_PULSE ? 7 : 9, 0);
-          }
-#pragma unroll
-          for (int p = 0; p < P; ++p) h[p] = hn[p];
-        }
-        step_products<P>(h, acc);
-        x += 8.f;
-      }
-      if (full < w1) {
-        step_partials<MODEL, P, true>(q, x, full + 4 * half, w1, tr0, dtr, h);
-        step_products<P>(h, acc);
-      }
+  // the first groups of all blocks come first
+  const unsigned item = (blockIdx.x * 4u + (unsigned)wid) / WPG;
+  int slot = (int)(item / (unsigned)a.nblk);
+  const int64_t i0 = (int64_t)(item - (unsigned)slot * (unsigned)a.nblk) * kGroupBlock;
+  int ngroups = 0;
+  if (slot < a.slots) {
+    pack_groups(a, i0, lane, slot == 0, pk);
+    ngroups = __builtin_amdgcn_readfirstlane(pk.groups);
+    // not selected: zero blocks (the factor's ridge makes them definite)
+    int t = 0;
+    for (unsigned long long z = pk.zero; z; z &= z - 1, ++t) {
+      if (t % a.slots != slot || wid % WPG) continue;
+      const int l = __builtin_ctzll(z);
+      const int64_t n = (int64_t)pk.K[l] * P, cnt = a.blocks ? n * P : n * n;
+      for (int64_t e = lane; e < cnt; e += 64) a.F[pk.fo[l] + e] = 0.0;
     }
-    // flush, one wave's products after the other: lane holds D[i][j] of rows
-    // j = lane % 32 and i = 8 (r/4) + 4 half + r % 4
-    for (int turn = 0; turn < 4; ++turn) {
-      __syncthreads();
-      if (wid == turn)
+  }
+  for (;; slot += a.slots) {
+    const bool have = slot < ngroups;
+    if (!__syncthreads_or(have)) return;
+    const int g = slot;
+    const int first = have ? pk.start[g] : 0, parts = have ? pk.start[g + 1] - first : 0;
+    // lane l < parts holds the group's l-th particle
+    int Kl = 0, end = 0;
+    int64_t ol = 0;
+    if (lane < parts) {
+      const int l = pk.perm[first + lane];
+      ol = pk.row[l];
+      Kl = pk.K[l];
+      gr.beta[lane] = a.beta ? a.beta[i0 + l] : 1.0;
+      gr.fo[lane] = pk.fo[l];
+      gr.K[lane] = Kl;
+    }
+    if (lane == 0) gr.parts = parts;
+    end = Kl;
+    for (int o = 1; o < 32; o <<= 1) {
+      const int y = __shfl_up(end, o);
+      if (lane >= o) end += y;
+    }
+    if (lane < parts) gr.r0[lane] = end - Kl;
+    // this lane's component: row `row` of the group
+    Comp<MODEL> q;
+    int64_t src = -1;  // its row of theta
+    for (int l = 0; l < parts; ++l) {
+      const int e = __builtin_amdgcn_readlane(end, l), k = __builtin_amdgcn_readlane(Kl, l);
+      const int64_t o = ((int64_t)__builtin_amdgcn_readlane((int)(ol >> 32), l) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)ol, l);
+      if (row >= e - k && row < e) src = o + row - (e - k);
+    }
+    if (src >= 0) {
+      double natural[P];
+      make_comp(a, a.theta + src * P, q, natural);
+      if (half == 0)
+        for (int p = 0; p < P; ++p) gr.scale[row * P + p] = 1.0 / natural[p];
+    }
+    const float tr0 = (float)(a.t_start / a.t_obs), dtr = (float)(a.dt / a.t_obs);
+    const float nf = centre(q);
+    // windows of at most 4096 samples, none across the split
+    const int nlo = (int)((a.split + kFlushSamples - 1) / kFlushSamples);
+    const int nwin = nlo + (int)((a.T - a.split + kFlushSamples - 1) / kFlushSamples);
+    for (int w = 0; w < nwin; w += WPG) {
+      const int win = w + wid % WPG;
+      float16v acc[NP];
 #pragma unroll
-        for (int y = 0; y < NP; ++y)
+      for (int y = 0; y < NP; ++y) acc[y] = float16v{};
+      if (have && win < nwin) {
+        const bool lo = win < nlo;
+        // sample indices fit in 32 bits (T <= 2^22)
+        const int w0 = lo ? win * kFlushSamples : (int)a.split + (win - nlo) * kFlushSamples;
+        const int last = lo ? (int)a.split : (int)a.T;
+        const int w1 = w0 + kFlushSamples < last ? w0 + kFlushSamples : last;
+        const int full = w0 + (w1 - w0) / 8 * 8;
+        float x = (float)(w0 + 4 * half) - nf;  // exact: integers below 2^24
+        half4 h[P];
+        if (full > w0) {
+          step_partials<MODEL, P, false>(q, x, w0 + 4 * half, w1, tr0, dtr, h);
+          int s = w0 + 8;
+          // the products of one step, the partials of the next
+          const auto step = [&](const half4(&hc)[P], half4(&hn)[P]) {
+            x += 8.f;
+            step_partials<MODEL, P, false>(q, x, s + 4 * half, w1, tr0, dtr, hn);
+            step_products<P>(hc, acc);
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            tile.d[y][(8 * (r >> 2) + 4 * half + (r & 3)) * 33 + row] = acc[y][r];
-      __syncthreads();
-      const int wt = w + turn % WPG;  // that wave's window
-      if (wt < nwin) flush_group<P>(a, tile, groups[turn], wt >= nlo, wt == 0);
+            for (int y = 0; y < NP; ++y) {
+              // one product, then a share of the next step's vector work
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x402, MODEL == SMCX_PULSE ? 7 : 9, 0);
+            }
+            s += 8;
+          };
+          half4 hn[P];
+#pragma unroll 1
+          while (s + 8 < full) {  // two steps: no copies from one to the next
+            step(h, hn);
+            step(hn, h);
+          }
+          if (s < full) {
+            step(h, hn);
+#pragma unroll
+            for (int p = 0; p < P; ++p) h[p] = hn[p];
+          }
+          step_products<P>(h, acc);
+          x += 8.f;
+        }
+        if (full < w1) {
+          step_partials<MODEL, P, true>(q, x, full + 4 * half, w1, tr0, dtr, h);
+          step_products<P>(h, acc);
+        }
+      }
+      // flush, one wave's products after the other: lane holds D[i][j] of rows
+      // j = lane % 32 and i = 8 (r/4) + 4 half + r % 4
+      for (int turn = 0; turn < 4; ++turn) {
+        __syncthreads();
+        if (wid == turn)
+#pragma unroll
+          for (int y = 0; y < NP; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              tile.d[y][(8 * (r >> 2) + 4 * half + (r & 3)) * 33 + row] = acc[y][r];
+        __syncthreads();
+        const int wt = w + turn % WPG;  // that wave's window
+        if (wt < nwin) flush_group<P>(a, tile, groups[turn], wt >= nlo, wt == 0);
+      }
     }
   }
 }
@@ -1235,22 +1278,24 @@ hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
 
 namespace {
 template <int MODEL>
-hipError_t launch_groups(const MetricArgs& a, int64_t windows, hipStream_t st) {
-  hipLaunchKernelGGL(metric_group_kernel, dim3((unsigned)a.nblk), dim3(kGroupBlock), 0, st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t items = (int64_t)a.nblk * kGroupBlock;  // most slots are empty
+hipError_t launch_groups(MetricArgs a, int64_t windows, hipStream_t st) {
   // one wave per group on a single window, else up to four windows of a group
   // at once (a long record of few particles has few groups)
-  if (windows == 1)
-    hipLaunchKernelGGL((metric_group_wave_kernel<MODEL, 1>), dim3((unsigned)((items + 3) / 4)),
-                       dim3(256), 0, st, a);
-  else if (windows == 2)
-    hipLaunchKernelGGL((metric_group_wave_kernel<MODEL, 2>), dim3((unsigned)((items + 1) / 2)),
-                       dim3(256), 0, st, a);
+  const int wpg = windows == 1 ? 1 : (windows == 2 ? 2 : 4);
+  // slots per block: its groups on average, and a quarter more for the blocks
+  // above it (beyond, a wave takes further groups; an idle one costs its
+  // packing); above 16 components a group holds one particle
+  const int64_t per = std::min<int64_t>(a.N, kGroupBlock);
+  const int64_t rows = (a.M * per + a.N - 1) / a.N;
+  const int64_t full = a.M > 16 * a.N ? per : (rows + 31) / 32;
+  a.slots = (int)std::min(per, full + (full + 3) / 4 + 1);
+  const dim3 grid((unsigned)(((int64_t)a.nblk * a.slots * wpg + 3) / 4)), block(256);
+  if (wpg == 1)
+    hipLaunchKernelGGL((metric_group_kernel<MODEL, 1>), grid, block, 0, st, a);
+  else if (wpg == 2)
+    hipLaunchKernelGGL((metric_group_kernel<MODEL, 2>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((metric_group_wave_kernel<MODEL, 4>), dim3((unsigned)items), dim3(256), 0, st,
-                       a);
+    hipLaunchKernelGGL((metric_group_kernel<MODEL, 4>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 }  // namespace
@@ -1259,10 +1304,10 @@ hipError_t launch_metric(int model, int P, int64_t N, int64_t M, int64_t T, doub
                          double dt, double inv_sigma2, int32_t k_max, const int64_t* offsets,
                          const double* theta, const double* beta, const int64_t* f_offsets,
                          int64_t f_size, double* F, int64_t split, int blocks, int* flag,
-                         const MetricWork& work, int n_cu, hipStream_t st, const uint8_t* mask) {
+                         int n_cu, hipStream_t st, const uint8_t* mask) {
   MetricArgs a{P, N, M, T, t_start, dt, inv_sigma2, (double)T * dt, k_max, offsets, theta,
-               beta, f_offsets, f_size, F, flag, 0, 0, 1, blocks, mask, split, work,
-               (int)((N + kGroupBlock - 1) / kGroupBlock)};
+               beta, f_offsets, f_size, F, flag, 0, 0, 1, blocks, mask, split,
+               (int)((N + kGroupBlock - 1) / kGroupBlock), 1};
   const int nmax = k_max * P;
   if (nmax > 128) return hipErrorInvalidValue;
   const int nb = nmax <= 32 ? 1 : (nmax <= 64 ? 2 : 4);
