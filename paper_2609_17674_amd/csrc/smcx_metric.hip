@@ -1313,19 +1313,25 @@ hipError_t launch_metric(int model, int P, int64_t N, int64_t M, int64_t T, doub
   const int nb = nmax <= 32 ? 1 : (nmax <= 64 ? 2 : 4);
   {
     // The grouped form saves vector work and takes several windows at once,
-    // but spends about 30 us on packing and flushing and more per step of
+    // but spends about 40 us on packing and flushing and more per step of
     // a lone wave (0.15 us against 0.09 with one block of coordinates). It wins
     // where the coordinate form would put four waves of work or more on each
-    // SIMD (pulses, K on 0..7, T = 4096: 222 -> 128 us at 4000 particles, 84 ->
-    // 122 at 1000; K on 0..21: 395 -> 194 at 4000, 142 -> 118 at 1000), or
-    // on more than two windows (200 particles, T = 20000: 333 -> 191 us).
+    // SIMD, with 1024 samples or more for their products (in us, coordinate
+    // against grouped form; pulses, K on 0..10: 6000 particles, T = 500: 60, 63,
+    // T = 1000: 95, 73; 4096, T = 500: 46, 64, T = 1000: 71, 71, T = 4096: 223,
+    // 115; 2048, T = 1500: 58, 73. K on 0..20, three products a sample: 2048,
+    // T = 500: 54, 58, T = 1000: 73, 65; 1024, T = 4096: 140, 115, left with the
+    // coordinate form. Sinusoids, K on 0..8: 4096, T = 500: 57, 74, T = 1500:
+    // 125, 104), or on more than two windows (256 pulse particles, T = 16384: 264,
+    // 131).
     // Beyond 64 coordinates the compiler rounds some of the coordinate
     // form's products to FP32 before FP16 and others once, depending on the
     // block; the grouped form would change F by 2e-7 there (below it gives the
     // same bits), so those keep the coordinate form.
     const int64_t windows = (split + kFlushSamples - 1) / kFlushSamples +
                             (T - split + kFlushSamples - 1) / kFlushSamples;
-    if (nb <= 2 && (windows > 2 || N * nb >= 16 * (int64_t)n_cu))
+    const int64_t waves = 16 * (int64_t)n_cu, products = N * (nb * (nb + 1) / 2);  // per sample
+    if (nb <= 2 && (windows > 2 || (N * nb >= waves && products * T >= 1024 * waves)))
       return model == SMCX_PULSE ? launch_groups<SMCX_PULSE>(a, windows, st)
                                  : launch_groups<SMCX_GBSINE>(a, windows, st);
   }
