@@ -1539,7 +1539,7 @@ static int metric_factor(smcx_problem* p, int64_t N, const int64_t* offsets, int
                 nmax, smcx::factor_lds_bytes(nmax), p->lds_max);
   hipStream_t st = (hipStream_t)hip_stream;
   hipError_t e = smcx::launch_metric_factor(p->P, N, M, p->k_max, offsets, f_offsets, f_size, F,
-                                            ridge, block, W, p->flag, p->order, p->n_cu, st, mask);
+                                            ridge, block, W, p->flag, p->n_cu, st, mask);
   if (e != hipSuccess) return hip_fail(e, "metric factor launch");
   return SMCX_OK;
 }

@@ -35,7 +35,6 @@
 // Error: FP16 rounding of J~ (2^-11 relative) bounds |dF~_ac| by about
 // 2^-10 sqrt(F~_aa F~_cc), plus FP32 accumulation over 512 steps.
 #include "smcx_internal.h"
-#include "smcx_prep.h"
 
 #include <algorithm>
 
@@ -717,7 +716,8 @@ struct FactorArgs {
   int block;        // 0: the whole block; b: its block-diagonal part in b x b blocks
   int* flag;
   const uint8_t* mask;  // [N] or nullptr: particles with mask[i] == 0 are skipped
-  const int32_t* order;  // [prep_ranks(N)] particles, largest K first (-1: none), or nullptr
+  int slices;       // register form: 1: slices of kFactorSlice particles, each handed out
+                    // largest K first; 0: particle order
 };
 
 __device__ __forceinline__ int tri(int r, int c) { return r * (r + 1) / 2 + c; }
@@ -900,7 +900,6 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
     wave_lds_order();
   }
   double pivot = 1.0;
-  bool good = true;
 #pragma unroll 1
   for (int jb = 0; jb < NR; jb += 8) {
     // the block's rows before its steps, for the update of the other columns:
@@ -971,8 +970,8 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
 #pragma unroll
     for (int u = 0; u < 8; ++u) r[NR - 8 + u] = t[u];
   }
-  if (!good) return false;
   const double s = 1.0 / sqrt(pivot);
+  asm volatile("" : "+v"(lane));  // what the output takes from it is formed anew, not held
 #pragma unroll
   for (int c0 = 0; c0 < NR; c0 += 16) {
     if (lane < NR)
@@ -980,56 +979,44 @@ __device__ __forceinline__ bool factor_rows(const FactorArgs& a, const double* F
       for (int u = 0; u < 16; ++u)
         if (c0 + u < NR) sh[lane * kRowPad + u] = r[c0 + u] * s;
     wave_lds_order();
-    const int c = c0 + sub;
+    const int c = c0 + (lane & 15);
     if (c < n)
-      for (int row = lane >> 4; row < n; row += 4) Wi[row * n + c] = sh[row * kRowPad + sub];
+      for (int row = lane >> 4; row < n; row += 4) Wi[row * n + c] = sh[row * kRowPad + (lane & 15)];
     wave_lds_order();
   }
   return true;
 }
 
-// Particles largest K first, as the ordering pass of the likelihood calls (every
-// slice of kPrepSlice sorted by itself, the slices' p-th particles in turn), but
-// of every particle: the factor validates for itself. With blocks of n = 3 to 60
-// in particle order the last, long ones left the device idle for a quarter of
-// the time (113 us repeated, against 85; the mean over populations of one size is 80).
-constexpr int kFactorKeys = 65;  // K of the register form: k_max P <= 64
+// The p-th longest particle of the slice of 64 that starts at i0, by one wave: its
+// index, or -1 where the slice has fewer. Handing out the longest of every slice,
+// then the second longest and so on starts the long blocks first, as one sorted
+// list would, and needs no list: a wave finds its own particle from one load of
+// the slice's offsets. With blocks of n = 3 to 60 in particle order the last,
+// long ones left the device idle for a quarter of the time (8192 blocks: 113 us
+// repeated; with a list from a launch of its own 86, and workspace that the
+// handle's calls on other streams share; this way 86. 20000 blocks: 205 to 213
+// with the list, 210 to 220). Particles of equal K come in index order, and every
+// particle is some wave's: an invalid one counts as the longest or as empty,
+// and the factor validates for itself.
+constexpr int kFactorSlice = 64;
 
-__global__ __launch_bounds__(kPrepBlock) void factor_order_kernel(const int64_t* offsets, int64_t N,
-                                                                  int64_t S, int32_t* order) {
-  __shared__ int hist[kFactorKeys];
-  const int tid = threadIdx.x;
-  const int64_t len = prep_slice_len(N, S), base = blockIdx.x * len;
-  const int64_t end = base + len < N ? base + len : N;
-  if (tid < kFactorKeys) hist[tid] = 0;
-  __syncthreads();
-  int key[kPrepUnroll];
-#pragma unroll
-  for (int u = 0; u < kPrepUnroll; ++u) {
-    const int64_t i = base + (int64_t)u * kPrepBlock + tid, j = i < N ? i : N - 1;
-    const int64_t K = offsets[j + 1] - offsets[j];
-    key[u] = i < end ? (int)min(max(K, (int64_t)0), (int64_t)(kFactorKeys - 1)) : -1;
-  }
-#pragma unroll
-  for (int u = 0; u < kPrepUnroll; ++u)
-    if (key[u] >= 0) atomicAdd(&hist[key[u]], 1);
-  __syncthreads();
-  if (tid < 64) {  // places of the keys 64, 63, ..: an exclusive prefix (key 0 follows them)
-    const int own = hist[kFactorKeys - 1 - tid];
-    int run = own;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(run, o);
-      if (tid >= o) run += y;
+__device__ __forceinline__ int64_t slice_particle(const FactorArgs& a, int64_t i0, int p) {
+  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int64_t i = i0 + lane, j = i < a.N ? i : a.N - 1;
+  const int64_t K = a.offsets[j + 1] - a.offsets[j];
+  const int key = i < a.N ? (int)min(max(K, (int64_t)0), (int64_t)a.k_max + 1) : -1;
+  for (int k = a.k_max + 1; k >= 0; --k) {
+    const unsigned long long same = __builtin_amdgcn_ballot_w64(key == k);
+    const int n = __popcll(same);
+    if (p >= n) {
+      p -= n;
+      continue;
     }
-    hist[kFactorKeys - 1 - tid] = run - own;
-    if (tid == 63) hist[0] = run;
+    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+    return i0 + __builtin_ctzll(__builtin_amdgcn_ballot_w64(key == k && before == p));
   }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < kPrepUnroll; ++u)
-    if (key[u] >= 0)
-      order[atomicAdd(&hist[key[u]], 1) * S + blockIdx.x] = (int32_t)(base + (int64_t)u * kPrepBlock + tid);
-  for (int64_t p = max(end - base, (int64_t)0) + tid; p < len; p += kPrepBlock) order[p * S + blockIdx.x] = -1;
+  return -1;
 }
 
 // One wave per particle, CAP >= k_max P rows at most.
@@ -1037,8 +1024,15 @@ template <int CAP>
 __global__ __launch_bounds__(64, (CAP <= 32 ? 5 : 3)) void factor_rows_kernel(FactorArgs a) {
   __shared__ double sh[CAP * kRowPad];
   const int lane = threadIdx.x;
-  const int64_t i = a.order ? a.order[blockIdx.x] : (int64_t)blockIdx.x;
-  if (i < 0) return;
+  int64_t i = blockIdx.x;
+  if (a.slices) {
+    // row p of the grid takes the slices' p-th particles, turned by p, so that a
+    // slice does not fall to the same dies every time
+    unsigned s = blockIdx.x + blockIdx.y;
+    while (s >= gridDim.x) s -= gridDim.x;
+    i = slice_particle(a, (int64_t)s * kFactorSlice, (int)blockIdx.y);
+    if (i < 0) return;
+  }
   const int64_t o0 = a.offsets[i], o1 = a.offsets[i + 1];
   if (!(o0 >= 0 && o1 >= o0 && o1 <= a.M && o1 - o0 <= a.k_max)) {
     if (lane == 0) atomicOr(a.flag, kFlagOffsets);
@@ -1234,8 +1228,7 @@ size_t factor_lds_bytes(int nmax) { return (size_t)nmax * (nmax + 1) / 2 * sizeo
 hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
                                 const int64_t* offsets, const int64_t* f_offsets, int64_t f_size,
                                 const double* F, const double* ridge, int block, double* W,
-                                int* flag, int32_t* order, int n_cu, hipStream_t st,
-                                const uint8_t* mask) {
+                                int* flag, int n_cu, hipStream_t st, const uint8_t* mask) {
   FactorArgs a{};
   a.P = P;
   a.N = N;
@@ -1256,15 +1249,10 @@ hipError_t launch_metric_factor(int P, int64_t N, int64_t M, int32_t k_max,
   // leave most lanes of either form idle
   if (block == 0 && k_max * P <= 64) {
     // more particles than the device holds at once (three waves per SIMD of
-    // the 64-row form): longest first, 5 us for a quarter of the time
-    int64_t ranks = N;
-    if (N > 12 * (int64_t)n_cu) {
-      const int64_t S = prep_slices(N);
-      ranks = prep_ranks(N);
-      hipLaunchKernelGGL(factor_order_kernel, dim3((unsigned)S), dim3(kPrepBlock), 0, st, offsets, N, S, order);
-      a.order = order;
-    }
-    const dim3 grid((unsigned)ranks);
+    // the 64-row form): longest first
+    a.slices = N > 12 * (int64_t)n_cu;
+    const dim3 grid = a.slices ? dim3((unsigned)((N + kFactorSlice - 1) / kFactorSlice), kFactorSlice)
+                               : dim3((unsigned)N);
     if (k_max * P <= 32)
       hipLaunchKernelGGL(factor_rows_kernel<32>, grid, dim3(64), 0, st, a);
     else
