@@ -1217,8 +1217,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // small K take fifty steps. In lockstep (a launch each for source rows, gradient
 // and leaf over the particles still extending) the late leaves cost 20 to 37 us
 // of launches for little work, and the host had to read after each doubling
-// whether any were left. Here the long chains, taken first (smallest K
-// first), overlap the short ones. Every value is formed by the operations of
+// whether any were left. Here the long chains, taken first, overlap the short
+// ones. Every value is formed by the operations of
 // the lockstep steps (smcx_nuts.h) in their order. 24000 particles, K on 1..10,
 // depth 6: 1210 us and six host reads in lockstep, 456 here, 250 to 330 of them the
 // longest trajectories' latency.
@@ -1648,8 +1648,11 @@ __global__ __launch_bounds__(64 * traj_waves<NR>(), 1) void fd_trajectory_kernel
     r = __builtin_amdgcn_readfirstlane(r);
     if (r >= cnt) return;
     FdItem it;
-    // the order's last rank first: smallest K
-    if (!fd_item_at(z.a, cnt - 1 - r, it) || it.K == 0) continue;
+    // with a mass matrix smallest K first (the order's last rank), whose trees run
+    // deepest; without one nearly all run to the end, and the largest K takes
+    // longest (3000 particles, K on 10..40, depth 6, 58 steps on average: 13.8 ms
+    // smallest first, 9.5 largest first; 40000, K on 1..10: 27.2, 26.1)
+    if (!fd_item_at(z.a, z.na.wmat ? cnt - 1 - r : r, it) || it.K == 0) continue;
     it.i = __builtin_amdgcn_readfirstlane((int)it.i);  // particles and rows are below 2^31
     it.m0 = __builtin_amdgcn_readfirstlane((int)it.m0);
     it.K = __builtin_amdgcn_readfirstlane(it.K);
