@@ -402,11 +402,14 @@ smcx::PrepArgs prep_args(smcx_problem* p, int64_t N, const int64_t* offsets, int
 // call runs in particle order without the ordering pass (pulses, K on 0..20, T = 1000: logL of 64
 // particles 14.4 -> 12.2 us a call, gradient of 1000 22.9 -> 18.9; beyond two
 // items per SIMD the ordering pass wins: birth/death of 2000 particles, T =
-// 4096, 41 us against 49). Results do not depend on the order. The
+// 4096, 41 us against 49), or, for a k_max in the hundreds, a place in the LDS
+// (gradient of 1000 sinusoid particles, K on 0..10, T = 4000, k_max = 512: 54 us
+// in particle order, 44 longest first). Results do not depend on the order. The
 // frequency-domain kernels leave the settling of K = 0 and invalid
 // particles to the ordering pass.
-Tiling call_tiling(const smcx_problem* p, Tiling t, int64_t N) {
-  if (t.sorted == 1 && !t.asked && !p->fd && N * t.nch <= 4 * (int64_t)p->n_cu) {
+Tiling call_tiling(const smcx_problem* p, Tiling t, int64_t N, bool grad) {
+  if (t.sorted == 1 && !t.asked && !p->fd &&
+      N * t.nch <= std::min<int64_t>(4, smcx::lds_items(p->model, p->k_max, grad)) * p->n_cu) {
     t.sorted = 0;
     t.strict = 1;
   }
@@ -696,7 +699,7 @@ int logl_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
   if (N == 0) return SMCX_OK;
   hipStream_t st = (hipStream_t)hip_stream;
   const double k0 = k0_tempered(p);
-  const Tiling t = call_tiling(p, p->tiling[kFwd], N);
+  const Tiling t = call_tiling(p, p->tiling[kFwd], N, false);
   smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, k0);
   a.split = p->split;
   a.k0_lo = k0_untempered(p);
@@ -725,7 +728,7 @@ static int grad_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64_
   if (N == 0) return SMCX_OK;
   hipStream_t st = (hipStream_t)hip_stream;
   const double k0 = k0_tempered(p);
-  const Tiling t = call_tiling(p, p->tiling[kGrad], N);
+  const Tiling t = call_tiling(p, p->tiling[kGrad], N, true);
   smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, k0);
   a.split = p->split;
   a.k0_lo = k0_untempered(p);
@@ -774,7 +777,7 @@ static int delta_batch(smcx_problem* p, int64_t N, const int64_t* offsets, int64
   if (N == 0 || (!theta_birth && !death_idx)) return SMCX_OK;
   if (p->k_max + 1 > 513) return fail(SMCX_EINVAL, "k_max too large for the birth slot");
   hipStream_t st = (hipStream_t)hip_stream;
-  const Tiling t = call_tiling(p, p->tiling[kDelta], N);
+  const Tiling t = call_tiling(p, p->tiling[kDelta], N, false);
   smcx::PopArgs a = base_args(p, N, offsets, M, theta, beta, t, 0, p->T, 0.0);
   a.split = p->split;
   a.k0_lo = k0_untempered(p);
@@ -838,7 +841,7 @@ int reweight_extend(smcx_problem* p, int64_t T1, int64_t T2, int64_t N, const in
   hipStream_t st = (hipStream_t)hip_stream;
   if (N > 0) {
     const double k0 = -0.5 * (p->prefix[T2] - p->prefix[T1]) * p->inv_sigma2;
-    const Tiling t = call_tiling(p, with_range(p->tiling[kFwd], T2 - T1), N);
+    const Tiling t = call_tiling(p, with_range(p->tiling[kFwd], T2 - T1), N, false);
     hipError_t e = hipSuccess;
     if (t.sorted) {
       smcx::PrepArgs pa = prep_args(p, N, offsets, M, nullptr, k0, 0);
@@ -938,7 +941,7 @@ int smcx_leapfrog(smcx_problem* p, int64_t N, const int64_t* offsets, int64_t M,
                               q_out, p_out, g_out};
   hipError_t e;
   const double k0 = k0_tempered(p);
-  const Tiling t = call_tiling(p, p->tiling[kGrad], N);
+  const Tiling t = call_tiling(p, p->tiling[kGrad], N, true);
   if (t.sorted) {
     smcx::PrepArgs pa = prep_args(p, N, offsets, M, beta, k0, 1);
     pa.k0_lo = k0_untempered(p);

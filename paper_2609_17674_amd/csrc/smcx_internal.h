@@ -316,5 +316,7 @@ hipError_t launch_plain_particle(int model, const double* d64, int64_t T, double
                                  double* logl, double* grad_rows, hipStream_t st);
 
 size_t pop_lds_bytes_per_wave(int model, int32_t k_max, bool grad);
+// Work items that a compute unit's LDS holds in the plain kernels (a wave each).
+int64_t lds_items(int model, int32_t k_max, bool grad);
 
 }  // namespace smcx

@@ -1102,6 +1102,7 @@ __global__ __launch_bounds__(256, (pop_waves_per_simd<MODEL, S, GRAD>())) void p
 // 300, K on 0..10, T = 16384: 54 -> 23; 64 sinusoid particles, K on 0..20, T =
 // 8000: 57 -> 20.
 constexpr int kPopTiles = 4;
+constexpr size_t kLdsPerCu = 160 << 10;
 
 template <int MODEL, int S, bool GRAD>
 __global__ __launch_bounds__(64 * kPopTiles, (pop_waves_per_simd<MODEL, S, GRAD>())) void pop_tile_kernel(
@@ -1608,6 +1609,29 @@ int waves_per_block(int model, int32_t k_max, bool grad) {
   return w;
 }
 
+// Tiles of a call's longest chunk (more than kPopTiles count as one more).
+int tile_count(const Tiling& t, const PopArgs& a) {
+  const int64_t len = std::min(a.chunk_len, a.s_hi - a.s_lo);
+  return (int)std::min<int64_t>((len + 64 * t.S - 1) / (64 * t.S), kPopTiles + 1);
+}
+
+// Whether a workgroup takes an item with a wave per tile. Every wave keeps the
+// constants for itself, so where the LDS and not the waves fill the device (k_max in
+// the hundreds) the plain kernel is better off from 1.5 rounds of its items on:
+// gradients of 4000 pulse particles, K on 0..10, T = 2000: k_max = 150 (1.3
+// rounds) 28.0 us plain, 27.5 tiles; 200 (2.0) 32.5, 33.1; 400 (3.9) 48.5, 54.2;
+// 2000, K on 0..20, T = 4096, k_max = 300 (1.3) 56.0, 47.7; birth/death of 4000
+// sinusoid particles, k_max = 300 (2.0) 32.0, 34.4. Workgroups of more than 64
+// KiB only where each has its place (300 pulse particles, T = 4096, k_max = 512,
+// birth/death: 41.5, 18).
+template <int MODEL>
+bool tile_form(const PopArgs& a, bool grad, int64_t items, int nt, size_t tile_lds, int64_t waves_per_cu) {
+  const int64_t n_cu = a.n_cu > 0 ? a.n_cu : 256;
+  if (nt < 2 || nt > kPopTiles || items * nt > waves_per_cu * n_cu) return false;
+  if (tile_lds > 65536) return items <= (int64_t)(kLdsPerCu / tile_lds) * n_cu;
+  return 2 * items <= 3 * lds_items(MODEL, a.k_max, grad) * n_cu;
+}
+
 template <int MODEL, int S, bool GRAD>
 const void* pop_fn(bool persist) {
   return persist ? (const void*)pop_kernel<MODEL, S, GRAD, true>
@@ -1643,12 +1667,10 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   // the waves of a likelihood pass fit the device at once (32 per unit; 8000
   // pulse particles, K on 0..5, T = 3000: 19.0 us against 19.6), and for the
   // gradient, whose items are longer, up to twice that (8000, K on 0..20, T =
-  // 4096: 85.5 against 82.2; 16384: 149.0 against 149.4)
-  const int64_t len = std::min(a.chunk_len, a.s_hi - a.s_lo);
-  const int nt = (int)std::min<int64_t>((len + 64 * t.S - 1) / (64 * t.S), kPopTiles + 1);
+  // 4096: 85.5 against 82.2)
+  const int nt = tile_count(t, a);
   const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, GRAD) + 64 * sizeof(double));
-  if (!a.persist && a.split <= a.s_lo && nt >= 2 && nt <= kPopTiles && tile_lds <= 65536 &&
-      items * nt <= (GRAD ? 64 : 32) * (int64_t)(a.n_cu > 0 ? a.n_cu : 256)) {
+  if (!a.persist && a.split <= a.s_lo && tile_form<MODEL>(a, GRAD, items, nt, tile_lds, GRAD ? 64 : 32)) {
     switch (t.S) {
       case 8: fn = (const void*)pop_tile_kernel<MODEL, 8, GRAD>; break;
       case 16: fn = (const void*)pop_tile_kernel<MODEL, 16, GRAD>; break;
@@ -1681,13 +1703,11 @@ hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st)
   const size_t lds = pop_lds_bytes_per_wave(MODEL, a.k_max, false) * wpb;
   const int64_t ranks = launch_ranks(a), items = ranks * a.nch;
   if (items == 0) return hipSuccess;
-  const int64_t len = std::min(a.chunk_len, a.s_hi - a.s_lo);
-  const int nt = (int)std::min<int64_t>((len + 64 * t.S - 1) / (64 * t.S), kPopTiles + 1);
+  const int nt = tile_count(t, a);
   const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, false) + 256 * sizeof(double));
   // (48 waves per unit: 3000 pulse particles, T = 4096, 12000 waves: 49 us against
   // 33; 1000 at T = 16000, 16000 waves: 44 against 49)
-  if (nt >= 2 && nt <= kPopTiles && tile_lds <= 65536 &&
-      items * nt <= 48 * (int64_t)(a.n_cu > 0 ? a.n_cu : 256)) {
+  if (tile_form<MODEL>(a, false, items, nt, tile_lds, 48)) {
     const dim3 grid((unsigned)items), block(64 * nt);
     switch (t.S) {
       case 8: hipLaunchKernelGGL((delta_tile_kernel<MODEL, 8>), grid, block, tile_lds, st, a); break;
@@ -1710,6 +1730,11 @@ hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st)
 }
 
 }  // namespace
+
+int64_t lds_items(int model, int32_t k_max, bool grad) {
+  const int wpb = waves_per_block(model, k_max, grad);
+  return (int64_t)(kLdsPerCu / (wpb * pop_lds_bytes_per_wave(model, k_max, grad))) * wpb;
+}
 
 size_t pop_lds_bytes_per_wave(int model, int32_t k_max, bool grad) {
   const size_t per = const_bytes(model) + (grad ? 2 * (size_t)n_params(model) * 8 : 0);
