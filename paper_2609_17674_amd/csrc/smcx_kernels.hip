@@ -1358,6 +1358,10 @@ __global__ __launch_bounds__(64 * kPopTiles, (delta_waves_per_simd<MODEL, S>()))
                              __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lds);
 }
 
+// Combine the chunk sums of birth/death in chunk order, a thread per particle; a
+// long record has up to 64 chunks of pulses, 1024 of sinusoids, whose loads are
+// in flight eight at a time (50 pulse particles, T = 2^18, 64 chunks: 18 us one by
+// one; 3 sinusoid particles, 2^22 samples: 203).
 __global__ __launch_bounds__(256) void delta_finalize_kernel(PopArgs a) {
   const int64_t rank = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   Item it;
@@ -1366,6 +1370,7 @@ __global__ __launch_bounds__(256) void delta_finalize_kernel(PopArgs a) {
   if (a.active && !a.active[i]) return;
   if (!a.theta_birth && (!a.death_idx || a.death_idx[i] < 0)) return;  // settled by the main pass
   double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
   for (int c = 0; c < a.nch; ++c) {
     const double* src = a.part + ((size_t)c * a.N + i) * 4;
     for (int q = 0; q < 4; ++q) s[q] += src[q];
