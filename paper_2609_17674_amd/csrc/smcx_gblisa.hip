@@ -1091,15 +1091,21 @@ __device__ __forceinline__ void fd_run(const PopArgs& a, const FdTables& tabs, c
 // per wave) holds four; the likelihood alone gains from more (128 bins, 40000
 // particles, K on 0..10: 168 us at four, 159 at five, 154 at six), and more
 // waves still would leave few particles' latency exposed (eight: 41 us for 1000
-// particles, K on 0..16, against 35 at six and 33 at four).
+// particles, K on 0..16, against 35 at six and 33 at four). 0: the compiler's
+// choice, for two records (held to four the schedule loses more than a wave gains:
+// gradient of 1441 particles, K on 0..26, 151 us at four, 126 left alone;
+// birth/death over 200 bins 111, 98; 40000, K on 1..10: gradient 598, 553).
 template <int MODE, int NR, bool BRIDGE>
-constexpr int fd_occupancy() { return MODE == 0 && NR == 2 && !BRIDGE ? 6 : 4; }
+constexpr int fd_occupancy() {
+  return BRIDGE ? 0 : (MODE == 0 && NR == 2 ? 6 : 4);
+}
 
 // One particle per wave; the hardware hands the workgroups out in the K-sorted
 // order. (BRIDGE apart: the two sides' constants together spill.)
 template <int MODE, int NR, bool BRIDGE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    fd_occupancy<MODE, NR, BRIDGE>(), fd_occupancy<MODE, NR, BRIDGE>()))) void fd_kernel(PopArgs a, const double* __restrict__ src) {
+    fd_occupancy<MODE, NR, BRIDGE>() ? fd_occupancy<MODE, NR, BRIDGE>() : 1,
+    fd_occupancy<MODE, NR, BRIDGE>() ? fd_occupancy<MODE, NR, BRIDGE>() : 8))) void fd_kernel(PopArgs a, const double* __restrict__ src) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   FdTables tabs;
