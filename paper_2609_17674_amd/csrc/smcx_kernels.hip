@@ -1349,9 +1349,13 @@ __global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta
 }
 
 // Few work items, as pop_tile_kernel: 100 pulse particles, K on 0..20, T = 4096:
-// 38 -> 15 us; 1500: 48 -> 22; 64 sinusoid particles, T = 8000: 33 -> 14.
+// 38 -> 15 us; 1500: 48 -> 22; 64 sinusoid particles, T = 8000: 33 -> 14. Up to
+// kDeltaTiles tiles, the default chunk of the longest pulse records (20 pulse
+// particles, T = 590147, K on 0..20: 107 -> 39 us).
+constexpr int kDeltaTiles = 8;
+
 template <int MODEL, int S>
-__global__ __launch_bounds__(64 * kPopTiles, (delta_waves_per_simd<MODEL, S>())) void delta_tile_kernel(
+__global__ __launch_bounds__(64 * kDeltaTiles, (delta_waves_per_simd<MODEL, S>())) void delta_tile_kernel(
     PopArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   delta_item<MODEL, S, true>(a, blockIdx.x, threadIdx.x & 63,
@@ -1614,10 +1618,11 @@ int waves_per_block(int model, int32_t k_max, bool grad) {
   return w;
 }
 
-// Tiles of a call's longest chunk (more than kPopTiles count as one more).
-int tile_count(const Tiling& t, const PopArgs& a) {
+// Tiles of a call's longest chunk (more than `most` count as none).
+int tile_count(const Tiling& t, const PopArgs& a, int most) {
   const int64_t len = std::min(a.chunk_len, a.s_hi - a.s_lo);
-  return (int)std::min<int64_t>((len + 64 * t.S - 1) / (64 * t.S), kPopTiles + 1);
+  const int64_t nt = (len + 64 * t.S - 1) / (64 * t.S);
+  return nt <= most ? (int)nt : 0;
 }
 
 // Whether a workgroup takes an item with a wave per tile. Every wave keeps the
@@ -1632,7 +1637,7 @@ int tile_count(const Tiling& t, const PopArgs& a) {
 template <int MODEL>
 bool tile_form(const PopArgs& a, bool grad, int64_t items, int nt, size_t tile_lds, int64_t waves_per_cu) {
   const int64_t n_cu = a.n_cu > 0 ? a.n_cu : 256;
-  if (nt < 2 || nt > kPopTiles || items * nt > waves_per_cu * n_cu) return false;
+  if (nt < 2 || items * nt > waves_per_cu * n_cu) return false;
   if (tile_lds > 65536) return items <= (int64_t)(kLdsPerCu / tile_lds) * n_cu;
   return 2 * items <= 3 * lds_items(MODEL, a.k_max, grad) * n_cu;
 }
@@ -1673,7 +1678,7 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   // pulse particles, K on 0..5, T = 3000: 19.0 us against 19.6), and for the
   // gradient, whose items are longer, up to twice that (8000, K on 0..20, T =
   // 4096: 85.5 against 82.2)
-  const int nt = tile_count(t, a);
+  const int nt = tile_count(t, a, kPopTiles);
   const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, GRAD) + 64 * sizeof(double));
   if (!a.persist && a.split <= a.s_lo && tile_form<MODEL>(a, GRAD, items, nt, tile_lds, GRAD ? 64 : 32)) {
     switch (t.S) {
@@ -1708,11 +1713,13 @@ hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st)
   const size_t lds = pop_lds_bytes_per_wave(MODEL, a.k_max, false) * wpb;
   const int64_t ranks = launch_ranks(a), items = ranks * a.nch;
   if (items == 0) return hipSuccess;
-  const int nt = tile_count(t, a);
+  const int nt = tile_count(t, a, kDeltaTiles);
   const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, false) + 256 * sizeof(double));
   // (48 waves per unit: 3000 pulse particles, T = 4096, 12000 waves: 49 us against
-  // 33; 1000 at T = 16000, 16000 waves: 44 against 49)
-  if (tile_form<MODEL>(a, false, items, nt, tile_lds, 48)) {
+  // 33; 1000 at T = 16000, 16000 waves: 44 against 49; the items of four tiles
+  // also where there are more, 12 per unit: 40 at T = 590147, 11.4 per unit, 58
+  // against 108; 2000 at T = 8000 in chunks of 6144, 15.6 per unit, 47 against 34)
+  if (tile_form<MODEL>(a, false, items, nt, tile_lds, nt > kPopTiles ? 12 * nt : 48)) {
     const dim3 grid((unsigned)items), block(64 * nt);
     switch (t.S) {
       case 8: hipLaunchKernelGGL((delta_tile_kernel<MODEL, 8>), grid, block, tile_lds, st, a); break;
