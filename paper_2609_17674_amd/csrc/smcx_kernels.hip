@@ -1180,29 +1180,32 @@ __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
 // over the block groups of its truncation support, as in the likelihood
 // passes: beyond it the template is below 2^-64 of its peak, which neither an
 // FP32 residual nor the FP64 sums can show (the sums of the candidate's own
-// template are skipped there too). The candidates' templates are formed again
+// template are skipped there too). A pulse's death candidate is formed again
 // for the inner products instead of held through the pass, which leaves
-// registers for seven waves per SIMD (pulses) instead of four. VALU issue
-// bounds it: 8192 pulse particles, K on 0..20, T = 4096, birth and death:
-// 102 -> 59 us; 500 sinusoid particles, K on 0..30, T = 2^17: 322 -> 286 us.
+// registers for seven waves per SIMD instead of four; a sinusoid's, whose
+// waves gain nothing from a fifth, is held (20000 particles, K on 1..2,
+// T = 8192: 228 us formed again, 192 held). VALU issue bounds it, birth and
+// death: 8192 pulse particles, K on 0..20, T = 4096: 102 -> 59 us; 500 sinusoid
+// particles, K on 0..20, T = 2^17: 241 -> 215 us.
 // (An unbranched path for tiles inside the support spills; four block groups
 // at a time instead of two is three times slower.)
 
-// Adds one candidate's <r, h> and <h, h> over the tile to the lane's sums.
-template <int MODEL, int S, bool LIN>
-__device__ __forceinline__ void delta_sums(const PopArgs& a, const typename Model<MODEL>::C& c,
-                                           int64_t tile, int lane, int64_t ce, bool split, double bw,
-                                           const float (&r)[S], double& x, double& y) {
+// Adds one candidate's <r, h> and <h, h> over the tile to the lane's sums;
+// values(fn) calls fn(j, h) for the values of its template.
+template <int S, class V>
+__device__ __forceinline__ void delta_sums(const PopArgs& a, V values, int64_t tile, int lane,
+                                           int64_t ce, bool split, double bw, const float (&r)[S],
+                                           double& x, double& y) {
   const int nv = (int)min(ce - tile, (int64_t)(64 * S)) - lane;
   if (!split) {
-    Model<MODEL>::template values<S, LIN>(c, tile, lane, [&](auto j, float h) {
+    values([&](auto j, float h) {
       const bool ok = 64 * j < nv;
       const double r1 = ok ? (double)r[j] : 0.0, h1 = ok ? (double)h : 0.0;
       x = fma(r1, h1, x);
       y = fma(h1, h1, y);
     });
   } else {  // per-sample weight: 1 before the split, beta after (products of floats are exact)
-    Model<MODEL>::template values<S, LIN>(c, tile, lane, [&](auto j, float h) {
+    values([&](auto j, float h) {
       const bool ok = 64 * j < nv;
       const double r1 = ok ? (double)r[j] : 0.0, h1 = ok ? (double)h : 0.0;
       const double ws = tile + 64 * j + lane < a.split ? 1.0 : bw;
@@ -1221,6 +1224,7 @@ __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MOD
                                             int64_t ce, bool split, double bw, double& xb,
                                             double& yb, double& xd, double& yd) {
   using M = Model<MODEL>;
+  constexpr bool kHold = MODEL == SMCX_GBSINE;  // keep the death candidate's template
   const int shared = j_death < 0 ? K : j_death;  // components the two residuals share
   for (int64_t tile = cs; tile < ce; tile += 64 * S) {
     float rf[S], rn[S];
@@ -1233,19 +1237,40 @@ __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MOD
     if (j_death >= 0) {
 #pragma unroll
       for (int jj = 0; jj < S; ++jj) rn[jj] = rf[jj];
-      if (birth) {
+      [[maybe_unused]] float hj[S];
+      if constexpr (kHold) {
+        const typename M::C c = cst[j_death];
+        M::template each<S, LIN>(c, tile, lane, [&](auto j, float e) {
+          hj[j] = c.A * e;
+          rf[j] = __builtin_fmaf(-c.A, e, rf[j]);
+        });
+      } else if (birth) {
         M::template sub1<S, LIN>(cst[j_death], tile, lane, rf);
+      }
+      if (birth) {
         for (int k = j_death + 1; k < K; ++k) M::template sub2<S, LIN>(cst[k], tile, lane, rf, rn);
       } else {
         for (int k = j_death + 1; k < K; ++k) M::template sub1<S, LIN>(cst[k], tile, lane, rn);
       }
-      delta_sums<MODEL, S, LIN>(a, cst[j_death], tile, lane, ce, split, bw, rn, tx, ty);
+      delta_sums<S>(
+          a,
+          [&](auto fn) {
+            if constexpr (kHold) {
+#pragma unroll
+              for (int jj = 0; jj < S; ++jj) fn(jj, hj[jj]);
+            } else {
+              M::template values<S, LIN>(cst[j_death], tile, lane, fn);
+            }
+          },
+          tile, lane, ce, split, bw, rn, tx, ty);
       xd += tx;
       yd += ty;
     }
     if (birth) {
       tx = ty = 0.0;
-      delta_sums<MODEL, S, LIN>(a, cst[K], tile, lane, ce, split, bw, rf, tx, ty);
+      delta_sums<S>(
+          a, [&](auto fn) { M::template values<S, LIN>(cst[K], tile, lane, fn); }, tile, lane, ce,
+          split, bw, rf, tx, ty);
       xb += tx;
       yb += ty;
     }
@@ -1254,7 +1279,7 @@ __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MOD
 
 template <int MODEL, int S>
 constexpr int delta_waves_per_simd() {  // what the registers allow without spills
-  return S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 5);
+  return S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 4);
 }
 
 // One birth/death work item; TILES as pop_item.
