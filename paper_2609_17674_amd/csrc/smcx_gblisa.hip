@@ -1898,10 +1898,23 @@ hipError_t launch_src_pass(const PopArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Particles up to which a launch gives each a workgroup: one wave per SIMD (1000
+// Whether a launch gives each particle a workgroup: up to one wave per SIMD (1000
 // particles, K on 0..10: gradient 35 against 27 us, likelihood 24 / 21,
-// birth/death 26 / 25; 2000: 38 / 44, 25 / 31, 28 / 41).
-int64_t fd_split_max(const PopArgs& a) { return 4 * (int64_t)(a.n_cu > 0 ? a.n_cu : 256); }
+// birth/death 26 / 25; 2000: 38 / 44, 25 / 31, 28 / 41). Half of those workgroups are
+// resident at once, and the second round costs more than it gives where no
+// particle keeps a wave of its own much longer than the others do: all of about
+// one K, up to six (1024 bridged particles, K = 1: gradient 17 against 28 us, birth/death
+// 22 / 33; K = 5: 34 / 43, 30 / 42), for birth/death up to 16 (11: 42 / 52; 20, over more
+// than 128 bins: 80 / 77), for the gradient over more than 128 bins up to three (4:
+// 34 / 30 of 600); and of 800 or more, K of three at most.
+template <int MODE>
+bool fd_split(const PopArgs& a, bool nr2) {
+  const int64_t n_cu = a.n_cu > 0 ? a.n_cu : 256;
+  if (a.N <= 2 * n_cu || a.N > 4 * n_cu) return a.N <= 2 * n_cu;
+  const int k_alike = MODE == 2 ? 16 : (MODE == 1 && !nr2 ? 3 : 6);
+  const bool alike = 5 * a.M >= 4 * a.N * a.k_max && a.M <= k_alike * a.N;
+  return !alike && (a.k_max > 3 || a.N <= 3 * n_cu);
+}
 
 template <int MODE>
 hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
@@ -1918,7 +1931,7 @@ hipError_t launch_fd_mode(const PopArgs& a, hipStream_t st) {
   // LDS bytes: the tables, and for the gradient a residual copy per wave
   const size_t lds2 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<2>() : 0);
   const size_t lds4 = 8 * fd_lds_words(br, 4, MODE == 1 ? resid_words<4>() : 0);
-  if (a.N <= fd_split_max(a)) {
+  if (fd_split<MODE>(a, nr2)) {
     const size_t s2 = 8 * fd_lds_words(br, 1, resid_words<2>() + 4 * 4 * kNs);
     const size_t s4 = 8 * fd_lds_words(br, 1, resid_words<4>() + 4 * 4 * kNs);
     const dim3 each((unsigned)launch_ranks(a));
