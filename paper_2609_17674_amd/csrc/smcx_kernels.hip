@@ -228,7 +228,11 @@ __device__ __forceinline__ GbC gb_make(const double* th, double t_start, double 
   const double pmax = fabs(a0) + fabs(r.a1) * sh + fabs(r.a2) * sh * sh;
   const double chirp = fabs(4096.0 * r.a2) * (double)S * S;
   if (!(pmax < 524287.0 && chirp < 0.015625)) {
-    if (pmax == pmax && chirp == chirp) atomicOr(flag, kFlagPhase);
+    // every wave of every chunk and tile comes here with the same component: once
+    // the bit is up it is only read (many atomics on one word take turns)
+    if (pmax == pmax && chirp == chirp &&
+        !(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFlagPhase))
+      atomicOr(flag, kFlagPhase);
     r.A = __builtin_nanf("");
   }
   return r;
