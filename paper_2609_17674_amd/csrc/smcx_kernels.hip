@@ -1153,6 +1153,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
   const double outer = a.split > a.s_lo ? 1.0 : (a.beta ? a.beta[i] : 1.0);
   if (lane == 0 && a.logl) {
     double ss = 0.0;
+#pragma unroll 8
     for (int c = 0; c < a.nch; ++c) ss += a.part[(size_t)c * a.N + i];
     a.logl[i] = outer * (-0.5 * ss * a.inv_sigma2);
   }
@@ -1160,6 +1161,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
   for (int k = lane; k < K; k += 64) {
     double sums[P];
     for (int p = 0; p < P; ++p) sums[p] = 0.0;
+#pragma unroll 8
     for (int c = 0; c < a.nch; ++c) {
       const double* src = a.part_g + ((size_t)c * a.m_max + m0 + k) * P;
       for (int p = 0; p < P; ++p) sums[p] += src[p];
