@@ -1311,7 +1311,10 @@ hipError_t launch_metric(int model, int P, int64_t N, int64_t M, int64_t T, doub
     // T = 500: 54, 58, T = 1000: 73, 65; 1024, T = 4096: 140, 115, left with the
     // coordinate form. Sinusoids, K on 0..8: 4096, T = 500: 57, 74, T = 1500:
     // 125, 104), or on more than two windows (256 pulse particles, T = 16384: 264,
-    // 131).
+    // 131). Its flush into whole matrices costs as much as 100 samples or more,
+    // twice that where the particles fill the coordinate form's blocks (dense, 40000
+    // sinusoid particles, T = 138, K on 1..8, 18 of 32 coordinates: 142, 190;
+    // T = 250: 215, 209; K on 0..10, 20 of 64, T = 138: 223, 197; 30000, T = 100: 0.96).
     // Beyond 64 coordinates the compiler rounds some of the coordinate
     // form's products to FP32 before FP16 and others once, depending on the
     // block; the grouped form would change F by 2e-7 there (below it gives the
@@ -1319,7 +1322,9 @@ hipError_t launch_metric(int model, int P, int64_t N, int64_t M, int64_t T, doub
     const int64_t windows = (split + kFlushSamples - 1) / kFlushSamples +
                             (T - split + kFlushSamples - 1) / kFlushSamples;
     const int64_t waves = 16 * (int64_t)n_cu, products = N * (nb * (nb + 1) / 2);  // per sample
-    if (nb <= 2 && (windows > 2 || (N * nb >= waves && products * T >= 1024 * waves)))
+    const int64_t t_dense = 5 * M * P > 64 * nb * N ? 224 : 120;  // above or below 0.4 filled
+    if (nb <= 2 && (windows > 2 || (N * nb >= waves && products * T >= 1024 * waves &&
+                                    (blocks || T >= t_dense))))
       return model == SMCX_PULSE ? launch_groups<SMCX_PULSE>(a, windows, st)
                                  : launch_groups<SMCX_GBSINE>(a, windows, st);
   }
