@@ -1283,13 +1283,64 @@ __device__ __forceinline__ void delta_tiles(const PopArgs& a, typename Model<MOD
   }
 }
 
+// Components whose constants a birth/death wave of pulses holds in the LDS at once in
+// the LONG kernels, whose particles mostly have fewer: room for k_max of them keeps
+// the waves away where it is not needed (k_max = 512, 16 KB a wave: 15161 particles, K
+// on 1..3, T = 7146: 234 us, 137 with this; 4699, K on 2..5, T = 65212: 628, 386).
+constexpr int kDeltaBatch = 127;
+
+// The tiles of a particle with more components: their constants batch by batch, for
+// each tile again, and the operations of delta_tiles in their order.
 template <int MODEL, int S>
+__device__ __forceinline__ void delta_tiles_long(const PopArgs& a, typename Model<MODEL>::C* cst, int64_t m0,
+                                              int i, int K, int j_death, bool birth, int lane, int64_t cs,
+                                              int64_t ce, bool split, double bw, double& xb, double& yb,
+                                              double& xd, double& yd) {
+  using M = Model<MODEL>;
+  constexpr int P = M::P;
+  auto sums = [&](const double* th, int64_t tile, const float (&r)[S], double& x, double& y) {
+    wave_sync();
+    if (lane == 0) cst[0] = M::make(th, a, S);
+    wave_sync();
+    M::template prepare<S>(cst, 1, tile, lane);
+    double tx = 0.0, ty = 0.0;
+    delta_sums<S>(
+        a, [&](auto fn) { M::template values<S, true>(cst[0], tile, lane, fn); }, tile, lane, ce, split,
+        bw, r, tx, ty);
+    x += tx;
+    y += ty;
+  };
+  for (int64_t tile = cs; tile < ce; tile += 64 * S) {
+    float rf[S], rn[S];
+    const float* dp = a.d32 + tile + lane;
+#pragma unroll
+    for (int jj = 0; jj < S; ++jj) rf[jj] = rn[jj] = dp[64 * jj];
+    for (int b0 = 0; b0 < K; b0 += kDeltaBatch) {
+      const int n = min(kDeltaBatch, K - b0);
+      wave_sync();  // the constants before have been read
+      for (int k = lane; k < n; k += 64) cst[k] = M::make(a.theta + (m0 + b0 + k) * P, a, S);
+      wave_sync();
+      M::template prepare<S>(cst, n, tile, lane);
+      for (int k = 0; k < n; ++k) {
+        if (b0 + k == j_death) {
+          M::template sub1<S, true>(cst[k], tile, lane, rf);
+        } else {
+          M::template sub2<S, true>(cst[k], tile, lane, rf, rn);
+        }
+      }
+    }
+    if (j_death >= 0) sums(a.theta + (m0 + j_death) * P, tile, rn, xd, yd);
+    if (birth) sums(a.theta_birth + (int64_t)i * P, tile, rf, xb, yb);
+  }
+}
+
+template <int MODEL, int S, bool LONG>
 constexpr int delta_waves_per_simd() {  // what the registers allow without spills
-  return S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 4);
+  return LONG ? (S <= 8 ? 7 : 5) : S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 4);
 }
 
 // One birth/death work item; TILES as pop_item.
-template <int MODEL, int S, bool TILES>
+template <int MODEL, int S, bool TILES, bool LONG>
 __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int lane, int wid,
                                            unsigned char* lds) {
   using M = Model<MODEL>;
@@ -1310,10 +1361,14 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
     return;
   }
 
-  C* cst = reinterpret_cast<C*>(lds + (size_t)wid * lds_wave_bytes(MODEL, a.k_max, false));
-  for (int k = lane; k < K; k += 64) cst[k] = M::make(a.theta + (m0 + k) * P, a, S);
-  if (birth && lane == 0) cst[K] = M::make(a.theta_birth + (int64_t)i * P, a, S);
-  wave_sync();
+  const size_t wave_bytes = lds_wave_bytes(MODEL, LONG ? kDeltaBatch : a.k_max, false);
+  C* cst = reinterpret_cast<C*>(lds + (size_t)wid * wave_bytes);
+  const bool batches = LONG && K > kDeltaBatch;
+  if (!batches) {
+    for (int k = lane; k < K; k += 64) cst[k] = M::make(a.theta + (m0 + k) * P, a, S);
+    if (birth && lane == 0) cst[K] = M::make(a.theta_birth + (int64_t)i * P, a, S);
+    wave_sync();
+  }
 
   int64_t cs = a.s_lo + (int64_t)c * a.chunk_len;
   int64_t ce = min(cs + a.chunk_len, a.s_hi);
@@ -1327,11 +1382,16 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
   // sinusoids take the exact tile phase here, whatever the components: the
   // templates of a birth and of the matching death must not depend on which
   // other components (or candidates) the two calls see
-  delta_tiles<MODEL, S, MODEL != SMCX_GBSINE>(a, cst, K, j_death, birth, lane, cs, ce, split, bw,
-                                              xb, yb, xd, yd);
+  if constexpr (LONG) {
+    if (batches)
+      delta_tiles_long<MODEL, S>(a, cst, m0, i, K, j_death, birth, lane, cs, ce, split, bw, xb, yb, xd, yd);
+  }
+  if (!batches)
+    delta_tiles<MODEL, S, MODEL != SMCX_GBSINE>(a, cst, K, j_death, birth, lane, cs, ce, split, bw,
+                                                xb, yb, xd, yd);
   if constexpr (TILES) {
     const int nw = blockDim.x >> 6;
-    double* sums = reinterpret_cast<double*>(lds + nw * lds_wave_bytes(MODEL, a.k_max, false));  // [nw][4][64]
+    double* sums = reinterpret_cast<double*>(lds + nw * wave_bytes);  // [nw][4][64]
     if (wid > 0) {
       double* mine = sums + wid * 256 + lane;
       mine[0] = xb;
@@ -1372,11 +1432,11 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
   }
 }
 
-template <int MODEL, int S>
-__global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta_kernel(PopArgs a) {
+template <int MODEL, int S, bool LONG>
+__global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S, LONG>())) void delta_kernel(PopArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  delta_item<MODEL, S, false>(a, (int64_t)blockIdx.x * (blockDim.x >> 6) + wid, threadIdx.x & 63, wid, lds);
+  delta_item<MODEL, S, false, LONG>(a, (int64_t)blockIdx.x * (blockDim.x >> 6) + wid, threadIdx.x & 63, wid, lds);
 }
 
 // Few work items, as pop_tile_kernel: 100 pulse particles, K on 0..20, T = 4096:
@@ -1385,11 +1445,11 @@ __global__ __launch_bounds__(256, (delta_waves_per_simd<MODEL, S>())) void delta
 // particles, T = 590147, K on 0..20: 107 -> 39 us).
 constexpr int kDeltaTiles = 8;
 
-template <int MODEL, int S>
-__global__ __launch_bounds__(64 * kDeltaTiles, (delta_waves_per_simd<MODEL, S>())) void delta_tile_kernel(
+template <int MODEL, int S, bool LONG>
+__global__ __launch_bounds__(64 * kDeltaTiles, (delta_waves_per_simd<MODEL, S, LONG>())) void delta_tile_kernel(
     PopArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  delta_item<MODEL, S, true>(a, blockIdx.x, threadIdx.x & 63,
+  delta_item<MODEL, S, true, LONG>(a, blockIdx.x, threadIdx.x & 63,
                              __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lds);
 }
 
@@ -1666,11 +1726,12 @@ int tile_count(const Tiling& t, const PopArgs& a, int most) {
 // KiB only where each has its place (300 pulse particles, T = 4096, k_max = 512,
 // birth/death: 41.5, 18).
 template <int MODEL>
-bool tile_form(const PopArgs& a, bool grad, int64_t items, int nt, size_t tile_lds, int64_t waves_per_cu) {
+bool tile_form(const PopArgs& a, int32_t k_max, bool grad, int64_t items, int nt, size_t tile_lds,
+               int64_t waves_per_cu) {
   const int64_t n_cu = a.n_cu > 0 ? a.n_cu : 256;
   if (nt < 2 || items * nt > waves_per_cu * n_cu) return false;
   if (tile_lds > 65536) return items <= (int64_t)(kLdsPerCu / tile_lds) * n_cu;
-  return 2 * items <= 3 * lds_items(MODEL, a.k_max, grad) * n_cu;
+  return 2 * items <= 3 * lds_items(MODEL, k_max, grad) * n_cu;
 }
 
 template <int MODEL, int S, bool GRAD>
@@ -1711,7 +1772,7 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   // 4096: 85.5 against 82.2)
   const int nt = tile_count(t, a, kPopTiles);
   const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, GRAD) + 64 * sizeof(double));
-  if (!a.persist && a.split <= a.s_lo && tile_form<MODEL>(a, GRAD, items, nt, tile_lds, GRAD ? 64 : 32)) {
+  if (!a.persist && a.split <= a.s_lo && tile_form<MODEL>(a, a.k_max, GRAD, items, nt, tile_lds, GRAD ? 64 : 32)) {
     switch (t.S) {
       case 8: fn = (const void*)pop_tile_kernel<MODEL, 8, GRAD>; break;
       case 16: fn = (const void*)pop_tile_kernel<MODEL, 16, GRAD>; break;
@@ -1738,34 +1799,47 @@ hipError_t launch_pop_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
   return launch_pop_fn<MODEL, GRAD>(fn, blocks, 64 * wpb, lds, ranks, a, st);
 }
 
+template <int MODEL, int S>
+const void* delta_fn(bool tiles, bool lng) {
+  if constexpr (MODEL == SMCX_PULSE) {
+    if (lng)
+      return tiles ? (const void*)delta_tile_kernel<MODEL, S, true> : (const void*)delta_kernel<MODEL, S, true>;
+  }
+  return tiles ? (const void*)delta_tile_kernel<MODEL, S, false> : (const void*)delta_kernel<MODEL, S, false>;
+}
+
 template <int MODEL>
 hipError_t launch_delta_model(const Tiling& t, const PopArgs& a, hipStream_t st) {
-  const int wpb = waves_per_block(MODEL, a.k_max, false);
-  const size_t lds = pop_lds_bytes_per_wave(MODEL, a.k_max, false) * wpb;
+  const int nt = tile_count(t, a, kDeltaTiles);
+  // batches of constants: where all k_max of them would fill the LDS (k_max = 200,
+  // 15062 particles, K on 0..2, T = 29898: 329 us, 353 in batches, whose waves have
+  // more registers; 254: 399, 353; few items in workgroups of more tiles, 10 at
+  // T = 5e5, 128: 24, 26; 200: 82, 26), and few particles have more than a batch (100
+  // of 128 to 200 components: 102, 141)
+  const bool lng = MODEL == SMCX_PULSE && a.k_max > (nt > kPopTiles ? 160 : 224) &&
+                   a.M <= kDeltaBatch / 2 * a.N;
+  const int32_t k_lds = lng ? kDeltaBatch : a.k_max;
+  const int wpb = waves_per_block(MODEL, k_lds, false);
+  const size_t per = pop_lds_bytes_per_wave(MODEL, k_lds, false);
   const int64_t ranks = launch_ranks(a), items = ranks * a.nch;
   if (items == 0) return hipSuccess;
-  const int nt = tile_count(t, a, kDeltaTiles);
-  const size_t tile_lds = nt * (pop_lds_bytes_per_wave(MODEL, a.k_max, false) + 256 * sizeof(double));
+  const size_t tile_lds = nt * (per + 256 * sizeof(double));
   // (48 waves per unit: 3000 pulse particles, T = 4096, 12000 waves: 49 us against
   // 33; 1000 at T = 16000, 16000 waves: 44 against 49; the items of four tiles
   // also where there are more, 12 per unit: 40 at T = 590147, 11.4 per unit, 58
   // against 108; 2000 at T = 8000 in chunks of 6144, 15.6 per unit, 47 against 34)
-  if (tile_form<MODEL>(a, false, items, nt, tile_lds, nt > kPopTiles ? 12 * nt : 48)) {
-    const dim3 grid((unsigned)items), block(64 * nt);
-    switch (t.S) {
-      case 8: hipLaunchKernelGGL((delta_tile_kernel<MODEL, 8>), grid, block, tile_lds, st, a); break;
-      case 16: hipLaunchKernelGGL((delta_tile_kernel<MODEL, 16>), grid, block, tile_lds, st, a); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    const dim3 grid((unsigned)((items + wpb - 1) / wpb)), block(64 * wpb);
-    switch (t.S) {
-      case 8: hipLaunchKernelGGL((delta_kernel<MODEL, 8>), grid, block, lds, st, a); break;
-      case 16: hipLaunchKernelGGL((delta_kernel<MODEL, 16>), grid, block, lds, st, a); break;
-      default: return hipErrorInvalidValue;
-    }
+  const bool tiles =
+      tile_form<MODEL>(a, k_lds, false, items, nt, tile_lds, nt > kPopTiles ? 12 * nt : 48);
+  const void* fn;
+  switch (t.S) {
+    case 8: fn = delta_fn<MODEL, 8>(tiles, lng); break;
+    case 16: fn = delta_fn<MODEL, 16>(tiles, lng); break;
+    default: return hipErrorInvalidValue;
   }
-  hipError_t e = hipGetLastError();
+  void* args[] = {const_cast<PopArgs*>(&a)};
+  hipError_t e = hipLaunchKernel(fn, dim3((unsigned)(tiles ? items : (items + wpb - 1) / wpb)),
+                                 dim3(64 * (tiles ? nt : wpb)), args, tiles ? tile_lds : per * wpb, st);
+  if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess || a.nch == 1) return e;
   hipLaunchKernelGGL(delta_finalize_kernel, dim3((unsigned)((ranks + 255) / 256)), dim3(256), 0, st,
                      a);
