@@ -330,8 +330,9 @@ int smcx_plain_logl_grad(smcx_problem* prob, int64_t N, const int64_t* offsets_h
  *   q_out, p_out, g_out  [M][P] FP64 state after the step (must not overlap
  *              the inputs); logl_out [N] tempered logL at q'
  * Other arguments as logl_grad_batch. Capture-safe: two kernel launches (the
- * drift shares the ordering pass's, where there is one) and the combination of
- * long records' chunks, no allocation, no host synchronisation. */
+ * drift shares the ordering pass's, where there is one), in the frequency domain
+ * three (the source rows at q' by themselves), and the combination of long
+ * records' chunks, no allocation, no host synchronisation. */
 int smcx_leapfrog(smcx_problem* prob, int64_t N, const int64_t* offsets, int64_t M,
                   const double* beta, double eps, const int8_t* dir, const uint8_t* active,
                   const double* q_in, const double* p_in, const double* g_in, double* q_out,
@@ -346,16 +347,17 @@ int smcx_leapfrog(smcx_problem* prob, int64_t N, const int64_t* offsets, int64_t
 int smcx_nuts_reserve(smcx_problem* prob, int32_t max_depth);
 
 /* One No-U-Turn transition (Sec. "No-U-Turn-Sampler") for every particle,
- * all trajectories built on the device, in lockstep (multinomial NUTS,
- * generalised U-turn criterion on every balanced sub-block and on the whole
- * trajectory, divergence when the energy rises by more than 1000 or a
- * position leaves the prior box, tree depth <= max_depth, identity metric;
+ * all trajectories built on the device (multinomial NUTS, generalised U-turn
+ * criterion on every balanced sub-block and on the whole trajectory,
+ * divergence when the energy rises by more than 1000 or a position leaves the
+ * prior box, tree depth <= max_depth, identity metric;
  * smcx_nuts_transition_metric below takes a dense mass matrix).
- * Each doubling of depth j runs 2^j batched leapfrog steps (smcx_leapfrog's
- * arithmetic) each followed by a controller pass, and is captured once into
- * a hipGraph and replayed when use_graph != 0 (the graph is rebuilt when any
- * pointer or size argument changes). The host synchronises once per
- * doubling to learn whether any trajectory is still growing.
+ * In the time domain all trajectories go in lockstep: each doubling of depth j
+ * runs 2^j batched leapfrog steps (smcx_leapfrog's arithmetic) each followed
+ * by a controller pass, and is captured once into a hipGraph and replayed when
+ * use_graph != 0 (the graph is rebuilt when any pointer or size argument
+ * changes). The host synchronises once per doubling to learn whether any
+ * trajectory is still growing.
  * Frequency-domain problems run every trajectory on its own in one launch:
  * no graph (use_graph makes no difference) and no host synchronisation.
  *   beta, eps          tempering and leapfrog step size (eps > 0)
@@ -513,14 +515,17 @@ int smcx_gauss_newton_metric_masked(smcx_problem* prob, int64_t N, const int64_t
  * triangle of each F block is read; W may equal F (in place). A block that
  * is not numerically positive definite (a pivot <= 0 or NaN) is written as
  * NaN and raises a device flag; offsets that disagree with (K_i P)^2 or
- * blocks beyond f_size skip the particle and raise a flag. One workgroup per
- * particle keeps its triangle in LDS: needs k_max P <= 128 and
+ * blocks beyond f_size skip the particle and raise a flag. One wave per
+ * particle: whole matrices of handles with k_max P <= 64 are kept in registers,
+ * larger ones and block mode as a triangle in LDS. Needs k_max P <= 128 and
  * (k_max P)(k_max P + 1)/2 doubles of LDS per workgroup (SMCX_EINVAL
- * otherwise). block = 0 factors the whole matrix; block = b (dividing P)
+ * otherwise). The two forms add in different orders: W's last bits depend on
+ * which one the handle's k_max selects, and on nothing else of the call.
+ * block = 0 factors the whole matrix; block = b (dividing P)
  * factors its block-diagonal part in b x b blocks and writes zeros between
  * them -- exact when F is block-diagonal, as the frequency-domain model's
  * per-source metric is with b = 8 -- using b (b + 1)/2 doubles of LDS.
- * Capture-safe: one launch, no allocation. */
+ * Capture-safe: one launch, no allocation; the handle's workspace is not used. */
 int smcx_metric_factor(smcx_problem* prob, int64_t N, const int64_t* offsets, int64_t M,
                        const int64_t* f_offsets, int64_t f_size, const double* F,
                        const double* ridge, int32_t block, double* W, void* hip_stream);

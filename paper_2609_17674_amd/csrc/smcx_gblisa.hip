@@ -136,8 +136,8 @@ struct Src {
 };
 
 // Source constants, one row of kSrcWords doubles per row of theta, written
-// by fd_src_kernel before each frequency-domain launch (one thread per
-// source) and read by the kernels at wave-uniform addresses through a
+// before each frequency-domain launch (with the ordering pass or by
+// fd_src_kernel, one lane per source) and read by the kernels at wave-uniform addresses through a
 // restrict-qualified pointer, so they arrive by scalar loads into scalar
 // registers instead of occupying vector registers in every lane. Words 0-32
 // hold the constants with the carrier bin q of the handle's record, word 33
@@ -1848,9 +1848,9 @@ __global__ __launch_bounds__(kPrepBlock) void fd_prep_kernel(PrepArgs p, int64_t
 constexpr int kSrcGroup = 16;
 
 __global__ __launch_bounds__(256) void fd_src_kernel(PopArgs a, double T2) {
-  // The rows of a group's particle are contiguous ([K][34] doubles): each
+  // The rows of a group's particle are contiguous ([K][46] doubles): each
   // lane builds its source's row in registers, and the group writes the
-  // rows out through LDS in two halves of 17 words, so that a store of the
+  // rows out through LDS in two halves of 23 words, so that a store of the
   // group covers 128 consecutive bytes instead of one word of each of 16
   // rows. The group's lanes are in one wave, whose LDS accesses complete in
   // order.
