@@ -99,13 +99,15 @@ Tiling smcx::default_tiling(int model, int kind, int64_t T) {
       // birth/death: short chunks on long records, where a wave's serial pass
       // over its components and tiles is what few particles wait for (4000 at
       // T = 16000: 199 us with chunks of 8192, 121 with 2048), but about 64 of
-      // them until a chunk has 8192 samples, and none split up to
-      // 4096 samples, whose four tiles few particles spread over waves anyhow
-      // and where the combine launch costs more (8192 particles: 66 us whole,
-      // 71 split). Chunks that grow on with the record leave few particles too
+      // them until a chunk has 8192 samples, and none split up to 5120 samples,
+      // whose tiles few particles spread over waves anyhow and where many pay
+      // more for the chunks than they gain (K on 0..20, whole against 2048: T =
+      // 5000, 300 particles: 15 us, 20, 2000: 32, 35, 4000: 58, 54, 8192:
+      // 76, 89, 20000: 157, 189; T = 7000, 2000: 43, 41, 4000: 79, 62, 20000:
+      // 215, 240). Chunks that grow on with the record leave few particles too
       // few waves (3 particles, K on 0..20, T = 2^22: 64 chunks 644 us, 512 165)
       const int64_t len = std::min<int64_t>(8192, std::max<int64_t>(2048, (T + 63) / 64));
-      t.chunk_len = round_up(T <= 4096 ? T : len, tile);
+      t.chunk_len = round_up(T <= 5120 ? T : len, tile);
     } else {
       t.chunk_len = T <= 8192 ? round_up(T, tile) : round_up(8192, tile);
     }
