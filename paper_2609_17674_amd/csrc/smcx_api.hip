@@ -265,6 +265,7 @@ smcx::PopArgs base_args(smcx_problem* p, int64_t N, const int64_t* offsets, int6
   a.strict = t.strict;
   a.persist = t.sorted == 2;
   a.n_cu = p->n_cu;
+  a.odd_data = !(p->prefix.back() < 1e76);  // FP32 ends at 3.4e38
   a.n_ranks = smcx::prep_ranks(N);
   a.nch = t.nch;
   a.chunk_len = t.chunk_len;

@@ -111,6 +111,7 @@ struct PopArgs {
   int n_cu;                // compute units of the device (grid sizes)
   int persist;             // 1: the population kernel's grid holds what the device runs
                            // at once and each wave steps through the work items
+  int odd_data;            // 1: the data hold values that FP32 does not (NaN, infinities)
   int fd_src_ready;        // 1: the caller has written fd_src for this launch's particles
   // bridge between two records (eq. reuse_bridge): the partner handle's data
   int fd_bridge;           // 1: target (1 - beta) logL_partner + beta logL_own

@@ -513,6 +513,13 @@ struct Model<SMCX_PULSE> {
   __device__ static C make(const double* th, const PopArgs& a, int /*S*/) {
     return pulse_make(th, a.t_start, a.dt);
   }
+  // whether FP32 holds the template (0 times an infinite or NaN factor is NaN)
+  __device__ static bool finite(const C& c) { return isfinite(c.A) && isfinite(c.a) && isfinite(c.fa); }
+  // evaluate the component on every sample
+  __device__ static void widen(C& c) {
+    c.lo = (int)-kSampleBound;
+    c.hi = (int)kSampleBound;
+  }
   // pulses have one tile path (LIN is ignored)
   __device__ static bool chord_ok(const C&, int) { return true; }
   __device__ static void linearize(C&, int) {}
@@ -1195,6 +1202,9 @@ __global__ __launch_bounds__(256) void finalize_kernel(PopArgs a) {
 // particles, K on 0..20, T = 2^17: 241 -> 215 us.
 // (An unbranched path for tiles inside the support spills; four block groups
 // at a time instead of two is three times slower.)
+// Where a component, a candidate or the data are not finite in FP32, every pulse of
+// the particle is taken over all samples: NaN and infinities then reach the sums
+// from outside a candidate's support too.
 
 // Adds one candidate's <r, h> and <h, h> over the tile to the lane's sums;
 // values(fn) calls fn(j, h) for the values of its template.
@@ -1293,14 +1303,22 @@ constexpr int kDeltaBatch = 127;
 // each tile again, and the operations of delta_tiles in their order.
 template <int MODEL, int S>
 __device__ __forceinline__ void delta_tiles_long(const PopArgs& a, typename Model<MODEL>::C* cst, int64_t m0,
-                                              int i, int K, int j_death, bool birth, int lane, int64_t cs,
-                                              int64_t ce, bool split, double bw, double& xb, double& yb,
-                                              double& xd, double& yd) {
+                                              int i, int K, int j_death, bool birth, bool odd, int lane,
+                                              int64_t cs, int64_t ce, bool split, double bw, double& xb,
+                                              double& yb, double& xd, double& yd) {
   using M = Model<MODEL>;
   constexpr int P = M::P;
+  for (int k = lane; k < K; k += 64) odd |= !M::finite(M::make(a.theta + (m0 + k) * P, a, S));
+  if (birth) odd |= !M::finite(M::make(a.theta_birth + (int64_t)i * P, a, S));
+  const bool wide = __any(odd);
+  auto make = [&](const double* th) {
+    typename M::C c = M::make(th, a, S);
+    if (wide) M::widen(c);
+    return c;
+  };
   auto sums = [&](const double* th, int64_t tile, const float (&r)[S], double& x, double& y) {
     wave_sync();
-    if (lane == 0) cst[0] = M::make(th, a, S);
+    if (lane == 0) cst[0] = make(th);
     wave_sync();
     M::template prepare<S>(cst, 1, tile, lane);
     double tx = 0.0, ty = 0.0;
@@ -1318,7 +1336,7 @@ __device__ __forceinline__ void delta_tiles_long(const PopArgs& a, typename Mode
     for (int b0 = 0; b0 < K; b0 += kDeltaBatch) {
       const int n = min(kDeltaBatch, K - b0);
       wave_sync();  // the constants before have been read
-      for (int k = lane; k < n; k += 64) cst[k] = M::make(a.theta + (m0 + b0 + k) * P, a, S);
+      for (int k = lane; k < n; k += 64) cst[k] = make(a.theta + (m0 + b0 + k) * P);
       wave_sync();
       M::template prepare<S>(cst, n, tile, lane);
       for (int k = 0; k < n; ++k) {
@@ -1337,6 +1355,13 @@ __device__ __forceinline__ void delta_tiles_long(const PopArgs& a, typename Mode
 template <int MODEL, int S, bool LONG>
 constexpr int delta_waves_per_simd() {  // what the registers allow without spills
   return LONG ? (S <= 8 ? 7 : 5) : S <= 8 ? (MODEL == SMCX_PULSE ? 8 : 7) : (MODEL == SMCX_PULSE ? 7 : 4);
+}
+
+// The tempering still to apply to an item's sums: under a split the samples after it
+// carry theirs (NaN where that is not finite, which a candidate with no sample there
+// does not show).
+__device__ __forceinline__ double delta_temper(const PopArgs& a, bool split, double bw) {
+  return !split ? bw : (a.split < a.s_hi ? fma(0.0, bw, 1.0) : 1.0);
 }
 
 // One birth/death work item; TILES as pop_item.
@@ -1364,10 +1389,23 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
   const size_t wave_bytes = lds_wave_bytes(MODEL, LONG ? kDeltaBatch : a.k_max, false);
   C* cst = reinterpret_cast<C*>(lds + (size_t)wid * wave_bytes);
   const bool batches = LONG && K > kDeltaBatch;
+  const bool split = a.split > a.s_lo;  // posterior-start bridge target
+  bool odd = a.odd_data != 0;
   if (!batches) {
-    for (int k = lane; k < K; k += 64) cst[k] = M::make(a.theta + (m0 + k) * P, a, S);
-    if (birth && lane == 0) cst[K] = M::make(a.theta_birth + (int64_t)i * P, a, S);
+    auto put = [&](int k, const double* th) {
+      const C c = M::make(th, a, S);
+      if constexpr (MODEL == SMCX_PULSE) odd |= !M::finite(c);
+      cst[k] = c;
+    };
+    for (int k = lane; k < K; k += 64) put(k, a.theta + (m0 + k) * P);
+    if (birth && lane == 0) put(K, a.theta_birth + (int64_t)i * P);
     wave_sync();
+    if constexpr (MODEL == SMCX_PULSE) {
+      if (__any(odd)) {
+        for (int k = lane; k < K + (birth ? 1 : 0); k += 64) M::widen(cst[k]);
+        wave_sync();
+      }
+    }
   }
 
   int64_t cs = a.s_lo + (int64_t)c * a.chunk_len;
@@ -1376,7 +1414,6 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
     cs += (int64_t)wid * 64 * S;
     ce = min(cs + 64 * S, ce);
   }
-  const bool split = a.split > a.s_lo;  // posterior-start bridge target
   const double bw = a.beta ? a.beta[i] : 1.0;
   double xb = 0.0, yb = 0.0, xd = 0.0, yd = 0.0;
   // sinusoids take the exact tile phase here, whatever the components: the
@@ -1384,7 +1421,7 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
   // other components (or candidates) the two calls see
   if constexpr (LONG) {
     if (batches)
-      delta_tiles_long<MODEL, S>(a, cst, m0, i, K, j_death, birth, lane, cs, ce, split, bw, xb, yb, xd, yd);
+      delta_tiles_long<MODEL, S>(a, cst, m0, i, K, j_death, birth, odd, lane, cs, ce, split, bw, xb, yb, xd, yd);
   }
   if (!batches)
     delta_tiles<MODEL, S, MODEL != SMCX_GBSINE>(a, cst, K, j_death, birth, lane, cs, ce, split, bw,
@@ -1420,7 +1457,7 @@ __device__ __forceinline__ void delta_item(const PopArgs& a, int64_t item, int l
   }
   if (lane != 0) return;
   if (z.nch == 1) {
-    const double b = split ? 1.0 : bw;  // tempering still to apply
+    const double b = delta_temper(z, split, bw);
     if (birth) z.dlogl_birth[i] = b * (xb - 0.5 * yb) * z.inv_sigma2;
     if (z.death_idx) z.dlogl_death[i] = j_death < 0 ? 0.0 : -(b * (xd - 0.5 * yd) * z.inv_sigma2);
   } else {
@@ -1470,7 +1507,7 @@ __global__ __launch_bounds__(256) void delta_finalize_kernel(PopArgs a) {
     const double* src = a.part + ((size_t)c * a.N + i) * 4;
     for (int q = 0; q < 4; ++q) s[q] += src[q];
   }
-  const double b = a.split > a.s_lo ? 1.0 : (a.beta ? a.beta[i] : 1.0);
+  const double b = delta_temper(a, a.split > a.s_lo, a.beta ? a.beta[i] : 1.0);
   if (a.theta_birth) a.dlogl_birth[i] = b * (s[0] - 0.5 * s[1]) * a.inv_sigma2;
   if (a.death_idx) {
     const int j = a.death_idx[i];
