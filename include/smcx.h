@@ -358,8 +358,9 @@ int smcx_nuts_reserve(smcx_problem* prob, int32_t max_depth);
  * use_graph != 0 (the graph is rebuilt when any pointer or size argument
  * changes). The host synchronises once per doubling to learn whether any
  * trajectory is still growing.
- * Frequency-domain problems run every trajectory on its own in one launch:
- * no graph (use_graph makes no difference) and no host synchronisation.
+ * Frequency-domain problems run every trajectory on its own in one launch
+ * (one leapfrog step of all together for max_depth = 1): no graph (use_graph
+ * makes no difference) and no host synchronisation.
  *   beta, eps          tempering and leapfrog step size (eps > 0)
  *   max_depth          at most the depth reserved with smcx_nuts_reserve
  *   prior_lo, prior_hi [P] box of the uniform prior, or both NULL
