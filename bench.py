@@ -88,8 +88,8 @@ SLOTS = {(0, "grad"): 10.0, (1, "grad"): 2.75 + 5.5, (0, "fwd"): 4.0, (1, "fwd")
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs, scaled by the same counters' readings for a device copy of
 # known size. Valid only for the kernel source they were taken on (its hash).
-PMC_TRAFFIC = {("gb_grad", "32,16384,1"): {"bytes": 2.3854e+07, "kernels_sha1": "177c0eb9effb22f0"},
-               ("pulse_batch", "64,4096,1"): {"bytes": 1.3485e+07, "kernels_sha1": "177c0eb9effb22f0"}}
+PMC_TRAFFIC = {("gb_grad", "32,16384,1"): {"bytes": 2.3850e+07, "kernels_sha1": "2cf0e6ae6162b9de"},
+               ("pulse_batch", "64,4096,1"): {"bytes": 1.3481e+07, "kernels_sha1": "2cf0e6ae6162b9de"}}
 
 
 def kernels_sha1():
